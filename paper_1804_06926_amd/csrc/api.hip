@@ -29,7 +29,7 @@ struct tc_ctx {
     uint16_t* d_given_chunk = nullptr;    // device [256] caller-chosen tile sizes (tc_profile_choices)
     int grid_override[tcx::NKERNEL] = {0, 0, 0};
     // selector network: float32 master, Adam moments, gradient, bf16 compute copy,
-    // and the per-sample training buffers (allocated on first use)
+    // and the partial gradient sums (allocated on first use)
     float* d_master = nullptr;
     float* d_adam_m = nullptr;
     float* d_adam_v = nullptr;
@@ -41,7 +41,7 @@ struct tc_ctx {
     tcx::MlpCompute* d_cw_tile = nullptr;
     uint8_t* d_learned_tile = nullptr;
     int tile_ready = 0;
-    float* d_acts = nullptr;
+    float* d_grad_rows = nullptr;
     int adam_step = 0;
     // batched counting: a stream for capture when the context's stream is the
     // null stream, and the captured graph of the last batch shape
@@ -253,7 +253,7 @@ tc_status tc_destroy(tc_ctx* ctx) {
         if (ctx->d_group) (void)hipFree(ctx->d_group);
         if (ctx->d_given) (void)hipFree(ctx->d_given);
         if (ctx->d_given_chunk) (void)hipFree(ctx->d_given_chunk);
-        float* bufs[] = {ctx->d_master, ctx->d_adam_m, ctx->d_adam_v, ctx->d_grad, ctx->d_loss, ctx->d_acts};
+        float* bufs[] = {ctx->d_master, ctx->d_adam_m, ctx->d_adam_v, ctx->d_grad, ctx->d_loss, ctx->d_grad_rows};
         for (float* p : bufs)
             if (p) (void)hipFree(p);
         if (ctx->d_cw) (void)hipFree(ctx->d_cw);
@@ -821,23 +821,10 @@ tc_status tc_profile_choices(tc_ctx* ctx, const int32_t* d_edges, int64_t num_ed
     return TC_OK;
 }
 
-static tc_status ensure_acts(tc_ctx* ctx) {
-    if (ctx->d_acts) return TC_OK;
-    const size_t per = 4 * tcx::MLP_H + tcx::MLP_OUT + 1;
-    hipError_t e = hipMalloc((void**)&ctx->d_acts, sizeof(float) * per * tcx::MLP_MAX_BATCH);
+static tc_status ensure_grad_rows(tc_ctx* ctx) {
+    if (ctx->d_grad_rows) return TC_OK;
+    hipError_t e = hipMalloc((void**)&ctx->d_grad_rows, sizeof(float) * (tcx::MLP_NPARAM + 1) * tcx::MLP_GRAD_ROWS);
     return e == hipSuccess ? TC_OK : hip_fail(ctx, e, "selector buffers");
-}
-
-static tcx::MlpActs acts_of(tc_ctx* ctx, int B) {
-    tcx::MlpActs a;
-    float* p = ctx->d_acts;
-    a.h1 = p; p += (size_t)B * tcx::MLP_H;
-    a.h2 = p; p += (size_t)B * tcx::MLP_H;
-    a.dh1 = p; p += (size_t)B * tcx::MLP_H;
-    a.dh2 = p; p += (size_t)B * tcx::MLP_H;
-    a.dz = p; p += (size_t)B * tcx::MLP_OUT;
-    a.loss = p;
-    return a;
 }
 
 tc_status tc_selector_set_params(tc_ctx* ctx, const float* h_params) {
@@ -997,9 +984,9 @@ static tc_status selector_grad(tc_ctx* ctx, const float* d_x, const int32_t* d_l
                                int32_t batch, float* h_loss) {
     if (!ctx || batch < 1 || batch > tcx::MLP_MAX_BATCH || !d_x || !d_labels) return TC_ERR_INVALID_ARG;
     if (!ctx->learned_ready) return arg_fail(ctx, TC_ERR_INVALID_ARG, "no selector parameters set");
-    tc_status st = ensure_acts(ctx);
+    tc_status st = ensure_grad_rows(ctx);
     if (st != TC_OK) return st;
-    tcx::mlp_gradient(ctx->d_cw, d_x, d_labels, d_weights, batch, acts_of(ctx, batch), ctx->d_grad, ctx->d_loss,
+    tcx::mlp_gradient(ctx->d_cw, d_x, d_labels, d_weights, batch, ctx->d_grad_rows, ctx->d_grad, ctx->d_loss,
                       ctx->stream);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && h_loss)

@@ -30,20 +30,14 @@ struct MlpCompute {
     float b3[MLP_OUT];
 };
 
-// Per-sample activations and errors of a training batch (device arrays).
-struct MlpActs {
-    float* h1;    // [B][32]
-    float* h2;    // [B][32]
-    float* dh1;   // [B][32]
-    float* dh2;   // [B][32]
-    float* dz;    // [B][3]
-    float* loss;  // [B]
-};
+// Rows of partial gradient sums of a training batch (MLP_NPARAM + 1 floats each: the
+// parameters, then the loss).
+constexpr int MLP_GRAD_ROWS = 512;
 
 void mlp_cast(const float* master, MlpCompute* cw, hipStream_t s);
 void mlp_forward(const MlpCompute* cw, const float* X, int B, float* logits, hipStream_t s);
-void mlp_gradient(const MlpCompute* cw, const float* X, const int32_t* y, const float* w, int B, const MlpActs& acts,
-                  float* grad, float* loss, hipStream_t s);
+void mlp_gradient(const MlpCompute* cw, const float* X, const int32_t* y, const float* w, int B, float* part,
+                  float* grad, float* loss, hipStream_t s);   // part: MLP_GRAD_ROWS rows
 void mlp_adam(float* master, const float* grad, float* m, float* v, float lr, int step, hipStream_t s);
 void mlp_select(const MlpCompute* cw, Ctrl* ctrl, uint8_t* choice, hipStream_t s);
 void bucket_features_launch(Ctrl* ctrl, hipStream_t s);

@@ -54,6 +54,23 @@ def test_forward_matches_oracle_within_error_bound(tc, B):
     np.testing.assert_array_equal(tc.selector_get_params(), theta)
 
 
+@pytest.mark.parametrize("B", [2, 31, 32, 33, 63, 691, 16384, 16385, 65535, 65536])
+def test_gradient_block_edges(tc, B):
+    """Batches around one round of 32 samples, one round for every block (16384) and the largest batch.
+    A sum passes at most 64 products in a block, 64 blocks in a slice and 8 slices (one rounding each),
+    after about 70 roundings in the layers, so its error is below about 206 * 2^-24 = 1.2e-5 of the sum
+    of absolute terms; 1e-4 of |g| + max|g| leaves a factor of 8 for cancellation between terms."""
+    import torch
+    theta = _params(5 + B)
+    X, y, w = _batch(B, 3 + B)
+    tc.selector_set_params(theta)
+    g, loss = tc.selector_gradient(torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), torch.from_numpy(w).cuda())
+    loss64, g64 = mlp.loss_and_grad(theta, X, y, w)
+    assert abs(loss - loss64) <= 1e-5 * max(1.0, abs(loss64))
+    err = np.abs(g.cpu().numpy().astype(np.float64) - g64)
+    assert np.all(err <= 1e-4 * (np.abs(g64) + np.max(np.abs(g64))) + 1e-7), np.max(err)
+
+
 @pytest.mark.parametrize("B,weighted", [(1, False), (300, True), (4096, True)])
 def test_gradient_matches_oracle(tc, B, weighted):
     """Tolerance: each gradient entry is a sum of B products formed from float32
