@@ -92,7 +92,10 @@ def algorithmic_bytes(tc, d_edges, n, stats):
     Per in-edge e = (u -> v) with a non-empty tail: 8 B (its entry) + 4 B per
     tail element; per tile (v, chunk of in-edges): 16 B of descriptors and
     offsets + 4 B per element of N+(v). The same figure holds for every
-    strategy (each must read the tail and N+(v) at least once).
+    strategy (each must read the tail and N+(v) at least once), except that
+    the bitmap strategy's hub kernel (single-vertex tiles of the 65535
+    top-ranked vertices, from 2^24 pairs and about 2^30 tail elements) reads
+    2 B per element.
     """
     import numpy as np
     rank, off, col = tc.build_csr(d_edges, n)
@@ -111,10 +114,16 @@ def algorithmic_bytes(tc, d_edges, n, stats):
     chunk = np.asarray(stats["bucket_chunk"], dtype=np.int64)[bucket]
     tiles = np.where(bucket != 255, (din + chunk - 1) // np.maximum(chunk, 1), 0)
     out = {}
+    nv, bo = np.asarray(stats["bucket_vertices"], dtype=np.float64), np.asarray(stats["bucket_out_edges"], dtype=np.float64)
+    real = np.arange(256) < 255
+    hub_on = d_edges.shape[0] >= 1 << 24 and (bo[real & (nv > 0)] ** 2 / (2 * nv[real & (nv > 0)])).sum() >= 1 << 30
+    hub = hub_on & (kern == 2) & (np.arange(n) >= n - 65535) & (4 << (bucket >> 4) > chunk)
+    size = np.where(hub, 2, 4)
     ek = kern[col[active]]
+    es = size[col[active]]
     for k, name in enumerate(("merge", "bsearch", "bitmap")):
-        e_bytes = int((8 + 4 * tail[active][ek == k]).sum())
-        t_bytes = int((tiles[kern == k] * (16 + 4 * dplus[kern == k])).sum())
+        e_bytes = int((8 + es[ek == k] * tail[active][ek == k]).sum())
+        t_bytes = int((tiles[kern == k] * (16 + size[kern == k] * dplus[kern == k])).sum())
         out[name] = e_bytes + t_bytes
     S = int((dplus[col]).sum())
     balg = 4 * (m + S) + 16 * m + 8 * (n + 1)   # merge-formulation minimum

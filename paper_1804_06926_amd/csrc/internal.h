@@ -155,4 +155,19 @@ constexpr uint32_t TILE_MULTI = 0x80000000u;
 constexpr int SEG_MAX = 256;          // vertices per multi-vertex tile
 constexpr int SEG_MAX_BITMAP = 32;    // vertices per multi-vertex tile of the bitmap kernel
 
+// The hub kernel (the bitmap strategy for the top-ranked vertices) covers the
+// HUB_SPAN highest ranks, as 16-bit offsets from the first of them; offset
+// HUB_NONE stands for every lower rank.
+constexpr uint32_t HUB_SPAN = 65535u;
+constexpr uint32_t HUB_NONE = 65535u;
+__host__ __device__ inline uint32_t hub_first(uint32_t n) { return n > HUB_SPAN ? n - HUB_SPAN : 0u; }
+// Its tables (device): per bucket the first hub tile, then the tile ranges of
+// the bitmap kernel and of the hub kernel, one per bucket in slot order: the
+// first tile, and the exclusive prefix of the tile counts with the total last.
+struct HubTab {
+    uint32_t first[NBUCKET];          // ~0: the bucket has no hub tile
+    uint32_t rest_tile[NBUCKET], rest_pref[NBUCKET + 1];
+    uint32_t hub_tile[NBUCKET], hub_pref[NBUCKET + 1];
+};
+
 }  // namespace tcx

@@ -37,13 +37,17 @@ struct IsectArgs {
     // list (the full-list and matrix formulations); the bitmap kernel then clips
     // each tail to the window it is testing. Count only.
     uint32_t clip;
+    // the hub kernel's columns (rank - hub_first, HUB_NONE below it; same indexes as
+    // col) and tile ranges, or null: the bitmap kernel then takes all its tiles
+    const uint16_t* col16;
+    const HubTab* hub;
 };
 
 // Blocks of one intersection kernel resident per CU (from the occupancy API);
 // mode: the bitmap kernel's output mode (0 for the edge kernels).
 int isect_blocks_per_cu(int ker, int mode);
 size_t isect_partials_bytes();
-// One intersection kernel over its tile range; per-block partial counts go to
+// One intersection kernel over its tile range (the bitmap strategy: two kernels, when a.hub is set); per-block partial counts go to
 // partials (isect_partials_bytes() of workspace shared by the three kernels).
 void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hipStream_t s);
 // ctrl->total = sum of all partial counts.

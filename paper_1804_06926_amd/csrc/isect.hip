@@ -56,13 +56,42 @@ struct SegsT {
 using Segs = SegsT<SEG_MAX>;
 
 // The next tile for this block after its first (static) one: t0 + the shared
-// counter of kernel ker, which is zero when the launch starts. Called by the
+// counter ker, which is zero when the launch starts. Called by the
 // whole block (barriers); the value is the same in every thread.
+constexpr int HUB_COUNTER = NKERNEL;   // the hub kernel's
 __device__ __forceinline__ uint32_t grab_tile(Ctrl* ctrl, int ker, uint32_t t0, uint32_t* s_tile) {
     __syncthreads();   // every thread has read the previous value
     if (threadIdx.x == 0) *s_tile = t0 + atomicAdd(&ctrl->tile_next[ker], 1u);
     __syncthreads();
     return *s_tile;
+}
+
+// Tile i of a launch whose tiles are not contiguous: ranges of tiles (tile,
+// pref of HubTab), i < pref[NBUCKET].
+struct TileRanges {   // a copy in LDS, for the hub kernel
+    uint32_t tile[NBUCKET], pref[NBUCKET + 1];
+    // Whole block; a barrier follows before use.
+    __device__ void load(const uint32_t* g_tile, const uint32_t* g_pref) {
+        for (uint32_t i = threadIdx.x; i < (uint32_t)NBUCKET; i += blockDim.x) tile[i] = g_tile[i];
+        for (uint32_t i = threadIdx.x; i <= (uint32_t)NBUCKET; i += blockDim.x) pref[i] = g_pref[i];
+    }
+    __device__ uint32_t at(uint32_t i) const {
+        uint32_t r = 0;   // the last range whose prefix is at most i
+#pragma unroll
+        for (uint32_t step = NBUCKET / 2; step > 0; step >>= 1)
+            if (pref[r + step] <= i) r += step;
+        return tile[r] + (i - pref[r]);
+    }
+};
+// The same in global memory, by a whole wave (four prefixes per lane): the bitmap
+// kernel has no LDS left for a copy at six blocks per CU.
+__device__ __forceinline__ uint32_t range_tile(const uint32_t* __restrict__ tile, const uint32_t* __restrict__ pref,
+                                               uint32_t i) {
+    static_assert(NBUCKET == 4 * WAVE, "four prefixes per lane");
+    uint32_t r = 0;   // prefixes at most i (pref[0] = 0 is one)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r += (uint32_t)__popcll(__ballot(pref[k * WAVE + lane_id()] <= i));
+    return tile[r - 1u] + (i - pref[r - 1u]);
 }
 
 // Decode tile t into segments (v, first in-edge, count); returns the count.
@@ -98,11 +127,10 @@ __device__ uint32_t load_tile(const IsectArgs& a, uint32_t t, SegsT<N>& S) {
     return nseg;
 }
 
-__device__ __forceinline__ void edge_done(const IsectArgs& a, uint32_t e, uint32_t v, uint32_t c,
-                                          bool middle = true) {
+__device__ __forceinline__ void edge_done(const IsectArgs& a, uint32_t e, uint32_t v, uint32_t c) {
     if (a.per_edge) a.per_edge[e] = c;
     if (a.support && c) atomicAdd(&a.support[e], c);
-    if (middle && a.per_middle && c) atomicAdd((unsigned long long*)&a.per_middle[v], (unsigned long long)c);
+    if (a.per_middle && c) atomicAdd((unsigned long long*)&a.per_middle[v], (unsigned long long)c);
     if (a.per_vertex && c) {
         atomicAdd((unsigned long long*)&a.per_vertex[a.src[e]], (unsigned long long)c);
         atomicAdd((unsigned long long*)&a.per_vertex[v], (unsigned long long)c);
@@ -168,15 +196,15 @@ __device__ __forceinline__ uint32_t col_at(const uint32_t* col, uint32_t i) {
     return col[i];
 }
 
-// Outputs of a bitmap launch: T only; also per in-edge counts (per-edge or
-// per-middle-vertex outputs); or also gathered per-vertex counts or edge
+// Outputs of a bitmap launch: T only; also per middle vertex (one sum per vertex
+// and tile); also per in-edge counts (per-edge outputs); or also gathered per-vertex counts or edge
 // support (the hits per element of N+(v), for t[w] and the support of edge
 // vw, are gathered in LDS); or the triangle list (the per-entry count is the
 // cursor of the entry's slots). Each mode sizes its LDS to what it uses.
 // BM_CLIP counts only, for tails that are whole rows: each tail and the middle
 // list are cut to the window being tested, and windows holding no element of
 // the middle list are skipped.
-enum { BM_COUNT = 0, BM_ENTRY = 1, BM_GATHER = 2, BM_LIST = 3, BM_CLIP = 4, BM_NMODE = 5 };
+enum { BM_COUNT = 0, BM_ENTRY = 1, BM_GATHER = 2, BM_LIST = 3, BM_CLIP = 4, BM_MIDDLE = 5, BM_NMODE = 6 };
 
 constexpr int EH = CHUNK_MAX / IS_NT;   // entries of a vertex per thread
 
@@ -220,19 +248,19 @@ __device__ __forceinline__ uint32_t wave_first_at_least(const uint32_t* col, uin
 // entries) and later owns the table slots with the same indexes, so each
 // phase needs one block scan. Returns the entries kept; nl = long entries,
 // L = total items. Whole block; contains barriers.
-template <bool CNT>
-__device__ __forceinline__ uint32_t entry_table(const uint32_t (&st_h)[EH], const uint32_t (&len_h)[EH],
+template <int NTB, int EPT, bool CNT>
+__device__ __forceinline__ uint32_t entry_table(const uint32_t (&st_h)[EPT], const uint32_t (&len_h)[EPT],
                                                 uint32_t* s_pref, uint32_t* s_base, uint32_t* s_cnt,
                                                 uint32_t* scratch, uint32_t& nl, uint32_t& L) {
     uint32_t f = 0;   // long entries in the high half, non-empty short ones in the low half
 #pragma unroll
-    for (int h = 0; h < EH; ++h) f += len_h[h] >= LONG_TAIL ? 0x10000u : (len_h[h] ? 1u : 0u);
+    for (int h = 0; h < EPT; ++h) f += len_h[h] >= LONG_TAIL ? 0x10000u : (len_h[h] ? 1u : 0u);
     uint32_t total;
-    const uint32_t ex = block_exclusive_scan<IS_NT>(f, scratch, &total);
+    const uint32_t ex = block_exclusive_scan<NTB>(f, scratch, &total);
     const uint32_t cl = total >> 16, cs = total & 0xFFFFu;
     uint32_t pl = ex >> 16, ps = cl + (ex & 0xFFFFu);
 #pragma unroll
-    for (int h = 0; h < EH; ++h) {   // lengths and starts in table order
+    for (int h = 0; h < EPT; ++h) {   // lengths and starts in table order
         if (!len_h[h]) continue;
         const uint32_t pos = len_h[h] >= LONG_TAIL ? pl++ : ps++;
         s_pref[pos] = len_h[h];
@@ -241,19 +269,19 @@ __device__ __forceinline__ uint32_t entry_table(const uint32_t (&st_h)[EH], cons
     }
     __syncthreads();
     const uint32_t nt = cl + cs;
-    uint32_t len[EH], st[EH], sum = 0;
+    uint32_t len[EPT], st[EPT], sum = 0;
 #pragma unroll
-    for (int h = 0; h < EH; ++h) {   // this thread's slots, rewritten in place below
-        const uint32_t k = EH * threadIdx.x + (uint32_t)h;
+    for (int h = 0; h < EPT; ++h) {   // this thread's slots, rewritten in place below
+        const uint32_t k = EPT * threadIdx.x + (uint32_t)h;
         len[h] = k < nt ? s_pref[k] : 0u;
         st[h] = k < nt ? s_base[k] : 0u;
         sum += len[h];
     }
     uint32_t items;
-    uint32_t run = block_exclusive_scan<IS_NT>(sum, scratch, &items);
+    uint32_t run = block_exclusive_scan<NTB>(sum, scratch, &items);
 #pragma unroll
-    for (int h = 0; h < EH; ++h) {
-        const uint32_t k = EH * threadIdx.x + (uint32_t)h;
+    for (int h = 0; h < EPT; ++h) {
+        const uint32_t k = EPT * threadIdx.x + (uint32_t)h;
         if (k < nt) {
             s_pref[k] = run;
             s_base[k] = st[h] - run;
@@ -272,7 +300,7 @@ template <int MODE, bool NARROW>
 __global__ __launch_bounds__(IS_NT, MODE == BM_GATHER ? 1 : 6) void k_isect_bitmap(IsectArgs a, uint64_t* partials) {
     constexpr bool GATHER = MODE == BM_GATHER;
     constexpr bool CLIP = MODE == BM_CLIP;
-    constexpr bool need_cnt = MODE != BM_COUNT && !CLIP;
+    constexpr bool need_cnt = MODE != BM_COUNT && MODE != BM_MIDDLE && !CLIP;
     __shared__ uint32_t s_nv[GATHER ? NV_MAX : 1];
     __shared__ uint32_t s_wc[GATHER ? NV_MAX : 1];
     __shared__ uint32_t bm[BM_WORDS + 1];        // + one always-zero word for out-of-window positions
@@ -286,15 +314,21 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_GATHER ? 1 : 6) void k_isect_bitm
     for (int i = threadIdx.x; i < (IS_NT / WAVE) * UNROLL * WAVE; i += IS_NT) (&s_flag[0][0][0])[i] = 0;
     uint64_t acc = 0;
     __shared__ uint32_t s_tile;
-    const uint32_t t_begin = a.ctrl->tile_begin[KER_BITMAP], t_end = a.ctrl->tile_begin[KER_BITMAP + 1];
-    for (uint32_t t = t_begin + blockIdx.x; t < t_end; t = grab_tile(a.ctrl, KER_BITMAP, t_begin + gridDim.x, &s_tile)) {
-        const uint32_t nseg = load_tile(a, t, S);
+    const uint32_t t_begin = a.ctrl->tile_begin[KER_BITMAP];
+    uint32_t ntile = a.ctrl->tile_begin[KER_BITMAP + 1] - t_begin;
+    // with the hub kernel beside it, this one takes the tiles that are left
+    constexpr bool RANGES = MODE == BM_COUNT || MODE == BM_MIDDLE;
+    const bool ranges = RANGES && a.hub && a.hub->hub_pref[NBUCKET] != 0;
+    if (ranges) ntile = a.hub->rest_pref[NBUCKET];
+    for (uint32_t i = blockIdx.x; i < ntile; i = grab_tile(a.ctrl, KER_BITMAP, gridDim.x, &s_tile)) {
+        const uint32_t nseg = load_tile(a, ranges ? range_tile(a.hub->rest_tile, a.hub->rest_pref, i) : t_begin + i, S);
         for (uint32_t sg = 0; sg < nseg; ++sg) {
             const uint32_t v = S.v[sg];
             const uint32_t e0 = S.e0[sg];
             const uint32_t ne = S.pref[sg + 1] - S.pref[sg];
             const uint32_t b0 = a.off[v], b1 = a.off[v + 1];
             const uint32_t nb = b1 - b0;
+            uint32_t seg_sum = 0;   // BM_MIDDLE: this thread's hits for v (below 2^32: a tile's tail elements)
             // the vertex's entries (ne <= CHUNK_MAX = EH * IS_NT: EH consecutive ones per thread)
             uint32_t st_h[EH], len_h[EH];
 #pragma unroll
@@ -309,7 +343,7 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_GATHER ? 1 : 6) void k_isect_bitm
             }
             // the table: once per vertex, or per window when the tails are clipped
             uint32_t nt = 0, nl = 0, L = 0;
-            if (!CLIP) nt = entry_table<need_cnt>(st_h, len_h, s_pref, s_base, s_cnt, S.scratch, nl, L);
+            if (!CLIP) nt = entry_table<IS_NT, EH, need_cnt>(st_h, len_h, s_pref, s_base, s_cnt, S.scratch, nl, L);
             const uint32_t lo = a.col[b0], hi = a.col[b1 - 1];
             const uint32_t base = lo & ~31u;
             const uint32_t nwin = (hi - base) / BM_BITS + 1;
@@ -356,7 +390,7 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_GATHER ? 1 : 6) void k_isect_bitm
                         st_h[h] = e2;
                         len_h[h] = e - e2;
                     }
-                    nt = entry_table<false>(cs_h, cl_h, s_pref, s_base, s_cnt, S.scratch, nl, L);
+                    nt = entry_table<IS_NT, EH, false>(cs_h, cl_h, s_pref, s_base, s_cnt, S.scratch, nl, L);
                 }
                 for (uint32_t j = j0 + threadIdx.x; j < j1; j += IS_NT) {
                     const uint32_t x = a.col[b0 + j] - wlo;
@@ -469,6 +503,7 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_GATHER ? 1 : 6) void k_isect_bitm
 #pragma unroll
                         for (int j = 0; j < UNROLL; ++j) hits += __builtin_amdgcn_ubfe(wd[j], xs[j], 1u);
                         acc += hits;
+                        if (MODE == BM_MIDDLE) seg_sum += hits;
                         if (!need_cnt) continue;
 #pragma unroll
                         for (int j = 0; j < UNROLL; ++j) {
@@ -517,22 +552,206 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_GATHER ? 1 : 6) void k_isect_bitm
                 }
             }
             if (need_cnt) {
-                uint32_t seg_hits = 0;
-                for (uint32_t k = threadIdx.x; k < nt; k += IS_NT) {
-                    edge_done(a, s_base[k] + s_pref[k] - 1u, v, s_cnt[k], false);
-                    seg_hits += s_cnt[k];
-                }
-                if (a.per_middle) {   // one update per vertex and tile
-                    uint32_t total;
-                    (void)block_exclusive_scan<IS_NT>(seg_hits, S.scratch, &total);
-                    if (threadIdx.x == 0 && total)
-                        atomicAdd((unsigned long long*)&a.per_middle[v], (unsigned long long)total);
-                }
+                for (uint32_t k = threadIdx.x; k < nt; k += IS_NT)
+                    edge_done(a, s_base[k] + s_pref[k] - 1u, v, s_cnt[k]);
+            }
+            if (MODE == BM_MIDDLE) {   // one update per vertex and tile
+                uint32_t total;
+                (void)block_exclusive_scan<IS_NT>(seg_sum, S.scratch, &total);
+                if (threadIdx.x == 0 && total)
+                    atomicAdd((unsigned long long*)&a.per_middle[v], (unsigned long long)total);
             }
             __syncthreads();
         }
     }
     block_partial(acc, partials);
+}
+
+// ------------------------------------------------------------------ hub kernel
+// The bitmap strategy for single-vertex tiles whose middle vertex is one of the
+// HUB_SPAN top-ranked ones (counts in all, or per middle vertex), where a skewed
+// graph has most of its work (R-MAT 24: 84% of the tail elements). The tail of
+// an in-edge (u -> v) holds only ranks above v, so here it lies inside those
+// ranks: it is read from 16-bit columns, half the bytes, and N+(v) is a byte
+// per rank in LDS (64 KB), so that an element costs a field extract, an LDS byte and
+// half an add instead of a word address, a bit test and an add.
+// A wave takes a share of the tile's in-edges, one per lane, orders them by
+// length, and eight lanes walk one tail together, a 16-byte chunk per lane and
+// step: eight tails of similar length per wave, HB_D steps of loads in flight,
+// and no item table, scan or barrier between the tile's set-up and its end. What a
+// first or last chunk holds beside the tail is turned into HUB_NONE by mask
+// words from an LDS table. The next tile's descriptor and in-edges are loaded
+// while the current one is walked. Bound: the line traffic of the tails beyond
+// L2: 91 GB of counted traffic at R-MAT 24, 7.4 TB/s. Measured there: this
+// kernel and the bitmap kernel for the remaining tiles 12.2 + 9.5 ms, the bitmap kernel
+// alone 30.1 ms; R-MAT 20 (tiles too short for the set-up to vanish) 0.65 + 0.19
+// against 0.89 ms. Steps in flight: 3 and 4 alike, 6 and 8 slower (23.2, 36.5 ms with the
+// bitmap kernel against 22.6: registers); 1024 threads with two steps 1% faster at
+// R-MAT 24 and 1% slower on a batch of Chung-Lu graphs.
+constexpr int HB_NT = 512;                // two blocks fit a CU by LDS
+constexpr int HB_W = HB_NT / WAVE;
+constexpr int HB_D = 3;                   // steps in flight
+constexpr uint32_t HB_L = 8;              // lanes per tail
+constexpr uint32_t HB_R = WAVE / HB_L;    // tails walked together by a wave
+constexpr uint32_t HB_E = 8;              // elements per chunk
+constexpr int HB_PARTIAL0 = 3072;         // partial slots of the bitmap kernel's share from here on
+static_assert(CHUNK_MAX <= HB_NT, "one in-edge per lane");
+
+// Order of magnitude of a step count: 0, 1, 2, 3, then two classes per doubling, at most HB_CLS - 1.
+constexpr int HB_CLS = 12;
+__device__ __forceinline__ uint32_t step_class(uint32_t steps) {
+    if (steps < 4u) return steps;
+    const uint32_t l = (uint32_t)floor_log2(steps);
+    const uint32_t c = 2u * l + ((steps >> (l - 1u)) & 1u);
+    return c < (uint32_t)HB_CLS ? c : (uint32_t)HB_CLS - 1u;
+}
+
+struct HubMasks {   // k first / last elements of a chunk set to ones
+    uint4 head[HB_E + 1], tail[HB_E + 1];
+};
+
+// Elements of this wave's tails that the map holds: S, E = start and end of
+// the lane's tail in the 16-bit columns (empty: S >= E).
+__device__ __forceinline__ uint32_t walk_tails(const uint4* __restrict__ chunks, uint32_t S, uint32_t E,
+                                               const uint8_t* map, const HubMasks& M) {
+    const uint32_t ln = (uint32_t)lane_id(), gl = ln % HB_L, gi = ln / HB_L;
+    // tails in order of length (descending classes), empty ones last
+    const uint32_t nch = S < E ? (E - 1u) / HB_E + 1u - S / HB_E : 0u;
+    const uint32_t cls = step_class((nch + HB_L - 1) / HB_L);
+    uint32_t pos = 0, base = 0, live = 0;
+#pragma unroll
+    for (int c = HB_CLS - 1; c >= 0; --c) {
+        const uint64_t B = __ballot(cls == (uint32_t)c);
+        const uint32_t below =
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(B >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)B, 0u));
+        if (cls == (uint32_t)c) pos = base + below;
+        if (c == 0) live = base;
+        base += (uint32_t)__popcll(B);
+    }
+    S = (uint32_t)__builtin_amdgcn_ds_permute((int)(pos * 4u), (int)S);
+    E = (uint32_t)__builtin_amdgcn_ds_permute((int)(pos * 4u), (int)E);
+    const uint32_t rounds = (live + HB_R - 1) / HB_R;
+    // one cursor per lane over (round, chunk); all lanes advance together
+    uint32_t r = 0, s = 0, e = 0, c = 0, c1 = 0, issued = 0, hits = 0;
+    auto fetch = [&]() {
+        const int from = (int)(((r * HB_R + gi) & (WAVE - 1)) * 4u);
+        s = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)S);
+        e = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)E);
+        c = s / HB_E + gl;
+        c1 = (r < rounds && s < e) ? (e - 1u) / HB_E + 1u : 0u;
+    };
+    uint4 x[HB_D];
+    uint32_t hk[HB_D], tk[HB_D];
+    auto issue = [&](int q) {
+        const bool on = c < c1;
+        x[q] = chunks[on ? c : 0u];   // unconditional: lanes without a chunk read a valid one
+        const int h = (int)(s - c * HB_E), t = (int)(c * HB_E + HB_E - e);
+        hk[q] = on ? (uint32_t)(h < 0 ? 0 : h) : HB_E;
+        tk[q] = on ? (uint32_t)(t < 0 ? 0 : t) : 0u;
+        if (r < rounds) ++issued;
+        if (__ballot(c + HB_L < c1)) c += HB_L;
+        else { ++r; fetch(); }
+    };
+    fetch();
+#pragma unroll
+    for (int q = 0; q < HB_D; ++q) issue(q);
+    for (uint32_t done = 0; done < issued; done += HB_D) {
+#pragma unroll
+        for (int q = 0; q < HB_D; ++q) {
+            const uint4 h = M.head[hk[q]], t = M.tail[tk[q]];
+            const uint32_t w[4] = {x[q].x | h.x | t.x, x[q].y | h.y | t.y, x[q].z | h.z | t.z, x[q].w | h.w | t.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) hits += (uint32_t)map[w[k] & 0xFFFFu] + (uint32_t)map[w[k] >> 16];
+            issue(q);
+        }
+    }
+    return hits;
+}
+
+template <bool MIDDLE>
+__global__ __launch_bounds__(HB_NT, 2 * HB_W / 4) void k_isect_hub(IsectArgs a, uint64_t* partials) {
+    __shared__ __align__(16) uint8_t map[HUB_SPAN + 1];   // map[HUB_NONE] stays zero
+    __shared__ HubMasks M;
+    __shared__ TileRanges R;
+    __shared__ uint32_t s_tile;
+    __shared__ uint64_t red[HB_W];
+    if (a.hub->hub_pref[NBUCKET] == 0) {   // no tile: not worth the set-up
+        if (threadIdx.x == 0) partials[blockIdx.x] = 0;
+        return;
+    }
+    R.load(a.hub->hub_tile, a.hub->hub_pref);
+    for (uint32_t i = threadIdx.x; i < (HUB_SPAN + 1) / 16; i += HB_NT) ((uint4*)map)[i] = make_uint4(0, 0, 0, 0);
+    if (threadIdx.x <= HB_E) {
+        const uint32_t k = threadIdx.x;
+        uint32_t h[4], t[4];
+        for (uint32_t q = 0; q < 4; ++q) {
+            h[q] = (2 * q < k ? 0xFFFFu : 0u) | (2 * q + 1 < k ? 0xFFFF0000u : 0u);
+            t[q] = (2 * q + k >= HB_E ? 0xFFFFu : 0u) | (2 * q + 1 + k >= HB_E ? 0xFFFF0000u : 0u);
+        }
+        M.head[k] = make_uint4(h[0], h[1], h[2], h[3]);
+        M.tail[k] = make_uint4(t[0], t[1], t[2], t[3]);
+    }
+    __syncthreads();
+    const uint32_t wv = (uint32_t)wave_id(), ln = (uint32_t)lane_id();
+    const uint32_t ntile = R.pref[NBUCKET];
+    uint64_t acc = 0;
+    // this lane's in-edge of tile d: the wave's share is a contiguous range
+    auto entry_of = [&](const uint4& d) -> uint64_t {
+        const uint32_t lo = d.z * wv / HB_W, hi = d.z * (wv + 1u) / HB_W;
+        return lo + ln < hi ? a.csc[d.y + lo + ln] : 0ull;   // tail start | tail end << 32; an empty tail
+    };
+    uint32_t i = blockIdx.x;
+    uint4 d = make_uint4(0, 0, 0, 0);
+    uint32_t b0 = 0, b1 = 0;
+    uint64_t ent = 0;
+    if (i < ntile) {
+        d = a.tiles[R.at(i)];   // {v, first in-edge, in-edges, 0}
+        ent = entry_of(d);
+        b0 = a.off[d.x];
+        b1 = a.off[d.x + 1];
+    }
+    while (i < ntile) {
+        for (uint32_t j = b0 + threadIdx.x; j < b1; j += HB_NT) map[a.col16[j]] = 1;
+        // the next tile, in flight during this one
+        const uint32_t inext = grab_tile(a.ctrl, HUB_COUNTER, gridDim.x, &s_tile);   // barriers: the map is complete
+        uint4 dn = d;
+        uint64_t ent_n = 0;
+        uint32_t b0n = 0, b1n = 0;
+        if (inext < ntile) {
+            dn = a.tiles[R.at(inext)];
+            ent_n = entry_of(dn);
+            b0n = a.off[dn.x];
+            b1n = a.off[dn.x + 1];
+        }
+        const uint32_t hits = walk_tails((const uint4*)a.col16, (uint32_t)ent, (uint32_t)(ent >> 32), map, M);
+        acc += hits;
+        if (MIDDLE) {   // one update per tile
+            const uint64_t t = wave_sum_u64(hits);
+            if (ln == 0) red[wv] = t;
+        }
+        __syncthreads();   // the map has been read
+        for (uint32_t j = b0 + threadIdx.x; j < b1; j += HB_NT) map[a.col16[j]] = 0;
+        __syncthreads();   // cleared before the next list is set
+        if (MIDDLE && threadIdx.x == 0) {
+            uint64_t t = 0;
+            for (int q = 0; q < HB_W; ++q) t += red[q];
+            if (t) atomicAdd((unsigned long long*)&a.per_middle[d.x], (unsigned long long)t);
+        }
+        i = inext;
+        d = dn;
+        ent = ent_n;
+        b0 = b0n;
+        b1 = b1n;
+    }
+    acc = wave_sum_u64(acc);
+    __syncthreads();
+    if (ln == 0) red[wv] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t t = 0;
+        for (int q = 0; q < HB_W; ++q) t += red[q];
+        partials[blockIdx.x] = t;
+    }
 }
 
 // ------------------------------------------------------------------ shared helpers for edge-centric kernels
@@ -753,9 +972,9 @@ static int num_cu() {
 
 // Persistent grids: as many blocks as the CUs hold at once (LDS and registers
 // decide), so that no block starts late and stretches the tail.
-static int resident_blocks(const void* fn) {
+static int resident_blocks(const void* fn, int threads = IS_NT) {
     int b = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, fn, IS_NT, 0) != hipSuccess || b <= 0) b = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, fn, threads, 0) != hipSuccess || b <= 0) b = 1;
     return b;
 }
 
@@ -763,7 +982,8 @@ static int bitmap_mode(const IsectArgs& a) {
     if (a.clip) return BM_CLIP;   // whole-row tails: counts only
     if (a.list_out) return BM_LIST;
     if (a.per_vertex || a.support) return BM_GATHER;
-    if (a.per_edge || a.per_middle) return BM_ENTRY;
+    if (a.per_edge) return BM_ENTRY;
+    if (a.per_middle) return BM_MIDDLE;
     return BM_COUNT;
 }
 
@@ -775,6 +995,8 @@ static const void* bitmap_fn(int mode, bool narrow) {
                                       : (const void*)k_isect_bitmap<BM_GATHER, false>;
         case BM_ENTRY: return narrow ? (const void*)k_isect_bitmap<BM_ENTRY, true>
                                      : (const void*)k_isect_bitmap<BM_ENTRY, false>;
+        case BM_MIDDLE: return narrow ? (const void*)k_isect_bitmap<BM_MIDDLE, true>
+                                      : (const void*)k_isect_bitmap<BM_MIDDLE, false>;
         case BM_CLIP: return narrow ? (const void*)k_isect_bitmap<BM_CLIP, true>
                                     : (const void*)k_isect_bitmap<BM_CLIP, false>;
         default: return narrow ? (const void*)k_isect_bitmap<BM_COUNT, true>
@@ -799,9 +1021,21 @@ size_t isect_partials_bytes() { return sizeof(uint64_t) * NKERNEL * PARTIALS_PER
 void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hipStream_t s) {
     const int mode = ker == KER_BITMAP ? bitmap_mode(a) : 0;
     if (grid <= 0) grid = num_cu() * isect_blocks_per_cu(ker, mode);
-    if (grid > PARTIALS_PER_KERNEL) grid = PARTIALS_PER_KERNEL;
+    const bool hub = ker == KER_BITMAP && a.hub;
+    const int cap = hub ? HB_PARTIAL0 : PARTIALS_PER_KERNEL;
+    if (grid > cap) grid = cap;
     uint64_t* p = partials + (size_t)ker * PARTIALS_PER_KERNEL;
     fill_u64(p, 0ull, PARTIALS_PER_KERNEL, s);
+    if (hub) {
+        static int per_cu = 0;
+        if (!per_cu) per_cu = resident_blocks((const void*)k_isect_hub<false>, HB_NT);
+        int hg = num_cu() * per_cu;
+        if (hg > PARTIALS_PER_KERNEL - HB_PARTIAL0) hg = PARTIALS_PER_KERNEL - HB_PARTIAL0;
+        if (a.per_middle)
+            hipLaunchKernelGGL(k_isect_hub<true>, dim3(hg), dim3(HB_NT), 0, s, a, p + HB_PARTIAL0);
+        else
+            hipLaunchKernelGGL(k_isect_hub<false>, dim3(hg), dim3(HB_NT), 0, s, a, p + HB_PARTIAL0);
+    }
     switch (ker) {
         case KER_MERGE: hipLaunchKernelGGL(k_isect_edges<true>, dim3(grid), dim3(IS_NT), 0, s, a, p); break;
         case KER_BSEARCH: hipLaunchKernelGGL(k_isect_edges<false>, dim3(grid), dim3(IS_NT), 0, s, a, p); break;
@@ -816,6 +1050,9 @@ void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hip
             } else if (mode == BM_CLIP) {
                 if (nw) hipLaunchKernelGGL((k_isect_bitmap<BM_CLIP, true>), dim3(grid), dim3(IS_NT), 0, s, a, p);
                 else hipLaunchKernelGGL((k_isect_bitmap<BM_CLIP, false>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            } else if (mode == BM_MIDDLE) {
+                if (nw) hipLaunchKernelGGL((k_isect_bitmap<BM_MIDDLE, true>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+                else hipLaunchKernelGGL((k_isect_bitmap<BM_MIDDLE, false>), dim3(grid), dim3(IS_NT), 0, s, a, p);
             } else if (mode == BM_ENTRY) {
                 if (nw) hipLaunchKernelGGL((k_isect_bitmap<BM_ENTRY, true>), dim3(grid), dim3(IS_NT), 0, s, a, p);
                 else hipLaunchKernelGGL((k_isect_bitmap<BM_ENTRY, false>), dim3(grid), dim3(IS_NT), 0, s, a, p);

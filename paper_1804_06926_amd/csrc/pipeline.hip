@@ -671,9 +671,11 @@ constexpr unsigned long long EDGE_TILES = 512;
 __global__ __launch_bounds__(NBUCKET) void k_select(Ctrl* ctrl, int mode, const uint8_t* __restrict__ learned,
                                                     const uint8_t* __restrict__ learned_tile,
                                                     const uint16_t* __restrict__ chunk_override,
-                                                    const uint8_t* __restrict__ group_override, int whole_rows) {
+                                                    const uint8_t* __restrict__ group_override, int whole_rows,
+                                                    HubTab* __restrict__ hub) {
     __shared__ uint32_t s_key[NBUCKET];
     const int b = threadIdx.x;
+    if (hub) hub->first[b] = ~0u;   // set by k_emit_tiles
     int ch;
     if (mode == SEL_FORCE_MERGE) ch = KER_MERGE;
     else if (mode == SEL_FORCE_BSEARCH) ch = KER_BSEARCH;
@@ -786,7 +788,8 @@ __global__ __launch_bounds__(NT) void k_emit_tiles(const uint32_t* __restrict__ 
                                                    const uint8_t* __restrict__ vbucket,
                                                    const uint32_t* __restrict__ inoff,
                                                    const uint32_t* __restrict__ tstart, int32_t n, Ctrl* ctrl,
-                                                   uint4* __restrict__ tiles, uint64_t tile_cap) {
+                                                   uint4* __restrict__ tiles, uint64_t tile_cap,
+                                                   HubTab* __restrict__ hub) {
     for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) {
         const uint32_t b = vbucket[vlist[i]];
         const int kk = b == BUCKET_NONE ? NKERNEL : ctrl->choice[b];
@@ -805,6 +808,10 @@ __global__ __launch_bounds__(NT) void k_emit_tiles(const uint32_t* __restrict__ 
                 const uint32_t v = vlist[i];
                 const uint32_t K = ctrl->chunk[b];
                 const uint32_t e_beg = inoff[v], e_end = inoff[v + 1];
+                // ranks ascend within a bucket, so its hub tiles are a suffix of its tiles
+                if (hub && kk == KER_BITMAP && v >= hub_first((uint32_t)n) &&
+                    ((uint32_t)i == ctrl->bstart[b] || vlist[i - 1] < hub_first((uint32_t)n)))
+                    hub->first[b] = t0;
                 for (uint32_t t = t0; t < t1 && t < tile_cap; ++t) {
                     const uint32_t e0 = e_beg + (t - t0) * K;
                     tiles[t] = make_uint4(v, e0, (e0 + K < e_end ? e0 + K : e_end) - e0, 0u);
@@ -816,6 +823,70 @@ __global__ __launch_bounds__(NT) void k_emit_tiles(const uint32_t* __restrict__ 
             for (int k = kk + 1; k <= NKERNEL; ++k) ctrl->tile_begin[k] = tstart[n];
             ctrl->ntiles = tstart[n];
         }
+    }
+}
+
+// Tile ranges of the bitmap kernel and of the hub kernel, per bucket in slot
+// order (one thread per slot). The hub kernel gets tiles on graphs with about
+// HUB_MIN_TAILS tail elements or more: its columns, its launch and its longer
+// set-up per tile cost 50 us and more, which it makes up for around there (R-MAT
+// 20, 1.2e9 tail elements: 2.69 -> 2.66 ms; R-MAT 21, 3e9: 5.52 -> 5.27 ms; Chung-Lu of 40
+// million pairs, 0.5e9: 6.99 ms without, 7.02 ms with it).
+constexpr uint64_t HUB_MIN_TAILS = 1ull << 30;
+__global__ __launch_bounds__(NBUCKET) void k_hub_ranges(const Ctrl* ctrl, const uint32_t* __restrict__ tstart,
+                                                        HubTab* __restrict__ hub) {
+    __shared__ uint32_t s_bucket[NBUCKET];
+    __shared__ uint32_t scratch[NBUCKET / WAVE];
+    const uint32_t r = threadIdx.x;
+    s_bucket[ctrl->slot[r]] = r;
+    __syncthreads();
+    const uint32_t b = s_bucket[r];
+    // tail elements of the graph, about: sum over u of d+(u)^2 / 2 from the buckets' means
+    const uint64_t nv = b != (uint32_t)BUCKET_NONE ? ctrl->bucket_nv[b] : 0u;
+    const double out = nv ? (double)ctrl->bucket_out[b] : 0.0;
+    __shared__ uint64_t scratch64[NBUCKET / WAVE];
+    uint64_t tails;
+    (void)block_exclusive_scan<NBUCKET>((uint64_t)(nv ? 0.5 * out * out / (double)nv : 0.0), scratch64, &tails);
+    const bool use = tails >= HUB_MIN_TAILS;   // the same in every thread
+    uint32_t t0 = 0, t1 = 0, h = 0;
+    if (nv && ctrl->choice[b] == KER_BITMAP) {
+        t0 = tstart[ctrl->bstart[b]];
+        t1 = tstart[ctrl->bend[b]];
+        h = use && hub->first[b] != ~0u ? hub->first[b] : t1;
+    }
+    uint32_t rest, hubs;
+    const uint32_t pr = block_exclusive_scan<NBUCKET>(h - t0, scratch, &rest);
+    const uint32_t ph = block_exclusive_scan<NBUCKET>(t1 - h, scratch, &hubs);
+    hub->rest_tile[r] = t0;
+    hub->rest_pref[r] = pr;
+    hub->hub_tile[r] = h;
+    hub->hub_pref[r] = ph;
+    if (r == 0) {
+        hub->rest_pref[NBUCKET] = rest;
+        hub->hub_pref[NBUCKET] = hubs;
+    }
+}
+
+// The hub kernel's 16-bit columns; left alone when there is no hub tile.
+// Eight columns per thread: two 16-byte loads, one 16-byte store (m is below
+// the capacity by at least the last group's padding: see hub_usable).
+__global__ __launch_bounds__(NT) void k_col16(const uint32_t* __restrict__ col, const Ctrl* ctrl, uint32_t base,
+                                              const HubTab* __restrict__ hub, uint16_t* __restrict__ out) {
+    if (hub->hub_pref[NBUCKET] == 0) return;
+    const uint64_t m = ctrl->m;
+    for (uint64_t i = ((uint64_t)blockIdx.x * NT + threadIdx.x) * 8; i < m; i += (uint64_t)gridDim.x * NT * 8) {
+        uint32_t x[8];
+        if (i + 8 <= m) {
+            const uint4 p = *(const uint4*)(col + i), q = *(const uint4*)(col + i + 4);
+            x[0] = p.x; x[1] = p.y; x[2] = p.z; x[3] = p.w;
+            x[4] = q.x; x[5] = q.y; x[6] = q.z; x[7] = q.w;
+        } else {
+            for (int k = 0; k < 8; ++k) x[k] = i + k < m ? col[i + k] : 0u;
+        }
+        uint32_t y[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) y[k] = x[k] >= base ? x[k] - base : HUB_NONE;
+        *(uint4*)(out + i) = make_uint4(y[0] | y[1] << 16, y[2] | y[3] << 16, y[4] | y[5] << 16, y[6] | y[7] << 16);
     }
 }
 
@@ -1016,6 +1087,8 @@ static IsectArgs isect_args(const RunArgs& r, const Layout& L, uint64_t* csc) {
     ia.inv = (const uint32_t*)(ws + L.inv);
     ia.col_narrow = (sym ? 2 * r.E : r.E) < ((int64_t)1 << 30) ? 1u : 0u;   // m <= E
     ia.clip = r.formulation != FORM_FILTERED ? 1u : 0u;
+    ia.col16 = nullptr;
+    ia.hub = nullptr;
     return ia;
 }
 
@@ -1032,9 +1105,42 @@ static uint64_t* csc_of(const RunArgs& r, const Layout& L) {
     return keys_in_sorted == (r.formulation == FORM_FILTERED) ? other : sorted;
 }
 
+// The hub kernel counts (in all, or per middle vertex) on the filtered graph.
+// Its 16-bit columns take the key buffer that the in-edge sort left free, 8 bytes
+// per pair against 2 and a last group of eight. From HUB_MIN_PAIRS on: the
+// preparing kernels and the extra launch cost 25 to 35 us on smaller graphs and
+// gain nothing there (R-MAT 16: 522 us without, 553 us with them; R-MAT 19: 1439 and 1476 us).
+constexpr int64_t HUB_MIN_PAIRS = 1 << 24;
+static bool hub_usable(const RunArgs& r) {
+    return r.formulation == FORM_FILTERED && r.E >= HUB_MIN_PAIRS && !r.per_vertex && !r.clustering &&
+           !r.per_edge_counts && !r.support && !r.list_out;
+}
+
+// Its tables take the degree count's bucket starts, dead since the degree stage.
+static HubTab* hub_tab(const RunArgs& r, const Layout& L) {
+    static_assert(sizeof(HubTab) <= 4 * ((1u << DEG_MAX_BUCKET_BITS) + 4), "hub tables fit the bucket starts");
+    return hub_usable(r) ? (HubTab*)((char*)r.ws + L.bstart) : nullptr;
+}
+
+// Fills the tables and the columns (after the tiles) and points ia at them.
+static void prepare_hub(const RunArgs& r, const Layout& L, const uint64_t* csc, IsectArgs& ia) {
+    HubTab* hub = hub_tab(r, L);
+    if (!hub) return;
+    char* ws = (char*)r.ws;
+    uint16_t* col16 = (uint16_t*)(csc == (const uint64_t*)(ws + L.keysA) ? ws + L.keysB : ws + L.keysA);
+    hipLaunchKernelGGL(k_hub_ranges, dim3(1), dim3(NBUCKET), 0, r.stream, ia.ctrl, (const uint32_t*)(ws + L.tstart),
+                       hub);
+    hipLaunchKernelGGL(k_col16, dim3(grid_for((size_t)r.E / 8 + 1)), dim3(NT), 0, r.stream, ia.col, ia.ctrl,
+                       hub_first((uint32_t)r.n), hub, col16);
+    ia.col16 = col16;
+    ia.hub = hub;
+}
+
 hipError_t launch_isect_stage(const RunArgs& r, hipEvent_t* ev) {
     const Layout L = make_layout(r.E, r.n);
-    const IsectArgs ia = isect_args(r, L, csc_of(r, L));
+    uint64_t* csc = csc_of(r, L);
+    IsectArgs ia = isect_args(r, L, csc);
+    prepare_hub(r, L, csc, ia);
     uint64_t* partials = (uint64_t*)((char*)r.ws + L.isect_partials);
     const int order[NKERNEL] = {KER_MERGE, KER_BSEARCH, KER_BITMAP};
     reset_tile_counters(ia.ctrl, r.stream);
@@ -1316,7 +1422,7 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
     if (learned_tile) mlp_select((const MlpCompute*)r.mlp_tile, ctrl, r.learned_tile, s);
     hipLaunchKernelGGL(k_select, dim3(1), dim3(NBUCKET), 0, s, ctrl, r.given ? (int)SEL_LEARNED : r.select,
                        r.given ? r.given : (learned ? r.learned : nullptr), learned_tile ? r.learned_tile : nullptr,
-                       r.chunk_override, r.group_override, r.formulation != FORM_FILTERED ? 1 : 0);
+                       r.chunk_override, r.group_override, r.formulation != FORM_FILTERED ? 1 : 0, hub_tab(r, L));
     mark(7);
     // ---- group: order vertices by (kernel, bucket); tiles
     hipLaunchKernelGGL(k_vkeys_slot, dim3(grid_for((size_t)n)), dim3(NT), 0, s, vbucket, n, ctrl, vkeysA);
@@ -1329,7 +1435,7 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
     hipLaunchKernelGGL(k_ntiles, dim3(grid_for((size_t)n)), dim3(NT), 0, s, vlist, vbucket, inoff, n, ctrl, tstart);
     scan_exclusive_sum_u32(tstart, tstart, (size_t)n + 1, scan_tmp, s);
     hipLaunchKernelGGL(k_emit_tiles, dim3(grid_for((size_t)n)), dim3(NT), 0, s, vlist, vbucket, inoff, tstart, n,
-                       ctrl, tiles, (uint64_t)L.tile_cap);
+                       ctrl, tiles, (uint64_t)L.tile_cap, hub_tab(r, L));
     if (r.per_edge_counts) fill_u32(r.per_edge_counts, 0u, (size_t)E, s);
     if (r.support) fill_u32(r.support, 0u, (size_t)E, s);
     if (r.per_vertex || r.per_middle || r.clustering) fill_u64(pv, 0ull, (size_t)n, s);
@@ -1339,7 +1445,8 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         return hipGetLastError();
     }
     // ---- intersections
-    const IsectArgs ia = isect_args(r, L, csc);
+    IsectArgs ia = isect_args(r, L, csc);
+    prepare_hub(r, L, csc, ia);
     uint64_t* partials = (uint64_t*)(ws + L.isect_partials);
     const int order[NKERNEL] = {KER_MERGE, KER_BSEARCH, KER_BITMAP};
     for (int q = 0; q < NKERNEL; ++q) {
