@@ -51,7 +51,11 @@ typedef enum tc_status {
 } tc_status;
 
 /* Which intersection strategy handles each degree-pair bucket. Every choice
- * gives the same exact counts; only the time differs. */
+ * gives the same exact counts; only the time differs. In the first two modes,
+ * T, t[v] and clustering coefficients of small graphs (at most 16384 vertices
+ * and 2^17 pairs) come from a bit matrix instead, without buckets, as long as
+ * the workspace holds tc_workspace_size() bytes; tc_last_stats then
+ * reports the selection these modes make. */
 typedef enum tc_select {
     TC_SELECT_HEURISTIC = 0,  /* fixed thresholds on the bucket's degrees */
     TC_SELECT_LEARNED = 1,    /* the context's trained selector network */
@@ -77,9 +81,10 @@ typedef struct tc_ctx tc_ctx;
 tc_status tc_create(tc_ctx** ctx, int device, void* hip_stream);
 tc_status tc_destroy(tc_ctx* ctx);
 
-/* Bytes of device workspace that a call with these sizes needs. The value
- * depends only on the arguments, so one workspace serves every call with
- * equal or smaller sizes. */
+/* Bytes of device workspace for a call with these sizes. The value depends
+ * only on the arguments, and one workspace serves every call with equal or
+ * smaller sizes (a small graph's bit matrix can make its size exceed a larger graph's:
+ * in a workspace without room for it, it is counted without the matrix). */
 tc_status tc_workspace_size(int64_t num_edges, int32_t num_vertices, const tc_options* opts, size_t* bytes);
 
 /*

@@ -104,6 +104,11 @@ bool options_ok(const tc_options* o) {
     return true;
 }
 
+// What tc_workspace_size reports: the pipeline's layout, or the small-graph path's where that is larger.
+size_t plain_workspace(int64_t E, int32_t n) {
+    return std::max(tcx::make_layout(E, n).total, tcx::small_workspace(E, n));
+}
+
 // 2E endpoints are indexed with 32-bit positions, with room for one sort tile
 constexpr int64_t kMaxEdges = ((int64_t)1 << 31) - ((int64_t)1 << 20);
 
@@ -165,11 +170,20 @@ tc_status run(tc_ctx* ctx, const int32_t* d_edges, int64_t E, int32_t n, void* w
         ctx->have_times = 0;
         return TC_OK;
     }
+    // small graphs: counts, per-vertex counts and coefficients on a bit matrix, where the
+    // workspace holds it (tc_workspace_size includes it; a smaller one that the pipeline
+    // can work in stays accepted). Forced strategies, stage times and per-edge outputs
+    // are the pipeline's.
+    const bool small = tcx::small_graph(E, n) && ws_bytes >= tcx::small_workspace(E, n) &&
+                       (sel == TC_SELECT_HEURISTIC || sel == TC_SELECT_LEARNED) && !timing && !ra.given &&
+                       !ra.stop_before_isect && ra.formulation == tcx::FORM_FILTERED && !ra.per_edge_counts &&
+                       !ra.support && !ra.csr_rank && !ra.per_middle && !ra.list_out;
     tcx::RunResult rr;
-    hipError_t e = tcx::run_pipeline(ra, &rr);
+    hipError_t e = small ? tcx::run_small(ra, d_result, (uint64_t)TC_ERR_VERTEX_RANGE, &rr)
+                         : tcx::run_pipeline(ra, &rr);
     if (e != hipSuccess) return hip_fail(ctx, e, "launch");
     if (d_result) {
-        tcx::publish_result(rr.ctrl_dev, d_result, (uint64_t)TC_ERR_VERTEX_RANGE, (uint64_t)TC_ERR_HIP, ctx->stream);
+        if (!small) tcx::publish_result(rr.ctrl_dev, d_result, (uint64_t)TC_ERR_VERTEX_RANGE, (uint64_t)TC_ERR_HIP, ctx->stream);
         ctx->have_times = 0;
         e = hipGetLastError();
         return e == hipSuccess ? TC_OK : hip_fail(ctx, e, "queue result");
@@ -272,7 +286,7 @@ tc_status tc_destroy(tc_ctx* ctx) {
 tc_status tc_workspace_size(int64_t num_edges, int32_t num_vertices, const tc_options* opts, size_t* bytes) {
     if (!bytes || num_edges < 0 || num_vertices < 0 || !options_ok(opts)) return TC_ERR_INVALID_ARG;
     if (num_edges > kMaxEdges) return TC_ERR_UNSUPPORTED;
-    *bytes = tcx::make_layout(num_edges, num_vertices).total;
+    *bytes = plain_workspace(num_edges, num_vertices);
     return TC_OK;
 }
 
@@ -316,7 +330,7 @@ tc_status tc_formulation_workspace_size(int64_t num_edges, int32_t num_vertices,
     if (formulation < TC_FORM_FILTERED || formulation > TC_FORM_MATRIX_UPPER) return TC_ERR_INVALID_ARG;
     if (num_edges > kMaxEdges) return TC_ERR_UNSUPPORTED;
     const bool sym = formulation == TC_FORM_FULL || formulation == TC_FORM_MATRIX;
-    *bytes = tcx::make_layout(num_edges, num_vertices).total +
+    *bytes = plain_workspace(num_edges, num_vertices) +
              (sym ? tcx::sym_extra_bytes(num_edges, num_vertices) : 0);
     return TC_OK;
 }

@@ -72,6 +72,19 @@ struct RunResult {
 };
 
 hipError_t run_pipeline(const RunArgs& r, RunResult* out);
+// Bucket features, the selector networks where they apply, and the strategy and tile shape
+// per bucket, from the control block's bucket statistics (hub: its table to reset, or null).
+void select_buckets(const RunArgs& r, Ctrl* ctrl, HubTab* hub);
+
+// ---- small graphs (small.hip): T, t[v] and clustering coefficients on a bit matrix
+constexpr int32_t SMALL_MAX_N = 16384;
+constexpr int64_t SMALL_MAX_PAIRS = 1 << 17;
+bool small_graph(int64_t E, int32_t n);
+size_t small_workspace(int64_t E, int32_t n);   // 0 for other sizes
+// The whole count; the control block ends up at the start of the workspace, as
+// run_pipeline's. With result (a queued call) T and the status go to result[0..1], as
+// publish_result's; without it the statistics that tc_last_stats reports are taken too.
+hipError_t run_small(const RunArgs& r, uint64_t* result, uint64_t range_status, RunResult* out);
 // Copies T and the status of a finished run to result[0..1] (device): range_status
 // for an id out of range, internal_status for a violated internal bound, else 0.
 void publish_result(const Ctrl* ctrl, uint64_t* result, uint64_t range_status, uint64_t internal_status,

@@ -29,6 +29,7 @@
 #include "isect.h"
 #include "mlp.h"
 #include "pipeline.h"
+#include "tiles.h"
 
 namespace tcx {
 
@@ -602,51 +603,20 @@ __global__ __launch_bounds__(NT) void k_sym_build(uint64_t* __restrict__ keys, c
 }
 
 // ------------------------------------------------------------------ buckets
-__device__ __forceinline__ uint32_t bucket_of(uint32_t din, uint32_t dout) {
-    if (din == 0 || dout == 0) return BUCKET_NONE;
-    const uint32_t li = min(14, floor_log2(din));
-    const uint32_t lo = min(15, floor_log2(dout));
-    return 16u * li + lo;
-}
-
 __global__ __launch_bounds__(NT) void k_vbucket(const uint32_t* __restrict__ off, const uint32_t* __restrict__ col,
                                                 const uint32_t* __restrict__ inoff, int32_t n,
                                                 uint8_t* __restrict__ vbucket, Ctrl* ctrl) {
-    __shared__ uint32_t s_nv[NBUCKET];
-    __shared__ unsigned long long s_in[NBUCKET], s_out[NBUCKET], s_work[NBUCKET], s_win[NBUCKET];
-    for (int b = threadIdx.x; b < NBUCKET; b += NT) {
-        s_nv[b] = 0;
-        s_in[b] = 0;
-        s_out[b] = 0;
-        s_work[b] = 0;
-        s_win[b] = 0;
-    }
+    __shared__ BucketSums S;
+    S.clear(NT);
     __syncthreads();
     for (int64_t v = (int64_t)blockIdx.x * NT + threadIdx.x; v < n; v += (int64_t)gridDim.x * NT) {
         const uint32_t din = inoff[v + 1] - inoff[v], dout = off[v + 1] - off[v];
         const uint32_t b = bucket_of(din, dout);
         vbucket[v] = (uint8_t)b;
-        if (b != BUCKET_NONE) {
-            atomicAdd(&s_nv[b], 1u);
-            atomicAdd(&s_in[b], (unsigned long long)din);
-            atomicAdd(&s_out[b], (unsigned long long)dout);
-            atomicAdd(&s_work[b], (unsigned long long)din * dout);
-            // windows the bitmap strategy walks for this middle list (first one
-            // aligned down to a word)
-            const uint32_t lo = col[off[v]], hi = col[off[v + 1] - 1];
-            atomicAdd(&s_win[b], (unsigned long long)(((hi - (lo & ~31u)) >> BM_WINDOW_LOG2) + 1u));
-        }
+        if (b != BUCKET_NONE) S.add(din, dout, col[off[v]], col[off[v + 1] - 1]);
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < NBUCKET; b += NT) {
-        if (s_nv[b]) {
-            atomicAdd(&ctrl->bucket_nv[b], s_nv[b]);
-            atomicAdd((unsigned long long*)&ctrl->bucket_in[b], s_in[b]);
-            atomicAdd((unsigned long long*)&ctrl->bucket_out[b], s_out[b]);
-            atomicAdd((unsigned long long*)&ctrl->bucket_work[b], s_work[b]);
-            atomicAdd((unsigned long long*)&ctrl->bucket_win[b], s_win[b]);
-        }
-    }
+    S.flush(ctrl, NT);
 }
 
 // ------------------------------------------------------------------ selection
@@ -673,7 +643,7 @@ __global__ __launch_bounds__(NBUCKET) void k_select(Ctrl* ctrl, int mode, const 
                                                     const uint16_t* __restrict__ chunk_override,
                                                     const uint8_t* __restrict__ group_override, int whole_rows,
                                                     HubTab* __restrict__ hub) {
-    __shared__ uint32_t s_key[NBUCKET];
+    __shared__ __align__(16) uint32_t s_key[NBUCKET];
     const int b = threadIdx.x;
     if (hub) hub->first[b] = ~0u;   // set by k_emit_tiles
     int ch;
@@ -722,25 +692,12 @@ __global__ __launch_bounds__(NBUCKET) void k_select(Ctrl* ctrl, int mode, const 
     s_key[b] = key;
     __syncthreads();
     uint32_t r = 0;
-    for (int q = 0; q < NBUCKET; ++q) r += (s_key[q] < key || (s_key[q] == key && q < b)) ? 1u : 0u;
+#pragma unroll 8
+    for (int q = 0; q < NBUCKET; q += 4) {   // keys are distinct but for the empty bucket's, the highest
+        const uint4 k = *(const uint4*)&s_key[q];
+        r += (k.x < key ? 1u : 0u) + (k.y < key ? 1u : 0u) + (k.z < key ? 1u : 0u) + (k.w < key ? 1u : 0u);
+    }
     ctrl->slot[b] = (uint8_t)r;
-}
-
-// Vertices per multi-vertex tile for bucket b (1 = chunks of single vertices).
-__device__ __forceinline__ uint32_t tile_group(const Ctrl* ctrl, uint32_t b) {
-    const uint32_t li = b >> 4;
-    if (li >= 14) return 1u;
-    const uint32_t maxin = 2u << li;   // in-degrees of the bucket are below this
-    const uint32_t K = ctrl->chunk[b];
-    if (2u * maxin > K) return 1u;
-    const uint32_t g = K / maxin;
-    // the edge-centric kernels stage the tile's lists in LDS when they fit:
-    // no more vertices than STAGE_MAX list elements at the bucket's longest
-    const uint32_t lo = b & 15u;
-    const uint32_t stage_cap = lo >= 12 ? 1u : (uint32_t)STAGE_MAX / (2u << lo);
-    const uint32_t cap = ctrl->choice[b] == KER_BITMAP ? (uint32_t)SEG_MAX_BITMAP
-                                                       : (stage_cap < (uint32_t)SEG_MAX ? stage_cap : (uint32_t)SEG_MAX);
-    return g > cap ? cap : (g > 1u ? g : 1u);
 }
 
 __global__ __launch_bounds__(NT) void k_vkeys_slot(const uint8_t* __restrict__ vbucket, int32_t n, const Ctrl* ctrl,
@@ -1190,6 +1147,18 @@ hipError_t launch_isect_range(const RunArgs& r, int ker, uint32_t t0, uint32_t t
     return hipGetLastError();
 }
 
+void select_buckets(const RunArgs& r, Ctrl* ctrl, HubTab* hub) {
+    hipStream_t s = r.stream;
+    const bool learned = !r.given && r.select == SEL_LEARNED && r.mlp && r.learned;
+    const bool learned_tile = learned && r.mlp_tile && r.learned_tile;
+    if (learned) mlp_select((const MlpCompute*)r.mlp, ctrl, r.learned, s);
+    else bucket_features_launch(ctrl, s);
+    if (learned_tile) mlp_select((const MlpCompute*)r.mlp_tile, ctrl, r.learned_tile, s);
+    hipLaunchKernelGGL(k_select, dim3(1), dim3(NBUCKET), 0, s, ctrl, r.given ? (int)SEL_LEARNED : r.select,
+                       r.given ? r.given : (learned ? r.learned : nullptr), learned_tile ? r.learned_tile : nullptr,
+                       r.chunk_override, r.group_override, r.formulation != FORM_FILTERED ? 1 : 0, hub);
+}
+
 hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
     hipStream_t s = r.stream;
     char* ws = (char*)r.ws;
@@ -1415,14 +1384,7 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
     const uint32_t* mcol = (r.formulation == FORM_FULL || r.formulation == FORM_MATRIX) ? sym_col(r, L) : col;
     hipLaunchKernelGGL(k_vbucket, dim3(grid_for((size_t)n, 2048)), dim3(NT), 0, s, moff, mcol, inoff, n, vbucket,
                        ctrl);
-    const bool learned = !r.given && r.select == SEL_LEARNED && r.mlp && r.learned;
-    const bool learned_tile = learned && r.mlp_tile && r.learned_tile;
-    if (learned) mlp_select((const MlpCompute*)r.mlp, ctrl, r.learned, s);
-    else bucket_features_launch(ctrl, s);
-    if (learned_tile) mlp_select((const MlpCompute*)r.mlp_tile, ctrl, r.learned_tile, s);
-    hipLaunchKernelGGL(k_select, dim3(1), dim3(NBUCKET), 0, s, ctrl, r.given ? (int)SEL_LEARNED : r.select,
-                       r.given ? r.given : (learned ? r.learned : nullptr), learned_tile ? r.learned_tile : nullptr,
-                       r.chunk_override, r.group_override, r.formulation != FORM_FILTERED ? 1 : 0, hub_tab(r, L));
+    select_buckets(r, ctrl, hub_tab(r, L));
     mark(7);
     // ---- group: order vertices by (kernel, bucket); tiles
     hipLaunchKernelGGL(k_vkeys_slot, dim3(grid_for((size_t)n)), dim3(NT), 0, s, vbucket, n, ctrl, vkeysA);
