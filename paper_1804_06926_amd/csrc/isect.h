@@ -23,6 +23,7 @@ struct IsectArgs {
     const uint4* tiles;         // [ntiles] tile descriptors (see TILE_MULTI)
     uint32_t* per_edge;         // [m] or null: c_e in CSR edge order
     uint64_t* per_vertex;       // [n] or null: t[] in rank space
+    uint32_t hot_first;         // first rank counted in LDS when per_vertex is set (see Hot)
     uint64_t* per_middle;       // [n] or null: triangles whose middle vertex is v (rank space)
     uint32_t* support;          // [m] or null: triangles containing each kept edge (CSR edge order)
     uint32_t col_narrow;        // 1 when col spans less than 4 GiB (32-bit byte offsets suffice)
@@ -44,8 +45,10 @@ struct IsectArgs {
 };
 
 // Blocks of one intersection kernel resident per CU (from the occupancy API);
-// mode: the bitmap kernel's output mode (0 for the edge kernels).
+// mode: the bitmap kernel's output mode (the edge kernels': counts only, or per vertex).
 int isect_blocks_per_cu(int ker, int mode);
+// First of the top ranks whose per-vertex counts are kept in LDS.
+uint32_t isect_hot_first(uint32_t n);
 size_t isect_partials_bytes();
 // One intersection kernel over its tile range (the bitmap strategy: two kernels, when a.hub is set); per-block partial counts go to
 // partials (isect_partials_bytes() of workspace shared by the three kernels).

@@ -43,7 +43,7 @@ static_assert(BM_BITS == (1u << BM_WINDOW_LOG2), "the selector's window feature 
 constexpr int UNROLL = 8;                 // bitmap kernel: tail loads in flight per lane
 constexpr uint32_t WT_MAX = 1024;         // bitmap kernel: 64-item windows per chunk of the item range
 constexpr uint32_t LONG_TAIL = 64;        // bitmap kernel: tails of at least one window are walked directly
-constexpr int NV_MAX = 2048;              // bitmap kernel, per-vertex mode: N+(v) kept for t[w] gathering
+constexpr int NV_MAX = 2048;              // bitmap kernel, support mode: longest N+(v) whose hits are gathered in LDS
 constexpr int PARTIALS_PER_KERNEL = 4096; // max blocks per intersection launch
 
 template <int N>
@@ -127,18 +127,44 @@ __device__ uint32_t load_tile(const IsectArgs& a, uint32_t t, SegsT<N>& S) {
     return nseg;
 }
 
-__device__ __forceinline__ void edge_done(const IsectArgs& a, uint32_t e, uint32_t v, uint32_t c) {
+// Per-vertex counts. Most triangles' highest vertex is one of a few hubs, and
+// device-wide atomics on one address serialise (about 23 ns each), so a block of
+// the bitmap or binary-search kernel counts the HOT_N top-ranked vertices in
+// LDS and adds them up once, at its end. (Merge path serves short lists, which
+// end in hubs less often, and lives on its occupancy: with these counters it
+// ran four blocks per CU instead of seven, and a uniform graph of 10
+// million pairs took 1577 us instead of 1501.) Measured per call with t[v]: R-MAT 16 994 -> 565 us; R-MAT 18
+// with clustering coefficients 2796 -> 1110 us (1024, 4096 and 8192 counters: 1151,
+// 1202 and 1380 us).
+constexpr uint32_t HOT_N = 2048;
+struct Hot {
+    uint32_t* cnt;    // LDS [HOT_N], or null: no vertex is counted in LDS
+    uint32_t first;   // rank of cnt[0]
+    __device__ void add(const IsectArgs& a, uint32_t x, uint32_t c) const {
+        if (cnt && x >= first) atomicAdd(&cnt[x - first], c);
+        else atomicAdd((unsigned long long*)&a.per_vertex[x], (unsigned long long)c);
+    }
+    // Whole block, before the first and after the last tile; barriers around are the caller's.
+    __device__ void clear() const {
+        for (uint32_t i = threadIdx.x; i < HOT_N; i += blockDim.x) cnt[i] = 0;
+    }
+    __device__ void flush(const IsectArgs& a) const {
+        for (uint32_t i = threadIdx.x; i < HOT_N; i += blockDim.x) {
+            const uint32_t q = (i + blockIdx.x * 64u) % HOT_N;   // blocks start at different counters
+            const uint32_t c = cnt[q];
+            if (c) atomicAdd((unsigned long long*)&a.per_vertex[first + q], (unsigned long long)c);
+        }
+    }
+};
+
+__device__ __forceinline__ void edge_done(const IsectArgs& a, const Hot& hot, uint32_t e, uint32_t v, uint32_t c) {
     if (a.per_edge) a.per_edge[e] = c;
     if (a.support && c) atomicAdd(&a.support[e], c);
     if (a.per_middle && c) atomicAdd((unsigned long long*)&a.per_middle[v], (unsigned long long)c);
     if (a.per_vertex && c) {
-        atomicAdd((unsigned long long*)&a.per_vertex[a.src[e]], (unsigned long long)c);
-        atomicAdd((unsigned long long*)&a.per_vertex[v], (unsigned long long)c);
+        hot.add(a, a.src[e], c);
+        hot.add(a, v, c);
     }
-}
-
-__device__ __forceinline__ void hit_vertex(const IsectArgs& a, uint32_t w) {
-    if (a.per_vertex) atomicAdd((unsigned long long*)&a.per_vertex[w], 1ull);
 }
 
 // Triangle (u, v, w) of in-edge e = (u -> v) at list slot pos, original ids.
@@ -155,8 +181,9 @@ __device__ __forceinline__ void list_write(const IsectArgs& a, uint64_t pos, uin
 
 // A hit w = col[ea] = col[eb] for in-edge ein: ea is the edge (u, w) of the
 // tail, eb the edge (v, w).
-__device__ __forceinline__ void hit(const IsectArgs& a, uint32_t w, uint32_t ea, uint32_t eb, uint32_t ein) {
-    hit_vertex(a, w);
+__device__ __forceinline__ void hit(const IsectArgs& a, const Hot& hot, uint32_t w, uint32_t ea, uint32_t eb,
+                                    uint32_t ein) {
+    if (a.per_vertex) hot.add(a, w, 1u);
     if (a.support) {
         atomicAdd(&a.support[ea], 1u);
         atomicAdd(&a.support[eb], 1u);
@@ -197,14 +224,16 @@ __device__ __forceinline__ uint32_t col_at(const uint32_t* col, uint32_t i) {
 }
 
 // Outputs of a bitmap launch: T only; also per middle vertex (one sum per vertex
-// and tile); also per in-edge counts (per-edge outputs); or also gathered per-vertex counts or edge
-// support (the hits per element of N+(v), for t[w] and the support of edge
-// vw, are gathered in LDS); or the triangle list (the per-entry count is the
-// cursor of the entry's slots). Each mode sizes its LDS to what it uses.
+// and tile); also per in-edge counts (per-edge outputs); per-vertex counts (t[w] in LDS counters
+// for the top ranks); edge support (the hits per element of N+(v), the support of
+// edge vw, are gathered in LDS; an element's position in the list is the
+// position of its bitmap word's first element plus the bits before it);
+// or the triangle list (the per-entry count is the cursor of the entry's
+// slots). Each mode sizes its LDS to what it uses.
 // BM_CLIP counts only, for tails that are whole rows: each tail and the middle
 // list are cut to the window being tested, and windows holding no element of
 // the middle list are skipped.
-enum { BM_COUNT = 0, BM_ENTRY = 1, BM_GATHER = 2, BM_LIST = 3, BM_CLIP = 4, BM_MIDDLE = 5, BM_NMODE = 6 };
+enum { BM_COUNT = 0, BM_ENTRY = 1, BM_VERTEX = 2, BM_LIST = 3, BM_CLIP = 4, BM_MIDDLE = 5, BM_SUPPORT = 6, BM_NMODE = 7 };
 
 constexpr int EH = CHUNK_MAX / IS_NT;   // entries of a vertex per thread
 
@@ -294,15 +323,19 @@ __device__ __forceinline__ uint32_t entry_table(const uint32_t (&st_h)[EPT], con
     return nt;
 }
 
-// Six blocks of four waves fit a CU by LDS in every mode but the gathering one
-// (44 KB); the register budget is held to the same occupancy (80 VGPRs).
+// Six blocks of four waves fit a CU by LDS in every mode but the per-vertex (35 KB:
+// four) and the support one (44 KB: three); the register budget is held to the same occupancy (80 VGPRs).
 template <int MODE, bool NARROW>
-__global__ __launch_bounds__(IS_NT, MODE == BM_GATHER ? 1 : 6) void k_isect_bitmap(IsectArgs a, uint64_t* partials) {
-    constexpr bool GATHER = MODE == BM_GATHER;
+__global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT ? 3 : 6)) void k_isect_bitmap(
+    IsectArgs a, uint64_t* partials) {
+    constexpr bool VERTEX = MODE == BM_VERTEX, SUPPORT = MODE == BM_SUPPORT;
     constexpr bool CLIP = MODE == BM_CLIP;
     constexpr bool need_cnt = MODE != BM_COUNT && MODE != BM_MIDDLE && !CLIP;
-    __shared__ uint32_t s_nv[GATHER ? NV_MAX : 1];
-    __shared__ uint32_t s_wc[GATHER ? NV_MAX : 1];
+    __shared__ uint32_t s_hot[VERTEX ? HOT_N : 1];
+    __shared__ uint32_t s_wc[SUPPORT ? NV_MAX : 1];       // hits per element of N+(v)
+    __shared__ uint16_t s_first[SUPPORT ? BM_WORDS : 1];  // position in N+(v) of a word's first element
+    const Hot hot = {VERTEX ? s_hot : nullptr, a.hot_first};
+    if (VERTEX) hot.clear();
     __shared__ uint32_t bm[BM_WORDS + 1];        // + one always-zero word for out-of-window positions
     __shared__ uint16_t s_wst[WT_MAX];           // entry holding the first item of each window of a chunk
     __shared__ uint32_t s_pref[CHUNK_MAX + 1];
@@ -347,12 +380,9 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_GATHER ? 1 : 6) void k_isect_bitm
             const uint32_t lo = a.col[b0], hi = a.col[b1 - 1];
             const uint32_t base = lo & ~31u;
             const uint32_t nwin = (hi - base) / BM_BITS + 1;
-            if (GATHER && nb <= (uint32_t)NV_MAX) {
-                for (uint32_t j = threadIdx.x; j < nb; j += IS_NT) {
-                    s_nv[j] = a.col[b0 + j];
-                    s_wc[j] = 0u;
-                }
-            }
+            const bool gather = SUPPORT && nb <= (uint32_t)NV_MAX;
+            if (gather)
+                for (uint32_t j = threadIdx.x; j < nb; j += IS_NT) s_wc[j] = 0u;
             __syncthreads();
             // clipped tails: each entry keeps a cursor (st_h, with len_h left) and the
             // value under it, so a window that holds none of its elements costs no load
@@ -394,7 +424,11 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_GATHER ? 1 : 6) void k_isect_bitm
                 }
                 for (uint32_t j = j0 + threadIdx.x; j < j1; j += IS_NT) {
                     const uint32_t x = a.col[b0 + j] - wlo;
-                    if (x < BM_BITS) atomicOr(&bm[x >> 5], 1u << (x & 31u));
+                    if (x < BM_BITS) {
+                        atomicOr(&bm[x >> 5], 1u << (x & 31u));
+                        if (gather && (j == 0 || (a.col[b0 + j - 1] - wlo) >> 5 != x >> 5))
+                            s_first[x >> 5] = (uint16_t)j;
+                    }
                 }
                 __syncthreads();
                 // All tails of the tile form one flat item range [0, L); item q of
@@ -505,31 +539,33 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_GATHER ? 1 : 6) void k_isect_bitm
                         acc += hits;
                         if (MODE == BM_MIDDLE) seg_sum += hits;
                         if (!need_cnt) continue;
+                        const bool long_round = W + WAVE * UNROLL <= lim;
 #pragma unroll
                         for (int j = 0; j < UNROLL; ++j) {
                             const uint32_t x = xs[j];
-                            if ((wd[j] >> (x & 31u)) & 1u) {
-                                const uint32_t slot = atomicAdd(&s_cnt[ks[j]], 1u);
+                            const bool is = (wd[j] >> (x & 31u)) & 1u;
+                            if (MODE != BM_LIST && long_round) {   // at most two entries in the window
+                                const uint64_t H = __ballot(is);
+                                const uint32_t at = s_pref[kj[j] + 1u] - (W + (uint32_t)j * WAVE);
+                                const uint64_t A = at < (uint32_t)WAVE ? (1ull << at) - 1ull : ~0ull;
+                                const uint32_t c = (uint32_t)__popcll(ln == 0 ? H & A : H & ~A);
+                                if (ln < 2 && c) atomicAdd(&s_cnt[kj[j] + ln], c);
+                            }
+                            if (is) {
                                 if (MODE == BM_LIST) {
+                                    const uint32_t slot = atomicAdd(&s_cnt[ks[j]], 1u);
                                     const uint32_t e = s_base[ks[j]] + s_pref[ks[j]] - 1u;
                                     list_write(a, a.list_off[e] + slot, e, x + wlo);
+                                } else if (!long_round) {
+                                    atomicAdd(&s_cnt[ks[j]], 1u);
                                 }
-                                if (GATHER) {
-                                    const uint32_t w = x + wlo;
-                                    if (a.support)   // edge (u, w): the tail element's own position
-                                        atomicAdd(&a.support[s_base[ks[j]] + W + (uint32_t)j * WAVE + ln], 1u);
-                                    if (nb <= (uint32_t)NV_MAX) {   // w's slot in N+(v), flushed per vertex
-                                        uint32_t lo3 = 0, hi3 = nb - 1;
-                                        while (lo3 < hi3) {
-                                            const uint32_t mid = (lo3 + hi3) >> 1;
-                                            if (s_nv[mid] < w) lo3 = mid + 1;
-                                            else hi3 = mid;
-                                        }
-                                        atomicAdd(&s_wc[lo3], 1u);
-                                    } else {
-                                        hit_vertex(a, w);
-                                        if (a.support) atomicAdd(&a.support[b0 + find_pos(a.col + b0, nb, w)], 1u);
-                                    }
+                                if (VERTEX) hot.add(a, x + wlo, 1u);
+                                if (SUPPORT) {   // edge (u, w): the tail element's own position
+                                    atomicAdd(&a.support[s_base[ks[j]] + W + (uint32_t)j * WAVE + ln], 1u);
+                                    if (gather)   // w's place in N+(v), flushed per vertex
+                                        atomicAdd(&s_wc[s_first[x >> 5] + __popc(wd[j] & ((1u << (x & 31u)) - 1u))], 1u);
+                                    else
+                                        atomicAdd(&a.support[b0 + find_pos(a.col + b0, nb, x + wlo)], 1u);
                                 }
                             }
                         }
@@ -543,17 +579,24 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_GATHER ? 1 : 6) void k_isect_bitm
                 }
                 __syncthreads();
             }
-            if (GATHER && nb <= (uint32_t)NV_MAX) {
+            if (gather) {
                 for (uint32_t j = threadIdx.x; j < nb; j += IS_NT) {
                     const uint32_t c = s_wc[j];
-                    if (!c) continue;
-                    if (a.per_vertex) atomicAdd((unsigned long long*)&a.per_vertex[s_nv[j]], (unsigned long long)c);
-                    if (a.support) atomicAdd(&a.support[b0 + j], c);
+                    if (c) atomicAdd(&a.support[b0 + j], c);
                 }
             }
-            if (need_cnt) {
+            if (VERTEX) {   // t[u] per in-edge, t[v] once per wave
+                uint32_t mine = 0;
+                for (uint32_t k = threadIdx.x; k < nt; k += IS_NT) {
+                    const uint32_t c = s_cnt[k];
+                    if (c) hot.add(a, a.src[s_base[k] + s_pref[k] - 1u], c);
+                    mine += c;
+                }
+                mine = wave_sum(mine);
+                if (lane_id() == 0 && mine) hot.add(a, v, mine);
+            } else if (need_cnt) {
                 for (uint32_t k = threadIdx.x; k < nt; k += IS_NT)
-                    edge_done(a, s_base[k] + s_pref[k] - 1u, v, s_cnt[k]);
+                    edge_done(a, hot, s_base[k] + s_pref[k] - 1u, v, s_cnt[k]);
             }
             if (MODE == BM_MIDDLE) {   // one update per vertex and tile
                 uint32_t total;
@@ -563,6 +606,10 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_GATHER ? 1 : 6) void k_isect_bitm
             }
             __syncthreads();
         }
+    }
+    if (VERTEX) {
+        __syncthreads();
+        hot.flush(a);
     }
     block_partial(acc, partials);
 }
@@ -785,7 +832,7 @@ __device__ __forceinline__ uint32_t find_seg(const Segs& S, uint32_t nseg, uint3
 // four interleaved branch-free lower bounds (halving the range each step),
 // so that every step issues four independent loads. Returns the matches; a
 // match at X[q] = Y[p] is edge ex0 + q and edge ey0 + p.
-__device__ __forceinline__ uint32_t search_list(const IsectArgs& a, const uint32_t* X, uint32_t nx,
+__device__ __forceinline__ uint32_t search_list(const IsectArgs& a, const Hot& hot, const uint32_t* X, uint32_t nx,
                                                 const uint32_t* Y, uint32_t ny, uint32_t g, uint32_t gl,
                                                 uint32_t ex0, uint32_t ey0, uint32_t ein) {
     uint32_t c = 0;
@@ -821,7 +868,7 @@ __device__ __forceinline__ uint32_t search_list(const IsectArgs& a, const uint32
             const uint32_t q = q0 + (uint32_t)u * g;
             if (q < nx && lb[u] < ny && y1[u] == xv[u]) {
                 ++c;
-                hit(a, xv[u], ex0 + q, ey0 + lb[u], ein);
+                hit(a, hot, xv[u], ex0 + q, ey0 + lb[u], ein);
             }
         }
     }
@@ -832,7 +879,7 @@ __device__ __forceinline__ uint32_t search_list(const IsectArgs& a, const uint32
 // ea0, eb0: CSR positions of A[0] (the tail) and B[0] (N+(v)); the in-edge
 // itself sits just before its tail, at ea0 - 1.
 template <bool MERGE>
-__device__ __forceinline__ uint32_t isect_edge(const IsectArgs& a, const uint32_t* A, uint32_t na, const uint32_t* B,
+__device__ __forceinline__ uint32_t isect_edge(const IsectArgs& a, const Hot& hot, const uint32_t* A, uint32_t na, const uint32_t* B,
                                                uint32_t nb, uint32_t g, uint32_t gl, uint32_t ea0, uint32_t eb0) {
     uint32_t c = 0;
     if (MERGE) {
@@ -858,20 +905,23 @@ __device__ __forceinline__ uint32_t isect_edge(const IsectArgs& a, const uint32_
                 while (j < nb && B[j] < av[u]) ++j;
                 if (j < nb && B[j] == av[u]) {
                     ++c;
-                    hit(a, av[u], ea0 + i + u, eb0 + j, ea0 - 1u);
+                    hit(a, hot, av[u], ea0 + i + u, eb0 + j, ea0 - 1u);
                 }
             }
         }
     } else if (na <= nb) {
-        c = search_list(a, A, na, B, nb, g, gl, ea0, eb0, ea0 - 1u);   // tail elements searched in N+(v)
+        c = search_list(a, hot, A, na, B, nb, g, gl, ea0, eb0, ea0 - 1u);   // tail elements searched in N+(v)
     } else {
-        c = search_list(a, B, nb, A, na, g, gl, eb0, ea0, ea0 - 1u);   // N+(v) searched in the tail
+        c = search_list(a, hot, B, nb, A, na, g, gl, eb0, ea0, ea0 - 1u);   // N+(v) searched in the tail
     }
     return c;
 }
 
-template <bool MERGE>
-__global__ __launch_bounds__(IS_NT, MERGE ? 7 : 6) void k_isect_edges(IsectArgs a, uint64_t* partials) {
+template <bool MERGE, bool VERTEX>
+__global__ __launch_bounds__(IS_NT, VERTEX ? 4 : (MERGE ? 7 : 6)) void k_isect_edges(IsectArgs a, uint64_t* partials) {
+    __shared__ uint32_t s_hot[VERTEX ? HOT_N : 1];
+    const Hot hot = {VERTEX ? s_hot : nullptr, a.hot_first};
+    if (VERTEX) hot.clear();   // the first tile's barriers follow
     __shared__ uint32_t sb[STAGE_MAX];
     __shared__ uint32_t s_boff[SEG_MAX + 1];
     __shared__ Segs S;
@@ -933,17 +983,21 @@ __global__ __launch_bounds__(IS_NT, MERGE ? 7 : 6) void k_isect_edges(IsectArgs 
                 const uint32_t nb = s_boff[sg + 1] - s_boff[sg];
                 const uint32_t bo = a.off[v];
                 // two call sites, so that each knows whether N+(v) is in LDS or in global memory
-                if (staged) c = isect_edge<MERGE>(a, a.col + s, end - s, sb + s_boff[sg], nb, g, gl, s, bo);
-                else c = isect_edge<MERGE>(a, a.col + s, end - s, a.col + bo, nb, g, gl, s, bo);
+                if (staged) c = isect_edge<MERGE>(a, hot, a.col + s, end - s, sb + s_boff[sg], nb, g, gl, s, bo);
+                else c = isect_edge<MERGE>(a, hot, a.col + s, end - s, a.col + bo, nb, g, gl, s, bo);
             }
             // reduce within the group of g lanes (g divides the wave)
             for (uint32_t o = g >> 1; o > 0; o >>= 1) c += __shfl_xor(c, (int)o, WAVE);
             if (q < ne && gl == 0) {
                 acc += c;
-                edge_done(a, e, v, c);
+                edge_done(a, hot, e, v, c);
             }
         }
         __syncthreads();
+    }
+    if (VERTEX) {
+        __syncthreads();
+        hot.flush(a);
     }
     block_partial(acc, partials);
 }
@@ -981,7 +1035,8 @@ static int resident_blocks(const void* fn, int threads = IS_NT) {
 static int bitmap_mode(const IsectArgs& a) {
     if (a.clip) return BM_CLIP;   // whole-row tails: counts only
     if (a.list_out) return BM_LIST;
-    if (a.per_vertex || a.support) return BM_GATHER;
+    if (a.support) return BM_SUPPORT;   // never with per-vertex counts
+    if (a.per_vertex) return BM_VERTEX;
     if (a.per_edge) return BM_ENTRY;
     if (a.per_middle) return BM_MIDDLE;
     return BM_COUNT;
@@ -991,8 +1046,10 @@ static const void* bitmap_fn(int mode, bool narrow) {
     switch (mode) {
         case BM_LIST: return narrow ? (const void*)k_isect_bitmap<BM_LIST, true>
                                     : (const void*)k_isect_bitmap<BM_LIST, false>;
-        case BM_GATHER: return narrow ? (const void*)k_isect_bitmap<BM_GATHER, true>
-                                      : (const void*)k_isect_bitmap<BM_GATHER, false>;
+        case BM_VERTEX: return narrow ? (const void*)k_isect_bitmap<BM_VERTEX, true>
+                                      : (const void*)k_isect_bitmap<BM_VERTEX, false>;
+        case BM_SUPPORT: return narrow ? (const void*)k_isect_bitmap<BM_SUPPORT, true>
+                                       : (const void*)k_isect_bitmap<BM_SUPPORT, false>;
         case BM_ENTRY: return narrow ? (const void*)k_isect_bitmap<BM_ENTRY, true>
                                      : (const void*)k_isect_bitmap<BM_ENTRY, false>;
         case BM_MIDDLE: return narrow ? (const void*)k_isect_bitmap<BM_MIDDLE, true>
@@ -1008,18 +1065,22 @@ int isect_blocks_per_cu(int ker, int mode) {
     static int cache[NKERNEL][BM_NMODE] = {};
     int& c = cache[ker][mode];
     if (!c) {
-        const void* fn = ker == KER_MERGE     ? (const void*)k_isect_edges<true>
-                         : ker == KER_BSEARCH ? (const void*)k_isect_edges<false>
+        const bool vertex = mode == BM_VERTEX;
+        const void* fn = ker == KER_MERGE ? (const void*)k_isect_edges<true, false>
+                         : ker == KER_BSEARCH ? (vertex ? (const void*)k_isect_edges<false, true>
+                                                        : (const void*)k_isect_edges<false, false>)
                                               : bitmap_fn(mode, true);
         c = resident_blocks(fn);
     }
     return c;
 }
 
+uint32_t isect_hot_first(uint32_t n) { return n > HOT_N ? n - HOT_N : 0u; }
+
 size_t isect_partials_bytes() { return sizeof(uint64_t) * NKERNEL * PARTIALS_PER_KERNEL; }
 
 void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hipStream_t s) {
-    const int mode = ker == KER_BITMAP ? bitmap_mode(a) : 0;
+    const int mode = ker == KER_BITMAP ? bitmap_mode(a) : (a.per_vertex ? BM_VERTEX : BM_COUNT);
     if (grid <= 0) grid = num_cu() * isect_blocks_per_cu(ker, mode);
     const bool hub = ker == KER_BITMAP && a.hub;
     const int cap = hub ? HB_PARTIAL0 : PARTIALS_PER_KERNEL;
@@ -1037,16 +1098,24 @@ void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hip
             hipLaunchKernelGGL(k_isect_hub<false>, dim3(hg), dim3(HB_NT), 0, s, a, p + HB_PARTIAL0);
     }
     switch (ker) {
-        case KER_MERGE: hipLaunchKernelGGL(k_isect_edges<true>, dim3(grid), dim3(IS_NT), 0, s, a, p); break;
-        case KER_BSEARCH: hipLaunchKernelGGL(k_isect_edges<false>, dim3(grid), dim3(IS_NT), 0, s, a, p); break;
+        case KER_MERGE:
+            hipLaunchKernelGGL((k_isect_edges<true, false>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            break;
+        case KER_BSEARCH:
+            if (a.per_vertex) hipLaunchKernelGGL((k_isect_edges<false, true>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            else hipLaunchKernelGGL((k_isect_edges<false, false>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            break;
         default: {
             const bool nw = a.col_narrow != 0;
             if (mode == BM_LIST) {
                 if (nw) hipLaunchKernelGGL((k_isect_bitmap<BM_LIST, true>), dim3(grid), dim3(IS_NT), 0, s, a, p);
                 else hipLaunchKernelGGL((k_isect_bitmap<BM_LIST, false>), dim3(grid), dim3(IS_NT), 0, s, a, p);
-            } else if (mode == BM_GATHER) {
-                if (nw) hipLaunchKernelGGL((k_isect_bitmap<BM_GATHER, true>), dim3(grid), dim3(IS_NT), 0, s, a, p);
-                else hipLaunchKernelGGL((k_isect_bitmap<BM_GATHER, false>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            } else if (mode == BM_VERTEX) {
+                if (nw) hipLaunchKernelGGL((k_isect_bitmap<BM_VERTEX, true>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+                else hipLaunchKernelGGL((k_isect_bitmap<BM_VERTEX, false>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            } else if (mode == BM_SUPPORT) {
+                if (nw) hipLaunchKernelGGL((k_isect_bitmap<BM_SUPPORT, true>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+                else hipLaunchKernelGGL((k_isect_bitmap<BM_SUPPORT, false>), dim3(grid), dim3(IS_NT), 0, s, a, p);
             } else if (mode == BM_CLIP) {
                 if (nw) hipLaunchKernelGGL((k_isect_bitmap<BM_CLIP, true>), dim3(grid), dim3(IS_NT), 0, s, a, p);
                 else hipLaunchKernelGGL((k_isect_bitmap<BM_CLIP, false>), dim3(grid), dim3(IS_NT), 0, s, a, p);

@@ -857,24 +857,46 @@ __global__ __launch_bounds__(NT) void k_map_pv(const uint64_t* __restrict__ pv, 
 // Local clustering coefficient C(v) = t[v] / C(d(v), 2) (zero when d(v) < 2)
 // and the number of wedges (paths of length two) sum_v C(d(v), 2), which with
 // T gives the transitivity 3T / wedges. d(v) is the simple-graph degree: the
-// out-degree of v's CSR row plus its in-degree over the kept edges.
+// out-degree of v's CSR row plus its in-degree over the kept edges: the grouped in-edges
+// (those with a non-empty tail) and the rows that end in v.
 constexpr unsigned CL_MAX_BLOCKS = 4096;   // block partials live in the intersection partials
 
-__global__ __launch_bounds__(NT) void k_indeg(const uint32_t* __restrict__ col, const Ctrl* ctrl,
-                                              uint32_t* __restrict__ indeg) {
-    const uint32_t m = ctrl->m;
-    for (uint64_t e = (uint64_t)blockIdx.x * NT + threadIdx.x; e < m; e += (uint64_t)gridDim.x * NT)
-        atomicAdd(&indeg[col[e]], 1u);
+// last[v] += rows whose highest neighbour is v: the in-edges that the in-edge
+// grouping leaves out. Most rows end in a few hubs, so the top LAST_N ranks
+// are counted in LDS (one atomic per kept edge into the in-degrees took 689 us at
+// R-MAT 18; this takes 6).
+constexpr uint32_t LAST_N = 8192;
+constexpr unsigned LAST_NT = 1024, LAST_BLOCKS = 128;
+__global__ __launch_bounds__(LAST_NT) void k_row_last(const uint32_t* __restrict__ off,
+                                                      const uint32_t* __restrict__ col, int32_t n,
+                                                      uint32_t* __restrict__ last) {
+    __shared__ uint32_t s_cnt[LAST_N];
+    const uint32_t first = (uint32_t)n > LAST_N ? (uint32_t)n - LAST_N : 0u;
+    for (uint32_t i = threadIdx.x; i < LAST_N; i += LAST_NT) s_cnt[i] = 0;
+    __syncthreads();
+    for (int64_t u = (int64_t)blockIdx.x * LAST_NT + threadIdx.x; u < n; u += (int64_t)gridDim.x * LAST_NT) {
+        const uint32_t a = off[u], b = off[u + 1];
+        if (a == b) continue;
+        const uint32_t v = col[b - 1];
+        if (v >= first) atomicAdd(&s_cnt[v - first], 1u);
+        else atomicAdd(&last[v], 1u);
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < LAST_N; i += LAST_NT) {
+        const uint32_t q = (i + blockIdx.x * 64u) % LAST_N;
+        if (s_cnt[q]) atomicAdd(&last[first + q], s_cnt[q]);
+    }
 }
 
 __global__ __launch_bounds__(NT) void k_clustering(const uint64_t* __restrict__ t, const uint32_t* __restrict__ inv,
                                                    const uint32_t* __restrict__ off,
-                                                   const uint32_t* __restrict__ indeg, int32_t n,
+                                                   const uint32_t* __restrict__ inoff,
+                                                   const uint32_t* __restrict__ last, int32_t n,
                                                    double* __restrict__ coeff, uint64_t* __restrict__ partials) {
     __shared__ uint64_t red[NT / WAVE];
     uint64_t acc = 0;
     for (int64_t r = (int64_t)blockIdx.x * NT + threadIdx.x; r < n; r += (int64_t)gridDim.x * NT) {
-        const uint64_t d = (uint64_t)(off[r + 1] - off[r]) + indeg[r];
+        const uint64_t d = (uint64_t)(off[r + 1] - off[r]) + (inoff[r + 1] - inoff[r]) + last[r];
         const uint64_t w = d < 2 ? 0ull : d * (d - 1) / 2;
         acc += w;
         coeff[inv[r]] = w ? (double)t[r] / (double)w : 0.0;
@@ -1035,6 +1057,7 @@ static IsectArgs isect_args(const RunArgs& r, const Layout& L, uint64_t* csc) {
     ia.tiles = (const uint4*)(ws + L.tiles);
     ia.per_edge = r.per_edge_counts;
     ia.per_vertex = (r.per_vertex || r.clustering) ? (uint64_t*)(ws + L.pv) : nullptr;
+    ia.hot_first = isect_hot_first((uint32_t)r.n);
     ia.per_middle = r.per_middle ? (uint64_t*)(ws + L.pv) : nullptr;
     ia.support = r.support;
     ia.list_off = r.list_off;
@@ -1422,11 +1445,12 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         hipLaunchKernelGGL(k_map_pv, dim3(grid_for((size_t)n)), dim3(NT), 0, s, pv, inv, n, r.per_vertex);
     else if (r.per_middle)
         hipLaunchKernelGGL(k_map_pv, dim3(grid_for((size_t)n)), dim3(NT), 0, s, pv, inv, n, r.per_middle);
-    if (r.clustering) {   // the degree offsets are dead by now: reuse them for the simple in-degree
+    if (r.clustering) {   // the degree offsets are dead by now: reuse them
         fill_u32(deg, 0u, (size_t)n, s);
-        hipLaunchKernelGGL(k_indeg, dim3(grid_for((size_t)E)), dim3(NT), 0, s, col, ctrl, deg);
+        hipLaunchKernelGGL(k_row_last, dim3(LAST_BLOCKS), dim3(LAST_NT), 0, s, off, col, n, deg);
         const unsigned g = grid_for((size_t)n, CL_MAX_BLOCKS);
-        hipLaunchKernelGGL(k_clustering, dim3(g), dim3(NT), 0, s, pv, inv, off, deg, n, r.clustering, partials);
+        hipLaunchKernelGGL(k_clustering, dim3(g), dim3(NT), 0, s, pv, inv, off, inoff, deg, n, r.clustering,
+                           partials);
         hipLaunchKernelGGL(k_sum_wedges, dim3(1), dim3(NT), 0, s, partials, g, ctrl);
     }
     if (r.per_edge_pairs)
