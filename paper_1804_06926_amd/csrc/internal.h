@@ -36,7 +36,7 @@ size_t radix_temp_bytes(size_t cap);
 // only partitions (ranks by LDS atomics): the keys come out sorted on
 // [bit_lo, bit_hi), but keys equal on those bits in no particular order, so
 // use it where that order is free (the whole key sorted, or a grouping).
-// 64-bit sorts of 2^26 keys or more without payload take their passes after the first
+// 64-bit sorts of 2^25 keys or more without payload take their passes after the first
 // in one kernel each (decoupled look-back, no histogram pass); a wait there
 // that runs out sets bit 1 of *err (nullptr: radix_err_word(temp, cap)). With
 // totals_given, an earlier kernel has counted radix_sort_totals(...) and every
@@ -84,7 +84,7 @@ struct RadixXf {
 // more (n > 0): the pass's histogram kernel also takes these global counts
 // (zeroing them first); ignored when the counts come from `counted`.
 // lb_tot: the global counts of this pass's digit (256), taken by an earlier
-// kernel; with 8192-key tiles (2^26 keys or more) the pass then runs as one
+// kernel; with 8192-key tiles (2^25 keys or more) the pass then runs as one
 // look-back kernel with no histogram (a wait that runs out sets bit 1 of *err;
 // nullptr: radix_err_word(temp, cap)); otherwise it is ignored.
 void radix_pass_u64(const uint64_t* kin, uint64_t* kout, size_t cap, int shift, int bits, const RadixXf& xf,

@@ -206,15 +206,17 @@ void scan_exclusive_sum_u64(const uint64_t* in, uint64_t* out, size_t len, void*
 // A tile is RS_NT threads x ITEMS keys: 16 keys per lane (4096-key tiles, longer
 // runs of equal digits for the scatter, half the count table) for sorts of at
 // least 2^22 keys, 8 (2048-key tiles, twice the blocks) below, and 32 for sorts
-// of at least 2^26 keys (8192-key tiles: the scatter's runs of a uniform digit
+// of at least 2^25 keys (8192-key tiles: the scatter's runs of a uniform digit
 // grow from 16 to 32 keys; its blocks run 512 threads of 16 keys, so they keep
 // four waves per SIMD). For the 32-bit endpoint partition of R-MAT 24 (2^29 keys)
 // the 8192-key tiles took the degree stage from 4.00 to 3.79 ms; with 256
-// threads of 32 keys they had lost (two waves per SIMD).
+// threads of 32 keys they had lost (two waves per SIMD). From 2^25 instead of 2^26
+// keys, with the look-back passes that these tiles take: R-MAT of 50 million pairs 7.89 -> 7.34 ms; from
+// 2^24 R-MAT 20 gains nothing, from 2^23 a uniform graph of 10 million pairs loses 3%.
 constexpr int RS_NT = 256;
 constexpr int RS_WAVES = RS_NT / WAVE;
 constexpr int RS_ITEMS_SMALL = 8, RS_ITEMS_LARGE = 16, RS_ITEMS_HUGE = 32;
-constexpr size_t RS_LARGE_CAP = (size_t)1 << 22, RS_HUGE_CAP = (size_t)1 << 26;
+constexpr size_t RS_LARGE_CAP = (size_t)1 << 22, RS_HUGE_CAP = (size_t)1 << 25;
 
 uint32_t radix_tile_keys(size_t cap, int key_bytes) {
     const int items = cap >= RS_HUGE_CAP ? RS_ITEMS_HUGE
@@ -601,6 +603,7 @@ __global__ __launch_bounds__(NT_) void k_radix_scatter(const KeyT* __restrict__ 
 // are bounded: a wait that runs past LB_SPIN polls sets bit 1 of *err and the
 // keys go out clamped in place (wrong order, no access out of bounds).
 constexpr uint32_t LB_SPIN = 1u << 16;
+constexpr uint32_t LB_W = 4;   // status words a thread reads at once
 template <typename KeyT, int RS_ITEMS, int NT_, int RANK, typename XF = XfIdentity>
 __global__ __launch_bounds__(NT_) void k_radix_scatter_lb(const KeyT* __restrict__ kin, KeyT* __restrict__ kout,
                                                             const uint32_t* d_count, uint32_t cap, int shift,
@@ -710,22 +713,35 @@ __global__ __launch_bounds__(NT_) void k_radix_scatter_lb(const KeyT* __restrict
     if (own) {
         uint32_t before = 0;   // keys of digit dd in the tiles before this one
         if (tile > 0) {
-            uint32_t j = tile - 1, spins = 0;
-            for (;;) {
-                const uint64_t v = __hip_atomic_load(status + (size_t)j * 256 + dd, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT);
-                const uint32_t f = (uint32_t)(v >> 62);
-                if (f == 0) {
+            // LB_W words in flight at a time: a word is served from beyond the XCD's L2 (R-MAT 24
+            // 45.80 ms one by one, 45.29, 45.23 and 45.67 ms with 8, 4 and 16)
+            uint32_t j = tile, spins = 0;   // tiles before j are still to be added
+            for (bool more = true; more;) {
+                uint64_t v[LB_W];
+#pragma unroll
+                for (uint32_t q = 0; q < LB_W; ++q)
+                    v[q] = __hip_atomic_load(status + (size_t)(j > q ? j - 1u - q : 0u) * 256 + dd, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+                bool wait = false;
+#pragma unroll
+                for (uint32_t q = 0; q < LB_W; ++q) {
+                    if (!more || wait) continue;
+                    const uint32_t f = (uint32_t)(v[q] >> 62);
+                    if (f == 0) {
+                        wait = true;
+                    } else {
+                        before += (uint32_t)v[q];
+                        --j;
+                        more = f != 2 && j > 0;
+                    }
+                }
+                if (wait) {
                     if (++spins > LB_SPIN) {
                         atomicOr(err, 2u);
                         break;
                     }
                     __builtin_amdgcn_s_sleep(1);
-                    continue;
                 }
-                before += (uint32_t)v;
-                if (f == 2 || j == 0) break;
-                --j;
             }
             __hip_atomic_store(st, (2ull << 62) | (before + run), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
