@@ -45,7 +45,7 @@ static unsigned grid_for(size_t n, unsigned cap = 16384) {
 // ------------------------------------------------------------------ degree
 // Input degree = loop-free valid pairs per vertex. Device-wide atomics would
 // serialise on hub vertices, so the 2E endpoints are first partitioned by
-// their high bits (one radix pass for ids of up to 24 bits, two up to 27), and
+// their high bits (one radix pass for ids of up to 25 bits, two up to 27), and
 // each bucket of 2^bw vertices is then counted in an LDS histogram of up to
 // 2^15 counters (128 KB); a wider bucket is counted in parts, each block
 // reading the whole bucket and counting the ids of its own part. Endpoints
@@ -53,7 +53,7 @@ static unsigned grid_for(size_t n, unsigned cap = 16384) {
 // each block also records how many it wrote, and they are taken off vertex
 // n - 1 at the end. Wider ids fall back to a full sort of the endpoints
 // (sentinel n, which sorts last) and run boundaries.
-constexpr int DEG_MAX_BW = 14;        // buckets of 2^14 vertices beyond 24-bit ids (two passes)
+constexpr int DEG_MAX_BW = 14;        // buckets of 2^14 vertices beyond 25-bit ids (two passes)
 constexpr int DEG_MAX_CW = 15;        // LDS histogram of at most 2^15 counters (128 KB)
 constexpr int DEG_MAX_BUCKET_BITS = 13;   // up to 8192 buckets (ids below 2^27)
 constexpr unsigned DEG_EP_BLOCKS = 1024;
@@ -63,7 +63,8 @@ __global__ __launch_bounds__(NT) void k_endpoints(const int2* __restrict__ edges
                                                   uint32_t* __restrict__ nsent, uint32_t* __restrict__ counts,
                                                   uint32_t ntiles, uint32_t tile_keys, RadixDigit dg,
                                                   uint32_t* __restrict__ pcounts, uint32_t pf, RadixDigit pdg,
-                                                  uint32_t* __restrict__ p2tot) {
+                                                  uint32_t* __restrict__ p2tot, uint32_t* __restrict__ deg) {
+    // deg: zeroed on the way, for the counts to come
     // tile t = endpoints [t * tile_keys, (t + 1) * tile_keys) = pairs [t * EPT, (t + 1) * EPT),
     // in rounds of NT * PER pairs; with counts set, the first digit of the endpoint sort is
     // counted per tile. With pcounts set, the digit pdg of the first id is counted too, per
@@ -80,6 +81,7 @@ __global__ __launch_bounds__(NT) void k_endpoints(const int2* __restrict__ edges
     if (pcounts) tp.clear();
     if (p2tot) tq.clear();
     __syncthreads();
+    for (int64_t v = (int64_t)blockIdx.x * NT + threadIdx.x; v < n; v += (int64_t)gridDim.x * NT) deg[v] = 0;
     bool bad = false;
     uint32_t sent = 0;
     for (uint32_t pt = blockIdx.x; pt < pntiles; pt += gridDim.x) {
@@ -145,26 +147,50 @@ __global__ __launch_bounds__(NT) void k_bucket_starts(const uint32_t* __restrict
     }
 }
 
-// Block (bucket b, part pt, split sp) counts, in LDS, the ids of part pt (ids
-// whose bits [cw, bw) equal pt, cw = min(bw, CW)) among its share of bucket b.
-// One split: plain stores of every count of the part; several: atomic adds
-// into the zeroed degree array. The 2^15-counter histogram leaves room for one
-// block per CU, so that size runs 1024 threads.
+// A block counts, in LDS, the ids of part pt (ids whose bits [cw, bw) equal pt,
+// cw = min(bw, CW)) among one stretch of at most `chunk` endpoints of a bucket
+// b: bucket b has ceil(size / chunk) stretches, blocks take them in bucket order (blocks past
+// the last one leave). A bucket of one stretch stores its counts; the others
+// add them to the degree array, which starts at zero. A hub makes its bucket
+// several times the mean, and its adds go to one LDS counter, a lane at a time,
+// so one block per bucket left the end of the kernel to that block (degree stage, one
+// stretch per bucket -> these: R-MAT 20 0.31 -> 0.28 ms, Chung-Lu of 6 million pairs
+// 0.35 -> 0.13 ms, of 148 million 6.15 -> 2.78 ms). Taking a wave's lanes that share
+// an id as one add instead was slower everywhere but in the last. The
+// 2^15-counter histogram leaves room for one block per CU, so that size runs 1024 threads.
 template <int CW, int NTB>
 __global__ __launch_bounds__(NTB) void k_bucket_count(const uint32_t* __restrict__ ep,
                                                       const uint32_t* __restrict__ bstart, int bw, uint32_t parts,
-                                                      uint32_t splits, int32_t n, uint32_t* __restrict__ deg) {
+                                                      uint32_t nb, uint32_t chunk, int32_t n,
+                                                      uint32_t* __restrict__ deg) {
     __shared__ uint32_t h[1u << CW];
+    __shared__ uint32_t s_bucket, s_stretch, s_stretches, scratch[NTB / WAVE];
     const int cw = bw < CW ? bw : CW;
     const uint32_t nh = 1u << cw, hmask = nh - 1u, bmask = (1u << bw) - 1u;
-    const uint32_t b = blockIdx.x / (parts * splits), rem = blockIdx.x % (parts * splits);
-    const uint32_t pt = rem / splits, sp = rem % splits;
+    const uint32_t slot = blockIdx.x / parts, pt = blockIdx.x % parts;
+    {   // the slot's bucket: a scan over the buckets' stretches
+        const uint32_t per = (nb + NTB - 1u) / NTB, q0 = threadIdx.x * per;
+        uint32_t cnt = 0, total;
+        for (uint32_t q = q0; q < q0 + per && q < nb; ++q) cnt += (bstart[q + 1] - bstart[q] + chunk - 1u) / chunk;
+        uint32_t at = block_exclusive_scan<NTB>(cnt, scratch, &total);
+        if (slot >= total) return;   // the same for the whole block
+        if (slot >= at && slot < at + cnt)
+            for (uint32_t q = q0;; ++q) {
+                const uint32_t c = (bstart[q + 1] - bstart[q] + chunk - 1u) / chunk;
+                if (slot < at + c) {
+                    s_bucket = q;
+                    s_stretch = slot - at;
+                    s_stretches = c;
+                    break;
+                }
+                at += c;
+            }
+    }
     for (uint32_t j = threadIdx.x; j < nh; j += NTB) h[j] = 0;
     __syncthreads();
-    const uint32_t s0 = bstart[b], s1 = bstart[b + 1];
-    const uint32_t len = s1 - s0;
-    const uint32_t a0 = s0 + (uint32_t)(((uint64_t)len * sp) / splits);
-    const uint32_t a1 = s0 + (uint32_t)(((uint64_t)len * (sp + 1)) / splits);
+    const uint32_t b = s_bucket, s0 = bstart[b], len = bstart[b + 1] - s0;
+    const uint32_t a0 = s0 + (uint32_t)(((uint64_t)len * s_stretch) / s_stretches);
+    const uint32_t a1 = s0 + (uint32_t)(((uint64_t)len * (s_stretch + 1u)) / s_stretches);
     constexpr int U = 8;
     for (uint32_t i0 = a0; i0 < a1; i0 += NTB * U) {
         uint32_t x[U];
@@ -184,25 +210,30 @@ __global__ __launch_bounds__(NTB) void k_bucket_count(const uint32_t* __restrict
     for (uint32_t j = threadIdx.x; j < nh; j += NTB) {
         const uint64_t v = v0 + j;
         if (v >= (uint64_t)n) break;
-        if (splits == 1) deg[v] = h[j];
+        if (s_stretches == 1) deg[v] = h[j];
         else if (h[j]) atomicAdd(&deg[v], h[j]);
     }
 }
 
-static void launch_bucket_count(const uint32_t* ep, const uint32_t* bst, int bw, uint32_t nb, uint32_t splits,
+// Endpoints per stretch: one and a half times the mean of 256 buckets (or of the buckets, where
+// they are more), so that ordinary buckets are one stretch and few buckets
+// still give enough blocks; at least 8192.
+static void launch_bucket_count(const uint32_t* ep, const uint32_t* bst, int bw, uint32_t nb, uint64_t len,
                                 int32_t n, uint32_t* deg, hipStream_t s) {
     const int cw = bw < DEG_MAX_CW ? bw : DEG_MAX_CW;
     const uint32_t parts = 1u << (bw - cw);
-    const dim3 grid(nb * parts * splits);
+    const uint64_t want = 3 * len / (2 * (uint64_t)(nb > 256u ? nb : 256u));
+    const uint32_t chunk = (uint32_t)(want > 8192 ? want : 8192);
+    const dim3 grid((unsigned)(parts * (nb + len / chunk + 1)));   // at least the stretches
     if (cw <= 12)
-        hipLaunchKernelGGL((k_bucket_count<12, NT>), grid, dim3(NT), 0, s, ep, bst, bw, parts, splits, n, deg);
+        hipLaunchKernelGGL((k_bucket_count<12, NT>), grid, dim3(NT), 0, s, ep, bst, bw, parts, nb, chunk, n, deg);
     else if (cw == 13)
-        hipLaunchKernelGGL((k_bucket_count<13, NT>), grid, dim3(NT), 0, s, ep, bst, bw, parts, splits, n, deg);
-    else if (cw == 14)   // ids past 24 bits: 2^14 counters (64 KB), 1024 threads (8 blocks ran 2 waves per SIMD)
-        hipLaunchKernelGGL((k_bucket_count<14, 1024>), grid, dim3(1024), 0, s, ep, bst, bw, parts, splits, n, deg);
+        hipLaunchKernelGGL((k_bucket_count<13, NT>), grid, dim3(NT), 0, s, ep, bst, bw, parts, nb, chunk, n, deg);
+    else if (cw == 14)   // ids past 25 bits: 2^14 counters (64 KB), 1024 threads (8 blocks ran 2 waves per SIMD)
+        hipLaunchKernelGGL((k_bucket_count<14, 1024>), grid, dim3(1024), 0, s, ep, bst, bw, parts, nb, chunk, n, deg);
     else
-        hipLaunchKernelGGL((k_bucket_count<DEG_MAX_CW, 1024>), grid, dim3(1024), 0, s, ep, bst, bw, parts, splits, n,
-                           deg);
+        hipLaunchKernelGGL((k_bucket_count<DEG_MAX_CW, 1024>), grid, dim3(1024), 0, s, ep, bst, bw, parts, nb, chunk,
+                           n, deg);
 }
 
 // deg[n - 1] -= the sentinel endpoints written by k_endpoints.
@@ -1218,17 +1249,17 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
     mark(0);
     // ---- degree: input pairs per vertex, from the sorted endpoints
     fill_u32((uint32_t*)ctrl, 0u, sizeof(Ctrl) / 4, s);
-    // bucket width: one partition pass of at most 8 bits up to 24-bit ids (buckets
-    // of 2^16 vertices counted in two parts at 24 bits), two (buckets of 2^14) up to 27 bits
+    // bucket width: one partition pass of at most 8 bits up to 25-bit ids (buckets
+    // of 2^17 vertices counted in four parts at 25 bits), two (buckets of 2^14) up to 27 bits
     const int vbits = bits_for((uint64_t)n);               // vertex ids fit in vbits bits
     const bool orient_part = vbits >= ORIENT_PART_MIN_BITS;
     uint32_t* p1_counts = nullptr;   // the orientation's first partition pass, counted by k_endpoints
     uint32_t p1_f = 1;
-    // and the digit totals of its second pass, which with 8192-key tiles (2^26 pairs or more)
+    // and the digit totals of its second pass, which with 8192-key tiles (2^25 pairs or more)
     // then looks back instead of running a histogram pass
     uint32_t* p2_tot =
         orient_part && radix_tile_keys((size_t)E, 8) == 8192u ? (uint32_t*)(ws + L.lb_aux) : nullptr;
-    const int bw = vbits <= 20 ? (vbits < 12 ? vbits : 12) : (vbits <= 24 ? vbits - 8 : DEG_MAX_BW);
+    const int bw = vbits <= 20 ? (vbits < 12 ? vbits : 12) : (vbits <= 25 ? vbits - 8 : DEG_MAX_BW);
     const bool bucketed = vbits - bw <= DEG_MAX_BUCKET_BITS;
     {
         uint32_t* ep = (uint32_t*)keysA;       // 2E uint32 fit in E uint64
@@ -1254,7 +1285,7 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         hipLaunchKernelGGL(k_endpoints, dim3(eg), dim3(NT), 0, s, edges, (uint64_t)E, n,
                            bucketed ? (uint32_t)(n - 1) : (uint32_t)n, ep, ctrl, partial,
                            ep_sort ? radix_first_counts(radix_tmp) : nullptr, ep_tiles, ep_tile, ep_dg, p1_counts,
-                           p1_f, RadixDigit{vbits - ORIENT_PART_BITS, (1u << ORIENT_PART_BITS) - 1u}, p2_tot);
+                           p1_f, RadixDigit{vbits - ORIENT_PART_BITS, (1u << ORIENT_PART_BITS) - 1u}, p2_tot, deg);
         if (bucketed) {
             // partition by bits [bw, vbits), then count per bucket
             const uint32_t nb = 1u << (vbits - bw);
@@ -1265,10 +1296,7 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
             uint32_t* bst = (uint32_t*)(ws + L.bstart);
             hipLaunchKernelGGL(k_bucket_starts, dim3(grid_for((size_t)nb + 1)), dim3(NT), 0, s, a0 ? ep_alt : ep,
                                (uint32_t)(2 * E), bw, nb, bst);
-            uint32_t splits = 1;
-            while (nb * splits < 256u && (uint64_t)splits * 65536u < (uint64_t)(2 * E) && splits < 64u) splits *= 2;
-            if (splits > 1) fill_u32(deg, 0u, (size_t)n, s);
-            launch_bucket_count(a0 ? ep_alt : ep, bst, bw, nb, splits, n, deg, s);
+            launch_bucket_count(a0 ? ep_alt : ep, bst, bw, nb, (uint64_t)(2 * E), n, deg, s);
             hipLaunchKernelGGL(k_drop_sentinels, dim3(1), dim3(NT), 0, s, partial, eg, n, deg);
         } else {
             const int a0 = radix_sort_u32(ep, ep_alt, nullptr, nullptr, nullptr, (size_t)(2 * E), 0,
