@@ -153,6 +153,9 @@ tc_status run(tc_ctx* ctx, const int32_t* d_edges, int64_t E, int32_t n, void* w
     ra.group_override = ctx->d_group;
     ra.grid_override = ctx->grid_override;
     ra.events = timing ? ctx->events : nullptr;
+    ra.result = d_result;
+    ra.range_status = (uint64_t)TC_ERR_VERTEX_RANGE;
+    ra.internal_status = (uint64_t)TC_ERR_HIP;
     if (E == 0 && d_result) {
         tcx::fill_u64(d_result, 0ull, 2, ctx->stream);
         if (ra.per_vertex && n > 0) tcx::fill_u64(ra.per_vertex, 0ull, (size_t)n, ctx->stream);
@@ -179,11 +182,9 @@ tc_status run(tc_ctx* ctx, const int32_t* d_edges, int64_t E, int32_t n, void* w
                        !ra.stop_before_isect && ra.formulation == tcx::FORM_FILTERED && !ra.per_edge_counts &&
                        !ra.support && !ra.csr_rank && !ra.per_middle && !ra.list_out;
     tcx::RunResult rr;
-    hipError_t e = small ? tcx::run_small(ra, d_result, (uint64_t)TC_ERR_VERTEX_RANGE, &rr)
-                         : tcx::run_pipeline(ra, &rr);
+    hipError_t e = small ? tcx::run_small(ra, &rr) : tcx::run_pipeline(ra, &rr);
     if (e != hipSuccess) return hip_fail(ctx, e, "launch");
     if (d_result) {
-        if (!small) tcx::publish_result(rr.ctrl_dev, d_result, (uint64_t)TC_ERR_VERTEX_RANGE, (uint64_t)TC_ERR_HIP, ctx->stream);
         ctx->have_times = 0;
         e = hipGetLastError();
         return e == hipSuccess ? TC_OK : hip_fail(ctx, e, "queue result");

@@ -25,7 +25,8 @@ void fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s);
 void fill_u64(uint64_t* p, uint64_t v, size_t n, hipStream_t s);
 size_t scan_temp_bytes();
 void scan_exclusive_sum_u32(const uint32_t* in, uint32_t* out, size_t len, void* temp, hipStream_t s);
-void scan_inclusive_max_u32(const uint32_t* in, uint32_t* out, size_t len, void* temp, hipStream_t s);
+// off[0] = 0, off[i + 1] = max(in[0..i]).
+void scan_offsets_max_u32(const uint32_t* in, uint32_t* off, size_t len, void* temp, hipStream_t s);
 void scan_exclusive_sum_u64(const uint64_t* in, uint64_t* out, size_t len, void* temp, hipStream_t s);
 size_t radix_temp_bytes(size_t cap);
 // Stable LSD sort of keys on bits [bit_lo, bit_hi) in ceil(bits / 8) passes of
@@ -102,6 +103,8 @@ RadixDigit radix_first_digit(int bit_lo, int bit_hi);
 // The first pass's count table inside temp: counts[d * ntiles + tile], 256
 // rows, ntiles = ceil(cap / radix_tile_keys(cap, key bytes)).
 uint32_t* radix_first_counts(void* temp);
+// After a sort of one pass (not a look-back one): the keys per digit, 256 counts.
+const uint32_t* radix_digit_totals(void* temp, size_t cap, int key_bytes);
 
 // ---- runsort.hip
 // Keys grouped by key >> shift (ascending; 1 <= shift <= 32) are sorted by the
@@ -132,8 +135,8 @@ struct Ctrl {
     uint32_t tile_next[NKERNEL + 1];  // per intersection kernel: tiles handed out after the first per block
                                       // (zeroed before every launch)
     uint64_t wedges;                  // sum over v of C(d(v), 2), simple degree (clustering runs only)
-    uint32_t bstart[NBUCKET];         // first / one-past-last position of each bucket
-    uint32_t bend[NBUCKET];           //   in the (kernel, bucket)-ordered vertex list
+    uint32_t bstart[NBUCKET];         // first / one-past-last position of each bucket in the
+    uint32_t bend[NBUCKET];           //   (kernel, bucket)-ordered vertex list (set by k_select)
     uint32_t bucket_nv[NBUCKET];      // vertices per bucket
     uint64_t bucket_in[NBUCKET];      // sum of in-degrees (non-empty tails) per bucket
     uint64_t bucket_out[NBUCKET];     // sum of out-degrees per bucket

@@ -50,10 +50,19 @@ int isect_blocks_per_cu(int ker, int mode);
 // First of the top ranks whose per-vertex counts are kept in LDS.
 uint32_t isect_hot_first(uint32_t n);
 size_t isect_partials_bytes();
-// One intersection kernel over its tile range (the bitmap strategy: two kernels, when a.hub is set); per-block partial counts go to
-// partials (isect_partials_bytes() of workspace shared by the three kernels).
-void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hipStream_t s);
-// ctrl->total = sum of all partial counts.
-void launch_reduce_total(uint64_t* partials, Ctrl* ctrl, hipStream_t s);
+// Partial counts that the kernels of one intersection stage write: `n` of them from `first` on,
+// per launch.
+struct IsectParts {
+    int launches = 0;
+    uint32_t first[NKERNEL + 1], n[NKERNEL + 1];
+};
+// One intersection kernel over its tile range (the bitmap strategy: two kernels, when a.hub is set);
+// per-block partial counts go to partials (isect_partials_bytes() of workspace shared by the
+// kernels), their places are added to parts (may be null).
+void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hipStream_t s, IsectParts* parts = nullptr);
+// ctrl->total = sum of all partial counts. With result (may be null): result[0] = the total,
+// result[1] = range_status for an id out of range, internal_status for another error bit, else 0.
+void launch_reduce_total(const uint64_t* partials, const IsectParts& parts, Ctrl* ctrl, uint64_t* result,
+                         uint64_t range_status, uint64_t internal_status, hipStream_t s);
 
 }  // namespace tcx

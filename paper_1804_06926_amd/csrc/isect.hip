@@ -1002,12 +1002,27 @@ __global__ __launch_bounds__(IS_NT, VERTEX ? 4 : (MERGE ? 7 : 6)) void k_isect_e
     block_partial(acc, partials);
 }
 
-// Sum of the per-block partial counts of all three kernels, in a fixed order.
-__global__ __launch_bounds__(IS_NT) void k_reduce_total(const uint64_t* __restrict__ partials, uint32_t count,
-                                                        Ctrl* ctrl) {
+// Sum of the per-block partial counts of the stage's kernels, in a fixed order.
+constexpr int RED_NT = 1024;
+__global__ __launch_bounds__(RED_NT) void k_reduce_total(const uint64_t* __restrict__ partials, IsectParts parts,
+                                                         Ctrl* ctrl, uint64_t* result, uint64_t range_status,
+                                                         uint64_t internal_status) {
+    __shared__ uint64_t red[RED_NT / WAVE];
     uint64_t acc = 0;
-    for (uint32_t i = threadIdx.x; i < count; i += IS_NT) acc += partials[i];
-    block_partial(acc, &ctrl->total);
+    for (int q = 0; q < parts.launches; ++q)
+        for (uint32_t i = threadIdx.x; i < parts.n[q]; i += RED_NT) acc += partials[parts.first[q] + i];
+    acc = wave_sum_u64(acc);
+    if (lane_id() == 0) red[wave_id()] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t s = 0;
+        for (int i = 0; i < RED_NT / WAVE; ++i) s += red[i];
+        ctrl->total = s;
+        if (result) {
+            result[0] = s;
+            result[1] = (ctrl->err & 1u) ? range_status : (ctrl->err ? internal_status : 0ull);
+        }
+    }
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1079,19 +1094,25 @@ uint32_t isect_hot_first(uint32_t n) { return n > HOT_N ? n - HOT_N : 0u; }
 
 size_t isect_partials_bytes() { return sizeof(uint64_t) * NKERNEL * PARTIALS_PER_KERNEL; }
 
-void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hipStream_t s) {
+void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hipStream_t s, IsectParts* parts) {
     const int mode = ker == KER_BITMAP ? bitmap_mode(a) : (a.per_vertex ? BM_VERTEX : BM_COUNT);
     if (grid <= 0) grid = num_cu() * isect_blocks_per_cu(ker, mode);
     const bool hub = ker == KER_BITMAP && a.hub;
     const int cap = hub ? HB_PARTIAL0 : PARTIALS_PER_KERNEL;
     if (grid > cap) grid = cap;
     uint64_t* p = partials + (size_t)ker * PARTIALS_PER_KERNEL;
-    fill_u64(p, 0ull, PARTIALS_PER_KERNEL, s);
+    auto note = [&](uint32_t first, int n) {   // every block of a launch writes its partial
+        if (!parts) return;
+        parts->first[parts->launches] = (uint32_t)(p - partials) + first;
+        parts->n[parts->launches++] = (uint32_t)n;
+    };
+    note(0, grid);
     if (hub) {
         static int per_cu = 0;
         if (!per_cu) per_cu = resident_blocks((const void*)k_isect_hub<false>, HB_NT);
         int hg = num_cu() * per_cu;
         if (hg > PARTIALS_PER_KERNEL - HB_PARTIAL0) hg = PARTIALS_PER_KERNEL - HB_PARTIAL0;
+        note(HB_PARTIAL0, hg);
         if (a.per_middle)
             hipLaunchKernelGGL(k_isect_hub<true>, dim3(hg), dim3(HB_NT), 0, s, a, p + HB_PARTIAL0);
         else
@@ -1134,9 +1155,10 @@ void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hip
     }
 }
 
-void launch_reduce_total(uint64_t* partials, Ctrl* ctrl, hipStream_t s) {
-    hipLaunchKernelGGL(k_reduce_total, dim3(1), dim3(IS_NT), 0, s, partials, (uint32_t)(NKERNEL * PARTIALS_PER_KERNEL),
-                       ctrl);
+void launch_reduce_total(const uint64_t* partials, const IsectParts& parts, Ctrl* ctrl, uint64_t* result,
+                         uint64_t range_status, uint64_t internal_status, hipStream_t s) {
+    hipLaunchKernelGGL(k_reduce_total, dim3(1), dim3(RED_NT), 0, s, partials, parts, ctrl, result, range_status,
+                       internal_status);
 }
 
 }  // namespace tcx

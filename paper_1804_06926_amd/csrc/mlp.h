@@ -40,6 +40,5 @@ void mlp_gradient(const MlpCompute* cw, const float* X, const int32_t* y, const 
                   float* grad, float* loss, hipStream_t s);   // part: MLP_GRAD_ROWS rows
 void mlp_adam(float* master, const float* grad, float* m, float* v, float lr, int step, hipStream_t s);
 void mlp_select(const MlpCompute* cw, Ctrl* ctrl, uint8_t* choice, hipStream_t s);
-void bucket_features_launch(Ctrl* ctrl, hipStream_t s);
 
 }  // namespace tcx

@@ -15,6 +15,7 @@
 #include "common.h"
 #include "internal.h"
 #include "mlp.h"
+#include "tiles.h"
 
 namespace tcx {
 
@@ -259,20 +260,6 @@ __global__ __launch_bounds__(256) void k_mlp_adam(float* __restrict__ master, co
     master[p] -= lr * (mp / c1) / (sqrtf(vp / c2) + eps);
 }
 
-// Bucket features (6 floats): the bucket's two degree classes and the log
-// sizes of its work, from the statistics gathered by the pipeline: the
-// LDS-bitmap windows its middle lists span (the bitmap strategy's set-up
-// count, which grows with the rank range a list covers and so with the
-// graph's size), in-edges, out-neighbours, and in-edges x out-degree.
-__device__ void bucket_features(const Ctrl* ctrl, int b, float (&f)[MLP_IN]) {
-    f[0] = (float)(b >> 4) / 14.f;
-    f[1] = (float)(b & 15) / 15.f;
-    f[2] = log2f(1.f + (float)ctrl->bucket_win[b]) / 32.f;
-    f[3] = log2f(1.f + (float)ctrl->bucket_in[b]) / 32.f;
-    f[4] = log2f(1.f + (float)ctrl->bucket_out[b]) / 32.f;
-    f[5] = log2f(1.f + (float)ctrl->bucket_work[b]) / 48.f;
-}
-
 // One bucket per group of lanes; the logits are those of k_mlp_forward. Argmax
 // ties go to the lower index.
 __global__ __launch_bounds__(NET_NT) void k_mlp_select(const MlpCompute* __restrict__ cw, Ctrl* ctrl,
@@ -292,13 +279,6 @@ __global__ __launch_bounds__(NET_NT) void k_mlp_select(const MlpCompute* __restr
         if (z[2] > (best ? z[1] : z[0])) best = 2;
         choice[b] = (uint8_t)best;
     }
-}
-
-// Features only (heuristic and forced modes), for training data.
-__global__ __launch_bounds__(NBUCKET) void k_bucket_features(Ctrl* ctrl) {
-    float x[MLP_IN];
-    bucket_features(ctrl, threadIdx.x, x);
-    for (int i = 0; i < MLP_IN; ++i) ctrl->features[threadIdx.x][i] = x[i];
 }
 
 // ------------------------------------------------------------------ launchers
@@ -328,8 +308,4 @@ void mlp_adam(float* master, const float* grad, float* m, float* v, float lr, in
 void mlp_select(const MlpCompute* cw, Ctrl* ctrl, uint8_t* choice, hipStream_t s) {
     hipLaunchKernelGGL(k_mlp_select, dim3(NBUCKET / NET_S), dim3(NET_NT), 0, s, cw, ctrl, choice);
 }
-void bucket_features_launch(Ctrl* ctrl, hipStream_t s) {
-    hipLaunchKernelGGL(k_bucket_features, dim3(1), dim3(NBUCKET), 0, s, ctrl);
-}
-
 }  // namespace tcx

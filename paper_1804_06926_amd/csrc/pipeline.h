@@ -63,6 +63,8 @@ struct RunArgs {
     uint32_t* list_cur;              //   device [m] zeroed cursors
     int32_t* list_out;               //   device [list_cap][3] output
     uint64_t list_cap;
+    uint64_t* result;                // device [2] or null: T and the status at the end (a queued call)
+    uint64_t range_status, internal_status;   // status values for an id out of range, another error bit
     int formulation;                 // FORM_*; other than FORM_FILTERED: T only (no per-edge or
                                      // per-vertex outputs), workspace make_layout + sym_extra_bytes
 };
@@ -82,14 +84,9 @@ constexpr int64_t SMALL_MAX_PAIRS = 1 << 17;
 bool small_graph(int64_t E, int32_t n);
 size_t small_workspace(int64_t E, int32_t n);   // 0 for other sizes
 // The whole count; the control block ends up at the start of the workspace, as
-// run_pipeline's. With result (a queued call) T and the status go to result[0..1], as
-// publish_result's; without it the statistics that tc_last_stats reports are taken too.
-hipError_t run_small(const RunArgs& r, uint64_t* result, uint64_t range_status, RunResult* out);
-// Copies T and the status of a finished run to result[0..1] (device): range_status
-// for an id out of range, internal_status for a violated internal bound, else 0.
-void publish_result(const Ctrl* ctrl, uint64_t* result, uint64_t range_status, uint64_t internal_status,
-                    hipStream_t s);
-
+// run_pipeline's. Without r.result (a queued call) the statistics that tc_last_stats
+// reports are taken too.
+hipError_t run_small(const RunArgs& r, RunResult* out);
 // ---- batched counting (batch.hip)
 struct BatchLayout {
     Layout pipe;   // the union graph's pipeline workspace comes first

@@ -132,26 +132,30 @@ __global__ __launch_bounds__(NT) void k_endpoints(const int2* __restrict__ edges
     }
 }
 
-// bstart[b] = first position of bucket b (ids >> bw == b) in the endpoints,
-// which the partition left ordered by bucket; bstart[nb] = len.
-__global__ __launch_bounds__(NT) void k_bucket_starts(const uint32_t* __restrict__ ep, uint32_t len, int bw,
-                                                      uint32_t nb, uint32_t* __restrict__ bstart) {
-    for (uint32_t b = blockIdx.x * NT + threadIdx.x; b <= nb; b += gridDim.x * NT) {
-        uint32_t lo = 0, hi = len;
-        while (lo < hi) {
-            const uint32_t mid = lo + (hi - lo) / 2;
-            if ((ep[mid] >> bw) < b) lo = mid + 1;
-            else hi = mid;
+// tot[b] = endpoints of bucket b (ids >> bw == b), which the partition left
+// ordered by bucket; for partitions of several passes (one pass leaves its digit totals).
+__global__ __launch_bounds__(NT) void k_bucket_sizes(const uint32_t* __restrict__ ep, uint32_t len, int bw,
+                                                     uint32_t nb, uint32_t* __restrict__ tot) {
+    for (uint32_t b = blockIdx.x * NT + threadIdx.x; b < nb; b += gridDim.x * NT) {
+        uint32_t at[2];
+        for (uint32_t q = 0; q < 2; ++q) {   // first positions of buckets b and b + 1
+            uint32_t lo = 0, hi = len;
+            while (lo < hi) {
+                const uint32_t mid = lo + (hi - lo) / 2;
+                if ((ep[mid] >> bw) < b + q) lo = mid + 1;
+                else hi = mid;
+            }
+            at[q] = b + q == nb ? len : lo;
         }
-        bstart[b] = b == nb ? len : lo;
+        tot[b] = at[1] - at[0];
     }
 }
 
 // A block counts, in LDS, the ids of part pt (ids whose bits [cw, bw) equal pt,
 // cw = min(bw, CW)) among one stretch of at most `chunk` endpoints of a bucket
 // b: bucket b has ceil(size / chunk) stretches, blocks take them in bucket order (blocks past
-// the last one leave). A bucket of one stretch stores its counts; the others
-// add them to the degree array, which starts at zero. A hub makes its bucket
+// the last one leave). tot: endpoints per bucket (null: one bucket of len_all). A bucket of one
+// stretch stores its counts; the others add them to the degree array, which starts at zero. A hub makes its bucket
 // several times the mean, and its adds go to one LDS counter, a lane at a time,
 // so one block per bucket left the end of the kernel to that block (degree stage, one
 // stretch per bucket -> these: R-MAT 20 0.31 -> 0.28 ms, Chung-Lu of 6 million pairs
@@ -160,35 +164,43 @@ __global__ __launch_bounds__(NT) void k_bucket_starts(const uint32_t* __restrict
 // 2^15-counter histogram leaves room for one block per CU, so that size runs 1024 threads.
 template <int CW, int NTB>
 __global__ __launch_bounds__(NTB) void k_bucket_count(const uint32_t* __restrict__ ep,
-                                                      const uint32_t* __restrict__ bstart, int bw, uint32_t parts,
-                                                      uint32_t nb, uint32_t chunk, int32_t n,
+                                                      const uint32_t* __restrict__ tot, uint32_t len_all, int bw,
+                                                      uint32_t parts, uint32_t nb, uint32_t chunk, int32_t n,
                                                       uint32_t* __restrict__ deg) {
     __shared__ uint32_t h[1u << CW];
-    __shared__ uint32_t s_bucket, s_stretch, s_stretches, scratch[NTB / WAVE];
+    __shared__ uint32_t s_bucket, s_start, s_size, s_stretch, s_stretches, scratch[NTB / WAVE];
     const int cw = bw < CW ? bw : CW;
     const uint32_t nh = 1u << cw, hmask = nh - 1u, bmask = (1u << bw) - 1u;
     const uint32_t slot = blockIdx.x / parts, pt = blockIdx.x % parts;
-    {   // the slot's bucket: a scan over the buckets' stretches
+    {   // the slot's bucket: a scan over the buckets' stretches, and over their sizes for its start
         const uint32_t per = (nb + NTB - 1u) / NTB, q0 = threadIdx.x * per;
-        uint32_t cnt = 0, total;
-        for (uint32_t q = q0; q < q0 + per && q < nb; ++q) cnt += (bstart[q + 1] - bstart[q] + chunk - 1u) / chunk;
+        uint32_t cnt = 0, size = 0, total;
+        for (uint32_t q = q0; q < q0 + per && q < nb; ++q) {
+            const uint32_t c = tot ? tot[q] : len_all;
+            cnt += (c + chunk - 1u) / chunk;
+            size += c;
+        }
         uint32_t at = block_exclusive_scan<NTB>(cnt, scratch, &total);
+        uint32_t pos = block_exclusive_scan<NTB>(size, scratch);
         if (slot >= total) return;   // the same for the whole block
         if (slot >= at && slot < at + cnt)
             for (uint32_t q = q0;; ++q) {
-                const uint32_t c = (bstart[q + 1] - bstart[q] + chunk - 1u) / chunk;
+                const uint32_t sz = tot ? tot[q] : len_all, c = (sz + chunk - 1u) / chunk;
                 if (slot < at + c) {
                     s_bucket = q;
+                    s_start = pos;
+                    s_size = sz;
                     s_stretch = slot - at;
                     s_stretches = c;
                     break;
                 }
                 at += c;
+                pos += sz;
             }
     }
     for (uint32_t j = threadIdx.x; j < nh; j += NTB) h[j] = 0;
     __syncthreads();
-    const uint32_t b = s_bucket, s0 = bstart[b], len = bstart[b + 1] - s0;
+    const uint32_t b = s_bucket, s0 = s_start, len = s_size;
     const uint32_t a0 = s0 + (uint32_t)(((uint64_t)len * s_stretch) / s_stretches);
     const uint32_t a1 = s0 + (uint32_t)(((uint64_t)len * (s_stretch + 1u)) / s_stretches);
     constexpr int U = 8;
@@ -218,7 +230,7 @@ __global__ __launch_bounds__(NTB) void k_bucket_count(const uint32_t* __restrict
 // Endpoints per stretch: one and a half times the mean of 256 buckets (or of the buckets, where
 // they are more), so that ordinary buckets are one stretch and few buckets
 // still give enough blocks; at least 8192.
-static void launch_bucket_count(const uint32_t* ep, const uint32_t* bst, int bw, uint32_t nb, uint64_t len,
+static void launch_bucket_count(const uint32_t* ep, const uint32_t* tot, int bw, uint32_t nb, uint64_t len,
                                 int32_t n, uint32_t* deg, hipStream_t s) {
     const int cw = bw < DEG_MAX_CW ? bw : DEG_MAX_CW;
     const uint32_t parts = 1u << (bw - cw);
@@ -226,30 +238,17 @@ static void launch_bucket_count(const uint32_t* ep, const uint32_t* bst, int bw,
     const uint32_t chunk = (uint32_t)(want > 8192 ? want : 8192);
     const dim3 grid((unsigned)(parts * (nb + len / chunk + 1)));   // at least the stretches
     if (cw <= 12)
-        hipLaunchKernelGGL((k_bucket_count<12, NT>), grid, dim3(NT), 0, s, ep, bst, bw, parts, nb, chunk, n, deg);
+        hipLaunchKernelGGL((k_bucket_count<12, NT>), grid, dim3(NT), 0, s, ep, tot, (uint32_t)len, bw, parts, nb, chunk, n,
+                           deg);
     else if (cw == 13)
-        hipLaunchKernelGGL((k_bucket_count<13, NT>), grid, dim3(NT), 0, s, ep, bst, bw, parts, nb, chunk, n, deg);
+        hipLaunchKernelGGL((k_bucket_count<13, NT>), grid, dim3(NT), 0, s, ep, tot, (uint32_t)len, bw, parts, nb, chunk, n,
+                           deg);
     else if (cw == 14)   // ids past 25 bits: 2^14 counters (64 KB), 1024 threads (8 blocks ran 2 waves per SIMD)
-        hipLaunchKernelGGL((k_bucket_count<14, 1024>), grid, dim3(1024), 0, s, ep, bst, bw, parts, nb, chunk, n, deg);
+        hipLaunchKernelGGL((k_bucket_count<14, 1024>), grid, dim3(1024), 0, s, ep, tot, (uint32_t)len, bw, parts, nb, chunk, n,
+                           deg);
     else
-        hipLaunchKernelGGL((k_bucket_count<DEG_MAX_CW, 1024>), grid, dim3(1024), 0, s, ep, bst, bw, parts, nb, chunk,
-                           n, deg);
-}
-
-// deg[n - 1] -= the sentinel endpoints written by k_endpoints.
-__global__ __launch_bounds__(NT) void k_drop_sentinels(const uint32_t* __restrict__ nsent, uint32_t nblocks,
-                                                       int32_t n, uint32_t* __restrict__ deg) {
-    __shared__ uint32_t red[NT / WAVE];
-    uint32_t t = 0;
-    for (uint32_t i = threadIdx.x; i < nblocks; i += NT) t += nsent[i];
-    t = wave_sum(t);
-    if (lane_id() == 0) red[wave_id()] = t;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t s = 0;
-        for (int k = 0; k < NT / WAVE; ++k) s += red[k];
-        deg[n - 1] -= s;
-    }
+        hipLaunchKernelGGL((k_bucket_count<DEG_MAX_CW, 1024>), grid, dim3(1024), 0, s, ep, tot, (uint32_t)len, bw, parts, nb,
+                           chunk, n, deg);
 }
 
 // dend[v] = one past the last occurrence of v among the sorted endpoints.
@@ -261,22 +260,86 @@ __global__ __launch_bounds__(NT) void k_endpoint_bounds(const uint32_t* __restri
     }
 }
 
-// Key (degree, id); OFFSETS: deg holds degree offsets [n + 1], else counts [n].
+// Key (min(degree, RANK_CAP), id), sorted on its upper half: two passes. The few
+// vertices of degree RANK_CAP or more (at most 2E / RANK_CAP) share the last
+// place there and are ordered by k_rank. (Sorting whole degrees took three or four
+// passes, for bits that a handful of hubs have; the rank stage with two, and with the first
+// digit counted here: R-MAT 20 85 -> 54 us, R-MAT 24 0.61 -> 0.43 ms.) OFFSETS: deg holds degree offsets
+// [n + 1], else counts [n], where vertex n - 1 still counts the sentinel
+// endpoints of nsent[0..nblocks): they are taken off here.
+constexpr uint32_t RANK_CAP = 0xFFFFu;
+constexpr int RANK_BITS = 16;
+
 template <bool OFFSETS>
-__global__ __launch_bounds__(NT) void k_vertex_keys(const uint32_t* __restrict__ deg, int32_t n,
-                                                    uint64_t* __restrict__ keys) {
-    for (int64_t v = (int64_t)blockIdx.x * NT + threadIdx.x; v < n; v += (int64_t)gridDim.x * NT) {
-        const uint32_t d = OFFSETS ? deg[v + 1] - deg[v] : deg[v];
-        keys[v] = ((uint64_t)d << 32) | (uint32_t)v;
+__device__ __forceinline__ uint32_t degree_at(const uint32_t* __restrict__ deg, uint32_t v) {
+    return OFFSETS ? deg[v + 1] - deg[v] : deg[v];
+}
+
+template <bool OFFSETS>
+__global__ __launch_bounds__(NT) void k_vertex_keys(uint32_t* __restrict__ deg, int32_t n,
+                                                    const uint32_t* __restrict__ nsent, uint32_t nblocks,
+                                                    uint64_t* __restrict__ keys, uint32_t* __restrict__ counts,
+                                                    uint32_t ntiles, uint32_t tile_keys, RadixDigit dg) {
+    __shared__ TileCounts tc;
+    __shared__ uint32_t s_sent;
+    tc.clear();
+    if (threadIdx.x == 0) s_sent = 0;
+    __syncthreads();
+    for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        if (!OFFSETS && tile == ntiles - 1) {   // the tile of vertex n - 1
+            uint32_t t = 0;
+            for (uint32_t i = threadIdx.x; i < nblocks; i += NT) t += nsent[i];
+            t = wave_sum(t);
+            if (lane_id() == 0) atomicAdd(&s_sent, t);
+            __syncthreads();
+        }
+        for (uint32_t r = threadIdx.x; r < tile_keys; r += NT) {
+            const uint64_t v = (uint64_t)tile * tile_keys + r;
+            if (v >= (uint64_t)n) break;
+            uint32_t d = degree_at<OFFSETS>(deg, (uint32_t)v);
+            if (!OFFSETS && v == (uint64_t)n - 1) {
+                d -= s_sent;
+                deg[v] = d;
+            }
+            const uint64_t key = ((uint64_t)(d < RANK_CAP ? d : RANK_CAP) << 32) | (uint32_t)v;
+            keys[v] = key;
+            tc.add((uint32_t)(key >> dg.shift) & dg.mask);
+        }
+        tc.flush(counts, ntiles, tile);
     }
 }
 
+// rank[v] = position of v; inv its inverse. Vertices of degree RANK_CAP or more stand
+// last, by id: each finds its place by comparing (degree, id) with the
+// others. Also clears rowend[0..n) and part[0..npart) for the stages to come.
+template <bool OFFSETS>
 __global__ __launch_bounds__(NT) void k_rank(const uint64_t* __restrict__ sorted, int32_t n,
-                                             uint32_t* __restrict__ rank, uint32_t* __restrict__ inv) {
+                                             const uint32_t* __restrict__ deg, uint32_t* __restrict__ rank,
+                                             uint32_t* __restrict__ inv, uint32_t* __restrict__ rowend,
+                                             uint32_t* __restrict__ part, uint32_t npart) {
+    for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < npart; i += gridDim.x * NT) part[i] = 0;
     for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) {
-        const uint32_t v = (uint32_t)sorted[i];
-        rank[v] = (uint32_t)i;
-        inv[i] = v;
+        const uint64_t key = sorted[i];
+        const uint32_t v = (uint32_t)key;
+        uint32_t pos = (uint32_t)i;
+        if ((uint32_t)(key >> 32) == RANK_CAP) {
+            uint32_t lo = 0, hi = (uint32_t)i;   // first of the capped keys
+            while (lo < hi) {
+                const uint32_t mid = lo + (hi - lo) / 2;
+                if ((uint32_t)(sorted[mid] >> 32) < RANK_CAP) lo = mid + 1;
+                else hi = mid;
+            }
+            pos = lo;
+            const uint32_t d = degree_at<OFFSETS>(deg, v);
+#pragma unroll 4
+            for (uint32_t j = lo; j < (uint32_t)n; ++j) {
+                const uint32_t u = (uint32_t)sorted[j], du = degree_at<OFFSETS>(deg, u);
+                pos += (du < d || (du == d && u < v)) ? 1u : 0u;
+            }
+        }
+        rank[v] = pos;
+        inv[pos] = v;
+        rowend[i] = 0;
     }
 }
 
@@ -477,7 +540,9 @@ __global__ __launch_bounds__(NT) void k_csc_keys(const uint32_t* __restrict__ co
                                                  const uint32_t* __restrict__ off, Ctrl* ctrl, int32_t n,
                                                  uint64_t* __restrict__ keys, int sh, int lbits,
                                                  uint32_t* __restrict__ counts, uint32_t ntiles, uint32_t tile_keys,
-                                                 RadixDigit dg) {
+                                                 RadixDigit dg, uint32_t* __restrict__ inend) {
+    // inend[0..n): cleared on the way, for k_csc_finish
+    for (int64_t v = (int64_t)blockIdx.x * NT + threadIdx.x; v < n; v += (int64_t)gridDim.x * NT) inend[v] = 0;
     __shared__ TileCounts tc;
     tc.clear();
     __syncthreads();
@@ -673,9 +738,15 @@ __global__ __launch_bounds__(NBUCKET) void k_select(Ctrl* ctrl, int mode, const 
                                                     const uint8_t* __restrict__ learned_tile,
                                                     const uint16_t* __restrict__ chunk_override,
                                                     const uint8_t* __restrict__ group_override, int whole_rows,
-                                                    HubTab* __restrict__ hub) {
-    __shared__ __align__(16) uint32_t s_key[NBUCKET];
+                                                    int features, HubTab* __restrict__ hub) {
+    __shared__ __align__(16) uint32_t s_key[NBUCKET], s_nv[NBUCKET];
     const int b = threadIdx.x;
+    s_nv[b] = b == BUCKET_NONE ? 0u : ctrl->bucket_nv[b];
+    if (features) {   // the selector networks write them otherwise
+        float f[MLP_IN];
+        bucket_features(ctrl, b, f);
+        for (int i = 0; i < MLP_IN; ++i) ctrl->features[b][i] = f[i];
+    }
     if (hub) hub->first[b] = ~0u;   // set by k_emit_tiles
     int ch;
     if (mode == SEL_FORCE_MERGE) ch = KER_MERGE;
@@ -722,39 +793,47 @@ __global__ __launch_bounds__(NBUCKET) void k_select(Ctrl* ctrl, int mode, const 
     const uint32_t key = (b == BUCKET_NONE) ? 0xFFFFFFFFu : ((uint32_t)ch << 16) | (uint32_t)(255 - (16 * lo + li));
     s_key[b] = key;
     __syncthreads();
-    uint32_t r = 0;
+    uint32_t r = 0, at = 0;   // buckets before this one, and their vertices
 #pragma unroll 8
     for (int q = 0; q < NBUCKET; q += 4) {   // keys are distinct but for the empty bucket's, the highest
-        const uint4 k = *(const uint4*)&s_key[q];
+        const uint4 k = *(const uint4*)&s_key[q], c = *(const uint4*)&s_nv[q];
         r += (k.x < key ? 1u : 0u) + (k.y < key ? 1u : 0u) + (k.z < key ? 1u : 0u) + (k.w < key ? 1u : 0u);
+        at += (k.x < key ? c.x : 0u) + (k.y < key ? c.y : 0u) + (k.z < key ? c.z : 0u) + (k.w < key ? c.w : 0u);
     }
     ctrl->slot[b] = (uint8_t)r;
+    ctrl->bstart[b] = at;
+    ctrl->bend[b] = at + s_nv[b];
 }
 
 __global__ __launch_bounds__(NT) void k_vkeys_slot(const uint8_t* __restrict__ vbucket, int32_t n, const Ctrl* ctrl,
-                                                   uint64_t* __restrict__ keys) {
-    for (int64_t v = (int64_t)blockIdx.x * NT + threadIdx.x; v < n; v += (int64_t)gridDim.x * NT)
-        keys[v] = ((uint64_t)ctrl->slot[vbucket[v]] << 32) | (uint32_t)v;
-}
-
-__global__ __launch_bounds__(NT) void k_vpos(const uint64_t* __restrict__ sorted, int32_t n,
-                                             const uint8_t* __restrict__ vbucket, Ctrl* ctrl,
-                                             uint32_t* __restrict__ vlist) {
-    for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) {
-        const uint32_t v = (uint32_t)sorted[i];
-        const uint32_t slot = (uint32_t)(sorted[i] >> 32);
-        vlist[i] = v;
-        const uint32_t b = vbucket[v];
-        if (i == 0 || (uint32_t)(sorted[i - 1] >> 32) != slot) ctrl->bstart[b] = (uint32_t)i;
-        if (i == n - 1 || (uint32_t)(sorted[i + 1] >> 32) != slot) ctrl->bend[b] = (uint32_t)(i + 1);
+                                                   uint64_t* __restrict__ keys, uint32_t* __restrict__ counts,
+                                                   uint32_t ntiles, uint32_t tile_keys, RadixDigit dg) {
+    __shared__ TileCounts tc;
+    __shared__ uint8_t s_slot[NBUCKET];
+    tc.clear();
+    s_slot[threadIdx.x] = ctrl->slot[threadIdx.x];
+    __syncthreads();
+    static_assert(NT == NBUCKET, "a slot per thread");
+    for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        for (uint32_t r = threadIdx.x; r < tile_keys; r += NT) {
+            const uint64_t v = (uint64_t)tile * tile_keys + r;
+            if (v >= (uint64_t)n) break;
+            const uint64_t key = ((uint64_t)s_slot[vbucket[v]] << 32) | (uint32_t)v;
+            keys[v] = key;
+            tc.add((uint32_t)(key >> dg.shift) & dg.mask);
+        }
+        tc.flush(counts, ntiles, tile);
     }
 }
 
-__global__ __launch_bounds__(NT) void k_ntiles(const uint32_t* __restrict__ vlist, const uint8_t* __restrict__ vbucket,
+// The vertex list and the tiles that start at each of its positions.
+__global__ __launch_bounds__(NT) void k_ntiles(const uint64_t* __restrict__ sorted, uint32_t* __restrict__ vlist,
+                                               const uint8_t* __restrict__ vbucket,
                                                const uint32_t* __restrict__ inoff, int32_t n, const Ctrl* ctrl,
                                                uint32_t* __restrict__ ntile) {
     for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) {
-        const uint32_t v = vlist[i];
+        const uint32_t v = (uint32_t)sorted[i];
+        vlist[i] = v;
         const uint32_t b = vbucket[v];
         uint32_t t = 0;
         if (b != BUCKET_NONE) {
@@ -990,19 +1069,6 @@ static void reset_tile_counters(Ctrl* ctrl, hipStream_t s) {
     fill_u32(ctrl->tile_next, 0u, NKERNEL + 1, s);
 }
 
-// result[0] = T, result[1] = range_status when an id was out of range, else 0.
-__global__ void k_publish(const Ctrl* ctrl, uint64_t* result, uint64_t range_status, uint64_t internal_status) {
-    if (threadIdx.x == 0) {
-        result[0] = ctrl->total;
-        result[1] = (ctrl->err & 1u) ? range_status : (ctrl->err ? internal_status : 0ull);
-    }
-}
-
-void publish_result(const Ctrl* ctrl, uint64_t* result, uint64_t range_status, uint64_t internal_status,
-                    hipStream_t s) {
-    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, ctrl, result, range_status, internal_status);
-}
-
 // Packed in-edge keys: v, e, and the tail length in the bits left over (at
 // most what the bound d+(u) <= sqrt(2E) needs; lengths that do not fit are
 // escaped). Without room for at least 6 length bits, e alone is kept.
@@ -1155,13 +1221,14 @@ hipError_t launch_isect_stage(const RunArgs& r, hipEvent_t* ev) {
     uint64_t* partials = (uint64_t*)((char*)r.ws + L.isect_partials);
     const int order[NKERNEL] = {KER_MERGE, KER_BSEARCH, KER_BITMAP};
     reset_tile_counters(ia.ctrl, r.stream);
+    IsectParts parts;
     if (ev) (void)hipEventRecord(ev[0], r.stream);
     for (int q = 0; q < NKERNEL; ++q) {
         const int k = order[q];
-        launch_isect(k, ia, r.grid_override ? r.grid_override[k] : 0, partials, r.stream);
+        launch_isect(k, ia, r.grid_override ? r.grid_override[k] : 0, partials, r.stream, &parts);
         if (ev) (void)hipEventRecord(ev[1 + q], r.stream);
     }
-    launch_reduce_total(partials, ia.ctrl, r.stream);
+    launch_reduce_total(partials, parts, ia.ctrl, nullptr, 0, 0, r.stream);
     return hipGetLastError();
 }
 
@@ -1206,11 +1273,10 @@ void select_buckets(const RunArgs& r, Ctrl* ctrl, HubTab* hub) {
     const bool learned = !r.given && r.select == SEL_LEARNED && r.mlp && r.learned;
     const bool learned_tile = learned && r.mlp_tile && r.learned_tile;
     if (learned) mlp_select((const MlpCompute*)r.mlp, ctrl, r.learned, s);
-    else bucket_features_launch(ctrl, s);
     if (learned_tile) mlp_select((const MlpCompute*)r.mlp_tile, ctrl, r.learned_tile, s);
     hipLaunchKernelGGL(k_select, dim3(1), dim3(NBUCKET), 0, s, ctrl, r.given ? (int)SEL_LEARNED : r.select,
                        r.given ? r.given : (learned ? r.learned : nullptr), learned_tile ? r.learned_tile : nullptr,
-                       r.chunk_override, r.group_override, r.formulation != FORM_FILTERED ? 1 : 0, hub);
+                       r.chunk_override, r.group_override, r.formulation != FORM_FILTERED ? 1 : 0, learned ? 0 : 1, hub);
 }
 
 hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
@@ -1261,6 +1327,7 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         orient_part && radix_tile_keys((size_t)E, 8) == 8192u ? (uint32_t*)(ws + L.lb_aux) : nullptr;
     const int bw = vbits <= 20 ? (vbits < 12 ? vbits : 12) : (vbits <= 25 ? vbits - 8 : DEG_MAX_BW);
     const bool bucketed = vbits - bw <= DEG_MAX_BUCKET_BITS;
+    uint32_t nsent_blocks = 0;   // blocks of k_endpoints that recorded sentinel endpoints
     {
         uint32_t* ep = (uint32_t*)keysA;       // 2E uint32 fit in E uint64
         uint32_t* ep_alt = (uint32_t*)keysB;
@@ -1293,11 +1360,17 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
             if (vbits > bw)
                 a0 = radix_sort_u32(ep, ep_alt, nullptr, nullptr, nullptr, (size_t)(2 * E), bw, vbits, radix_tmp, s,
                                     true, true, &ctrl->err);   // a grouping: the order inside a bucket is free
-            uint32_t* bst = (uint32_t*)(ws + L.bstart);
-            hipLaunchKernelGGL(k_bucket_starts, dim3(grid_for((size_t)nb + 1)), dim3(NT), 0, s, a0 ? ep_alt : ep,
-                               (uint32_t)(2 * E), bw, nb, bst);
-            launch_bucket_count(a0 ? ep_alt : ep, bst, bw, nb, (uint64_t)(2 * E), n, deg, s);
-            hipLaunchKernelGGL(k_drop_sentinels, dim3(1), dim3(NT), 0, s, partial, eg, n, deg);
+            const uint32_t* tot = nullptr;   // one bucket: no partition
+            if (vbits - bw > 8) {
+                uint32_t* sizes = (uint32_t*)(ws + L.bstart);
+                hipLaunchKernelGGL(k_bucket_sizes, dim3(grid_for((size_t)nb)), dim3(NT), 0, s, a0 ? ep_alt : ep,
+                                   (uint32_t)(2 * E), bw, nb, sizes);
+                tot = sizes;
+            } else if (vbits > bw) {
+                tot = radix_digit_totals(radix_tmp, (size_t)(2 * E), 4);
+            }
+            launch_bucket_count(a0 ? ep_alt : ep, tot, bw, nb, (uint64_t)(2 * E), n, deg, s);
+            nsent_blocks = eg;
         } else {
             const int a0 = radix_sort_u32(ep, ep_alt, nullptr, nullptr, nullptr, (size_t)(2 * E), 0,
                                           bits_for((uint64_t)n + 1), radix_tmp, s, true, true,
@@ -1305,21 +1378,35 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
             fill_u32(rowend, 0u, (size_t)n, s);
             hipLaunchKernelGGL(k_endpoint_bounds, dim3(grid_for((size_t)(2 * E))), dim3(NT), 0, s, a0 ? ep_alt : ep,
                                (uint64_t)(2 * E), n, rowend);
-            fill_u32(deg, 0u, 1, s);
-            scan_inclusive_max_u32(rowend, deg + 1, (size_t)n, scan_tmp, s);   // deg[] holds degree offsets
+            scan_offsets_max_u32(rowend, deg, (size_t)n, scan_tmp, s);   // deg[] holds degree offsets
         }
     }
     mark(1);
     // ---- rank: sort (degree, id); degrees are below 2E + 1
-    if (bucketed)
-        hipLaunchKernelGGL(k_vertex_keys<false>, dim3(grid_for((size_t)n)), dim3(NT), 0, s, deg, n, vkeysA);
-    else
-        hipLaunchKernelGGL(k_vertex_keys<true>, dim3(grid_for((size_t)n)), dim3(NT), 0, s, deg, n, vkeysA);
+    const Chunking uc = chunking((uint64_t)E);   // of the unique pass, whose counts k_rank clears
     {
-        const int dbits = bits_for((uint64_t)2 * (uint64_t)E + 1);
+        const uint32_t v_tile = radix_tile_keys((size_t)n, 8);
+        const uint32_t v_tiles = (uint32_t)(((uint64_t)n + v_tile - 1) / v_tile);
+        const dim3 vg(v_tiles < 16384u ? v_tiles : 16384u);
+        int dbits = bits_for((uint64_t)2 * (uint64_t)E + 1);
+        if (dbits > RANK_BITS) dbits = RANK_BITS;
+        const RadixDigit v_dg = radix_first_digit(32, 32 + dbits);
+        uint32_t* v_counts = radix_first_counts(radix_tmp);
+        if (bucketed)
+            hipLaunchKernelGGL(k_vertex_keys<false>, vg, dim3(NT), 0, s, deg, n, partial, nsent_blocks, vkeysA,
+                               v_counts, v_tiles, v_tile, v_dg);
+        else
+            hipLaunchKernelGGL(k_vertex_keys<true>, vg, dim3(NT), 0, s, deg, n, partial, 0u, vkeysA, v_counts,
+                               v_tiles, v_tile, v_dg);
         const int alt = radix_sort_u64(vkeysA, vkeysB, nullptr, nullptr, nullptr, (size_t)n, 32, 32 + dbits,
-                                       radix_tmp, s, false, false, &ctrl->err);
-        hipLaunchKernelGGL(k_rank, dim3(grid_for((size_t)n)), dim3(NT), 0, s, alt ? vkeysB : vkeysA, n, rank, inv);
+                                       radix_tmp, s, true, false, &ctrl->err);
+        const dim3 rg(grid_for((size_t)n));
+        if (bucketed)
+            hipLaunchKernelGGL(k_rank<false>, rg, dim3(NT), 0, s, alt ? vkeysB : vkeysA, n, deg, rank, inv, rowend,
+                               partial, uc.nblk + 1);
+        else
+            hipLaunchKernelGGL(k_rank<true>, rg, dim3(NT), 0, s, alt ? vkeysB : vkeysA, n, deg, rank, inv, rowend,
+                               partial, uc.nblk + 1);
     }
     mark(2);
     // ---- orient
@@ -1367,19 +1454,15 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
     uint64_t* sorted = alt ? keysB : keysA;
     uint64_t* other = alt ? keysA : keysB;
     // the row sort also counts the kept (first of equal) keys per chunk of the unique pass
-    const Chunking uc = chunking((uint64_t)E);
-    fill_u32(partial, 0u, (size_t)uc.nblk + 1, s);
     sort_runs_u64(sorted, other, (size_t)E, nb, true, sentinel, partial, uc.chunk, s);
     mark(4);
     // ---- unique + CSR
     {
         const Chunking c = uc;
         scan_exclusive_sum_u32(partial, partial, (size_t)c.nblk + 1, scan_tmp, s);
-        fill_u32(rowend, 0u, (size_t)n, s);
         hipLaunchKernelGGL(k_unique_write, dim3(c.nblk), dim3(NT), 0, s, sorted, (uint64_t)E, sentinel, ctrl, c.chunk,
                            partial, c.nblk, nb, col, src, rowend);
-        fill_u32(off, 0u, 1, s);
-        scan_inclusive_max_u32(rowend, off + 1, (size_t)n, scan_tmp, s);
+        scan_offsets_max_u32(rowend, off, (size_t)n, scan_tmp, s);
     }
     mark(5);
     if (r.csr_rank) {   // CSR export only: stop after the induced subgraph
@@ -1399,17 +1482,15 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         const CscPacking pk = csc_packing(E, n);
         hipLaunchKernelGGL(k_csc_keys, dim3(e_tiles < 16384u ? e_tiles : 16384u), dim3(NT), 0, s, col, src, off,
                            ctrl, n, other, pk.sh, pk.lbits, radix_first_counts(radix_tmp), e_tiles, e_tile,
-                           radix_first_digit(pk.sh, pk.sh + nbv));
+                           radix_first_digit(pk.sh, pk.sh + nbv), rowend);
         const int alt2 = radix_sort_u64(other, sorted, nullptr, nullptr, &ctrl->m, (size_t)E, pk.sh, pk.sh + nbv,
                                         radix_tmp, s, true, true, &ctrl->err);
         // bounds and tail ranges in one pass, into the buffer the sort left free
         const uint64_t* ckeys = alt2 ? sorted : other;
         csc = alt2 ? other : sorted;
-        fill_u32(rowend, 0u, (size_t)n, s);
         hipLaunchKernelGGL(k_csc_finish, dim3(grid_for(((size_t)E + 1) / 2)), dim3(NT), 0, s, ckeys,
                            csc, ctrl, n, rowend, pk.sh, src, off, pk.ebits, pk.lbits);
-        fill_u32(inoff, 0u, 1, s);
-        scan_inclusive_max_u32(rowend, inoff + 1, (size_t)n, scan_tmp, s);
+        scan_offsets_max_u32(rowend, inoff, (size_t)n, scan_tmp, s);
     } else {
         // ---- all in-edges grouped by v; the symmetric adjacency; the streamed ranges
         const int sh = bits_for((uint64_t)E) > 0 ? bits_for((uint64_t)E) : 1;
@@ -1420,8 +1501,7 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         csc = alt2 ? sorted : other;
         fill_u32(rowend, 0u, (size_t)n, s);
         hipLaunchKernelGGL(k_sym_bounds, dim3(grid_for((size_t)E)), dim3(NT), 0, s, csc, ctrl, rowend, sh);
-        fill_u32(inoff, 0u, 1, s);
-        scan_inclusive_max_u32(rowend, inoff + 1, (size_t)n, scan_tmp, s);
+        scan_offsets_max_u32(rowend, inoff, (size_t)n, scan_tmp, s);
         uint32_t* fo = sym_off(r, L);
         if (r.formulation != FORM_MATRIX_UPPER) {
             hipLaunchKernelGGL(k_sym_rows, dim3(grid_for((size_t)n + 1)), dim3(NT), 0, s, inoff, off, n, fo);
@@ -1438,14 +1518,16 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
     select_buckets(r, ctrl, hub_tab(r, L));
     mark(7);
     // ---- group: order vertices by (kernel, bucket); tiles
-    hipLaunchKernelGGL(k_vkeys_slot, dim3(grid_for((size_t)n)), dim3(NT), 0, s, vbucket, n, ctrl, vkeysA);
     {
+        const uint32_t v_tile = radix_tile_keys((size_t)n, 8);
+        const uint32_t v_tiles = (uint32_t)(((uint64_t)n + v_tile - 1) / v_tile);
+        hipLaunchKernelGGL(k_vkeys_slot, dim3(v_tiles < 16384u ? v_tiles : 16384u), dim3(NT), 0, s, vbucket, n, ctrl,
+                           vkeysA, radix_first_counts(radix_tmp), v_tiles, v_tile, radix_first_digit(32, 40));
         const int a3 = radix_sort_u64(vkeysA, vkeysB, nullptr, nullptr, nullptr, (size_t)n, 32, 40, radix_tmp, s,
-                                      false, false, &ctrl->err);
-        hipLaunchKernelGGL(k_vpos, dim3(grid_for((size_t)n)), dim3(NT), 0, s, a3 ? vkeysB : vkeysA, n, vbucket, ctrl,
-                           vlist);
+                                      true, false, &ctrl->err);
+        hipLaunchKernelGGL(k_ntiles, dim3(grid_for((size_t)n)), dim3(NT), 0, s, a3 ? vkeysB : vkeysA, vlist, vbucket,
+                           inoff, n, ctrl, tstart);
     }
-    hipLaunchKernelGGL(k_ntiles, dim3(grid_for((size_t)n)), dim3(NT), 0, s, vlist, vbucket, inoff, n, ctrl, tstart);
     scan_exclusive_sum_u32(tstart, tstart, (size_t)n + 1, scan_tmp, s);
     hipLaunchKernelGGL(k_emit_tiles, dim3(grid_for((size_t)n)), dim3(NT), 0, s, vlist, vbucket, inoff, tstart, n,
                        ctrl, tiles, (uint64_t)L.tile_cap, hub_tab(r, L));
@@ -1462,12 +1544,13 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
     prepare_hub(r, L, csc, ia);
     uint64_t* partials = (uint64_t*)(ws + L.isect_partials);
     const int order[NKERNEL] = {KER_MERGE, KER_BSEARCH, KER_BITMAP};
+    IsectParts parts;
     for (int q = 0; q < NKERNEL; ++q) {
         const int k = order[q];
-        launch_isect(k, ia, r.grid_override ? r.grid_override[k] : 0, partials, s);
+        launch_isect(k, ia, r.grid_override ? r.grid_override[k] : 0, partials, s, &parts);
         mark(9 + q);
     }
-    launch_reduce_total(partials, ctrl, s);
+    launch_reduce_total(partials, parts, ctrl, r.result, r.range_status, r.internal_status, s);
     // ---- finish
     if (r.per_vertex)
         hipLaunchKernelGGL(k_map_pv, dim3(grid_for((size_t)n)), dim3(NT), 0, s, pv, inv, n, r.per_vertex);

@@ -33,9 +33,12 @@ void fill_u64(uint64_t* p, uint64_t v, size_t n, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------ scans
-// Three phases over a fixed number of blocks: per-block reduction, a scan of
-// the block partials in one block, then each block scans its chunk with its
-// partial as the carry-in. Works in place (out == in).
+// Two kernels over a fixed number of blocks: per-block reduction, then each
+// block reduces the partials before it (1024 at most) for its carry-in and
+// scans its chunk. One block needs only the second. Works in place (out == in).
+// Chunks of one block step (2048 elements) up to 1024 blocks: 8192 left the kernels of a
+// million elements to 128 blocks, and a kernel of its own scanned the partials
+// (a scan of 2^20 elements 28.5 -> 12.6 us).
 constexpr int SCAN_NT = 256;
 constexpr int SCAN_MAX_BLOCKS = 1024;
 constexpr int SCAN_ITEMS = 8;   // elements per thread per step
@@ -101,42 +104,16 @@ __global__ __launch_bounds__(SCAN_NT) void k_scan_reduce(const T* in, size_t len
     if (threadIdx.x == 0) partial[blockIdx.x] = acc;
 }
 
-// Exclusive scan of up to SCAN_MAX_BLOCKS partials in one block; partial[nb] = total.
-template <typename Op, typename T>
-__global__ __launch_bounds__(SCAN_NT) void k_scan_partials(T* partial, int nb) {
-    __shared__ T scratch[SCAN_NT / WAVE];
-    constexpr int PER = SCAN_MAX_BLOCKS / SCAN_NT;
-    T v[PER];
-    T local = Op::template ident<T>();
-    for (int k = 0; k < PER; ++k) {
-        const int i = threadIdx.x * PER + k;
-        v[k] = i < nb ? partial[i] : Op::template ident<T>();
-        local = Op::apply(local, v[k]);
-    }
-    T total;
-    T inc = block_scan_inclusive<Op>(local, scratch, &total);
-    // exclusive base for this thread = inclusive of previous thread
-    T prev = (T)__shfl_up(inc, 1, WAVE);
-    __shared__ T wave_last[SCAN_NT / WAVE];
-    if (lane_id() == WAVE - 1) wave_last[wave_id()] = inc;
-    __syncthreads();
-    if (lane_id() == 0) prev = wave_id() == 0 ? Op::template ident<T>() : wave_last[wave_id() - 1];
-    T run = prev;
-    for (int k = 0; k < PER; ++k) {
-        const int i = threadIdx.x * PER + k;
-        if (i < nb) partial[i] = run;
-        run = Op::apply(run, v[k]);
-    }
-    if (threadIdx.x == 0) partial[nb] = total;
-}
-
 template <typename Op, typename T, bool INCLUSIVE>
 __global__ __launch_bounds__(SCAN_NT) void k_scan_down(const T* in, T* out, size_t len, size_t chunk,
-                                                       const T* partial) {
+                                                       const T* partial, T* lead) {
     __shared__ T scratch[SCAN_NT / WAVE];
     const size_t b0 = (size_t)blockIdx.x * chunk;
     const size_t b1 = b0 + chunk < len ? b0 + chunk : len;
-    T carry = partial[blockIdx.x];
+    T carry = Op::template ident<T>();
+    for (unsigned i = threadIdx.x; i < blockIdx.x; i += SCAN_NT) carry = Op::apply(carry, partial[i]);
+    carry = block_reduce<Op>(carry, scratch);
+    if (lead && blockIdx.x == 0 && threadIdx.x == 0) *lead = Op::template ident<T>();
     // SCAN_ITEMS consecutive elements per thread: loaded together, scanned in
     // registers, then one block scan of the thread totals per SCAN_NT * SCAN_ITEMS
     for (size_t base = b0; base < b1; base += (size_t)SCAN_NT * SCAN_ITEMS) {
@@ -176,27 +153,25 @@ __global__ __launch_bounds__(SCAN_NT) void k_scan_down(const T* in, T* out, size
 
 size_t scan_temp_bytes() { return sizeof(uint64_t) * (SCAN_MAX_BLOCKS + 1); }
 
+// lead (may be null): set to the identity, for offsets that start one element before out.
 template <typename Op, typename T, bool INCLUSIVE>
-static void scan_impl(const T* in, T* out, size_t len, void* temp, hipStream_t s) {
+static void scan_impl(const T* in, T* out, size_t len, void* temp, hipStream_t s, T* lead = nullptr) {
     if (len == 0) return;
-    int nb = (int)((len + 8191) / 8192);
-    if (nb > SCAN_MAX_BLOCKS) nb = SCAN_MAX_BLOCKS;
-    if (nb < 1) nb = 1;
-    size_t chunk = (len + nb - 1) / nb;
-    chunk = (chunk + SCAN_NT - 1) / SCAN_NT * SCAN_NT;
-    nb = (int)((len + chunk - 1) / chunk);
+    constexpr size_t STEP = (size_t)SCAN_NT * SCAN_ITEMS;
+    size_t chunk = (len + SCAN_MAX_BLOCKS - 1) / SCAN_MAX_BLOCKS;
+    chunk = (chunk + STEP - 1) / STEP * STEP;
+    const int nb = (int)((len + chunk - 1) / chunk);
     T* partial = (T*)temp;
-    hipLaunchKernelGGL((k_scan_reduce<Op, T>), dim3(nb), dim3(SCAN_NT), 0, s, in, len, chunk, partial);
-    hipLaunchKernelGGL((k_scan_partials<Op, T>), dim3(1), dim3(SCAN_NT), 0, s, partial, nb);
+    if (nb > 1) hipLaunchKernelGGL((k_scan_reduce<Op, T>), dim3(nb), dim3(SCAN_NT), 0, s, in, len, chunk, partial);
     hipLaunchKernelGGL((k_scan_down<Op, T, INCLUSIVE>), dim3(nb), dim3(SCAN_NT), 0, s, in, out, len, chunk,
-                       (const T*)partial);
+                       (const T*)partial, lead);
 }
 
 void scan_exclusive_sum_u32(const uint32_t* in, uint32_t* out, size_t len, void* temp, hipStream_t s) {
     scan_impl<OpSum, uint32_t, false>(in, out, len, temp, s);
 }
-void scan_inclusive_max_u32(const uint32_t* in, uint32_t* out, size_t len, void* temp, hipStream_t s) {
-    scan_impl<OpMax, uint32_t, true>(in, out, len, temp, s);
+void scan_offsets_max_u32(const uint32_t* in, uint32_t* off, size_t len, void* temp, hipStream_t s) {
+    scan_impl<OpMax, uint32_t, true>(in, off + 1, len, temp, s, off);
 }
 void scan_exclusive_sum_u64(const uint64_t* in, uint64_t* out, size_t len, void* temp, hipStream_t s) {
     scan_impl<OpSum, uint64_t, false>(in, out, len, temp, s);
@@ -812,6 +787,11 @@ RadixDigit radix_first_digit(int bit_lo, int bit_hi) {
 }
 
 uint32_t* radix_first_counts(void* temp) { return (uint32_t*)temp; }
+
+const uint32_t* radix_digit_totals(void* temp, size_t cap, int key_bytes) {
+    const size_t ntiles = rs_ntiles(cap, radix_tile_keys(cap, key_bytes));
+    return (const uint32_t*)((char*)temp + align_up(sizeof(uint32_t) * 256 * (ntiles + 1), 256));
+}
 
 // The ranking of a pass: lane masks for 32-bit keys (twice the keys per byte
 // moved, so the 8-ballot match costs twice as much per byte there); for

@@ -44,7 +44,7 @@ constexpr int SR_V = 64;               // rank: vertices per block of SB_NT thre
 static int row_k(int32_t n) { return n <= 4096 ? 1 : (n <= 8192 ? 2 : 4); }
 
 struct SmallLayout {
-    size_t bits, pairs, seg, key, dsim, t2, rank, lo, hi, dplus, din, total;
+    size_t bits, pairs, seg, key, dsim, t2, rank, lo, hi, dplus, din, tiles, total;
 };
 
 static SmallLayout small_layout(int64_t E, int32_t n) {
@@ -63,6 +63,7 @@ static SmallLayout small_layout(int64_t E, int32_t n) {
     L.hi = take(4 * nn);
     L.dplus = take(4 * nn);
     L.din = take(4 * nn);
+    L.tiles = take(4 * NBUCKET);
     L.total = o;
     return L;
 }
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(SB_NT) void k_small_build(const int2* __restrict__ 
                                                        uint64_t* __restrict__ bits, uint32_t* __restrict__ pairs,
                                                        uint2* __restrict__ seg, uint32_t* __restrict__ key,
                                                        uint32_t* __restrict__ dsim, uint32_t* __restrict__ t2,
-                                                       Ctrl* ctrl) {
+                                                       uint32_t* __restrict__ tiles, Ctrl* ctrl) {
     constexpr uint32_t R = 16u * K, W = 64u * K;   // rows, words per row
     __shared__ uint64_t s_row[R * W];
     __shared__ uint32_t s_deg[R], s_sim[R], s_at[R], s_below, s_bad;
@@ -92,8 +93,10 @@ __global__ __launch_bounds__(SB_NT) void k_small_build(const int2* __restrict__ 
     for (uint32_t i = threadIdx.x; i < R * W; i += SB_NT) s_row[i] = 0;
     if (threadIdx.x < R) s_deg[threadIdx.x] = 0;
     if (threadIdx.x == 0) { s_below = 0; s_bad = 0; }
-    if (blockIdx.x == 0)
+    if (blockIdx.x == 0) {
         for (uint32_t i = threadIdx.x; i < sizeof(Ctrl) / 4; i += SB_NT) ((uint32_t*)ctrl)[i] = 0;
+        if (threadIdx.x < NBUCKET) tiles[threadIdx.x] = 0;
+    }
     __syncthreads();
     uint32_t below = 0;   // endpoints before this block's rows (of loops and bad pairs too: a bound on its place)
     uint32_t top = 0;     // highest id (negative ones wrap past every n)
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(SF_NT) void k_small_finish(const uint32_t* __restri
                                                         const uint32_t* __restrict__ dplus, int stats,
                                                         uint64_t* __restrict__ per_vertex, double* __restrict__ coeff,
                                                         uint64_t* __restrict__ result, uint64_t range_status,
-                                                        Ctrl* ctrl) {
+                                                        uint32_t* __restrict__ tiles, Ctrl* ctrl) {
     __shared__ uint64_t s_t[SF_NT / WAVE], s_w[SF_NT / WAVE];
     __shared__ uint32_t s_m, s_tiles[NBUCKET], s_ker[NKERNEL], s_last;
     if (threadIdx.x == 0) s_m = 0;
@@ -412,7 +415,7 @@ __global__ __launch_bounds__(SF_NT) void k_small_finish(const uint32_t* __restri
         s_w[wave_id()] = w;
     }
     __syncthreads();
-    uint32_t* tiles = ctrl->bend;   // tiles of the single-vertex buckets; the tile layout's field, unused here
+    // tiles: of the single-vertex buckets (cleared by the build)
     // The sums meet in device-scope atomics alone, and each is complete (its old value has come
     // back) before the barrier ahead of the ticket, so no cache has to be written back.
     uint32_t seen = 0;
@@ -460,8 +463,8 @@ __global__ __launch_bounds__(SF_NT) void k_small_finish(const uint32_t* __restri
 
 // ------------------------------------------------------------------ launcher
 template <int K>
-static void run_k(const RunArgs& r, const SmallLayout& L, uint64_t* result, uint64_t range_status) {
-    const bool stats = !result;
+static void run_k(const RunArgs& r, const SmallLayout& L) {
+    const bool stats = !r.result;   // a queued call has no use for them
     char* ws = (char*)r.ws;
     hipStream_t s = r.stream;
     Ctrl* ctrl = (Ctrl*)ws;
@@ -470,12 +473,12 @@ static void run_k(const RunArgs& r, const SmallLayout& L, uint64_t* result, uint
     uint2* seg = (uint2*)(ws + L.seg);
     uint32_t *key = (uint32_t*)(ws + L.key), *dsim = (uint32_t*)(ws + L.dsim), *t2 = (uint32_t*)(ws + L.t2),
              *rank = (uint32_t*)(ws + L.rank), *lo = (uint32_t*)(ws + L.lo), *hi = (uint32_t*)(ws + L.hi),
-             *dplus = (uint32_t*)(ws + L.dplus), *din = (uint32_t*)(ws + L.din);
+             *dplus = (uint32_t*)(ws + L.dplus), *din = (uint32_t*)(ws + L.din), *tiles = (uint32_t*)(ws + L.tiles);
     const uint32_t n = (uint32_t)r.n, nblk = (n + 16u * K - 1) / (16u * K);
     static_assert(SMALL_MAX_N / (16 * 4) <= SM_BLOCKS && 8192 / (16 * 2) <= SM_BLOCKS && 4096 / 16 <= SM_BLOCKS,
                   "a segment per build block");
     hipLaunchKernelGGL(k_small_build<K>, dim3(nblk), dim3(SB_NT), 0, s, (const int2*)r.edges, (uint32_t)r.E, r.n, bits,
-                       pairs, seg, key, dsim, t2, ctrl);
+                       pairs, seg, key, dsim, t2, tiles, ctrl);
     // at most 2E pairs, and one short chunk per segment
     const uint64_t chunks = 2ull * (uint64_t)r.E / SM_CHUNK + nblk;
     const unsigned grid = (unsigned)((chunks + SC_NT / WAVE - 1) / (SC_NT / WAVE));
@@ -489,15 +492,15 @@ static void run_k(const RunArgs& r, const SmallLayout& L, uint64_t* result, uint
         select_buckets(r, ctrl, nullptr);
     }
     hipLaunchKernelGGL(k_small_finish, dim3((n + SF_NT - 1) / SF_NT), dim3(SF_NT), 0, s, t2, dsim, seg, nblk, n, din, dplus, stats ? 1 : 0,
-                       r.per_vertex, r.clustering, result, range_status, ctrl);
+                       r.per_vertex, r.clustering, r.result, r.range_status, tiles, ctrl);
 }
 
-hipError_t run_small(const RunArgs& r, uint64_t* result, uint64_t range_status, RunResult* out) {
+hipError_t run_small(const RunArgs& r, RunResult* out) {
     const SmallLayout L = small_layout(r.E, r.n);
     switch (row_k(r.n)) {
-        case 1: run_k<1>(r, L, result, range_status); break;
-        case 2: run_k<2>(r, L, result, range_status); break;
-        default: run_k<4>(r, L, result, range_status); break;
+        case 1: run_k<1>(r, L); break;
+        case 2: run_k<2>(r, L); break;
+        default: run_k<4>(r, L); break;
     }
     out->ctrl_dev = (Ctrl*)r.ws;
     return hipGetLastError();

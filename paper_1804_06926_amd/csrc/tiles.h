@@ -4,6 +4,7 @@
 #include "common.h"
 #include "internal.h"
 #include "isect.h"
+#include "mlp.h"
 
 namespace tcx {
 
@@ -47,6 +48,20 @@ struct BucketSums {
         }
     }
 };
+
+// Bucket features (6 floats): the bucket's two degree classes and the log
+// sizes of its work, from the statistics gathered by the pipeline: the
+// LDS-bitmap windows its middle lists span (the bitmap strategy's set-up
+// count, which grows with the rank range a list covers and so with the
+// graph's size), in-edges, out-neighbours, and in-edges x out-degree.
+__device__ __forceinline__ void bucket_features(const Ctrl* ctrl, int b, float (&f)[MLP_IN]) {
+    f[0] = (float)(b >> 4) / 14.f;
+    f[1] = (float)(b & 15) / 15.f;
+    f[2] = log2f(1.f + (float)ctrl->bucket_win[b]) / 32.f;
+    f[3] = log2f(1.f + (float)ctrl->bucket_in[b]) / 32.f;
+    f[4] = log2f(1.f + (float)ctrl->bucket_out[b]) / 32.f;
+    f[5] = log2f(1.f + (float)ctrl->bucket_work[b]) / 48.f;
+}
 
 // Vertices per multi-vertex tile for bucket b (1 = chunks of single vertices).
 __device__ __forceinline__ uint32_t tile_group(const Ctrl* ctrl, uint32_t b) {
