@@ -95,7 +95,8 @@ def algorithmic_bytes(tc, d_edges, n, stats):
     strategy (each must read the tail and N+(v) at least once), except that
     the bitmap strategy's hub kernel (single-vertex tiles of the 65535
     top-ranked vertices, from 2^24 pairs and about 2^30 tail elements) reads
-    2 B per element.
+    2 B per element, and its group kernel (the last 16384 of them, 32 at a time)
+    reads a row once for all its members of a group.
     """
     import numpy as np
     rank, off, col = tc.build_csr(d_edges, n)
@@ -121,6 +122,13 @@ def algorithmic_bytes(tc, d_edges, n, stats):
     size = np.where(hub, 2, 4)
     ek = kern[col[active]]
     es = size[col[active]]
+    if hub_on and n >= 65535:
+        member = hub[col] & (col >= n - 16384)
+        follows = np.zeros(m, dtype=bool)
+        follows[1:] = (member[1:] & (src[1:] == src[:-1]) & (col[:-1] >= n - 16384)
+                       & ((col[1:] - (n - 16384)) // 32 == (col[:-1] - (n - 16384)) // 32))
+        es = np.where(follows[active], 0, es)
+        tiles = np.where(hub & (np.arange(n) >= n - 16384), np.minimum(tiles, 1), tiles)
     for k, name in enumerate(("merge", "bsearch", "bitmap")):
         e_bytes = int((8 + es[ek == k] * tail[active][ek == k]).sum())
         t_bytes = int((tiles[kern == k] * (16 + size[kern == k] * dplus[kern == k])).sum())

@@ -132,7 +132,7 @@ struct Ctrl {
     uint32_t tile_begin[NKERNEL + 1]; // tile range per intersection kernel
     uint32_t m_active;                // in-edges with work (non-empty tail, d+(v) > 0)
     uint32_t pad0;
-    uint32_t tile_next[NKERNEL + 1];  // per intersection kernel: tiles handed out after the first per block
+    uint32_t tile_next[NKERNEL + 2];  // per intersection kernel: tiles handed out after the first per block
                                       // (zeroed before every launch)
     uint64_t wedges;                  // sum over v of C(d(v), 2), simple degree (clustering runs only)
     uint32_t bstart[NBUCKET];         // first / one-past-last position of each bucket in the
@@ -167,10 +167,24 @@ __host__ __device__ inline uint32_t hub_first(uint32_t n) { return n > HUB_SPAN 
 // Its tables (device): per bucket the first hub tile, then the tile ranges of
 // the bitmap kernel and of the hub kernel, one per bucket in slot order: the
 // first tile, and the exclusive prefix of the tile counts with the total last.
+// The hub group kernel, where it runs, has the last of them: the GRP_SPAN highest
+// ranks in groups of GRP_N. Its tiles are stretches of grp_edges in-edges of a
+// group, counted by grp_pref; grp_inc says which of a group's vertices
+// it counts (those with single-vertex tiles of the bitmap strategy).
+constexpr uint32_t GRP_SPAN = 1u << 14, GRP_N = 32, GRP_COUNT = GRP_SPAN / GRP_N;
+__host__ __device__ inline uint32_t grp_first(uint32_t n) { return n - GRP_SPAN; }   // n >= HUB_SPAN
 struct HubTab {
     uint32_t first[NBUCKET];          // ~0: the bucket has no hub tile
+    uint32_t grp[NBUCKET];            // its first tile of the group kernel's vertices, or ~0
     uint32_t rest_tile[NBUCKET], rest_pref[NBUCKET + 1];
     uint32_t hub_tile[NBUCKET], hub_pref[NBUCKET + 1];
+    uint32_t grp_inc[GRP_COUNT], grp_pref[GRP_COUNT + 1], grp_edges;
+    uint32_t used;                    // tiles of the hub and the group kernel
 };
+// An in-edge entry (tail start | tail end << 32) whose row holds an earlier member of
+// the same group (only where the group kernel may run).
+constexpr uint64_t CSC_FOLLOWS = 1ull << 63;
+__host__ __device__ inline uint32_t tail_start(uint64_t entry) { return (uint32_t)entry; }
+__host__ __device__ inline uint32_t tail_end(uint64_t entry) { return (uint32_t)(entry >> 32) & 0x7FFFFFFFu; }
 
 }  // namespace tcx

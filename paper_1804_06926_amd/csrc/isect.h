@@ -42,6 +42,8 @@ struct IsectArgs {
     // col) and tile ranges, or null: the bitmap kernel then takes all its tiles
     const uint16_t* col16;
     const HubTab* hub;
+    bool groups;           // the group kernel runs too (it counts in all only)
+    uint32_t first_rank;   // the lowest rank of its groups
 };
 
 // Blocks of one intersection kernel resident per CU (from the occupancy API);
@@ -49,14 +51,15 @@ struct IsectArgs {
 int isect_blocks_per_cu(int ker, int mode);
 // First of the top ranks whose per-vertex counts are kept in LDS.
 uint32_t isect_hot_first(uint32_t n);
+int isect_group_blocks();   // blocks of the group kernel's launch
 size_t isect_partials_bytes();
 // Partial counts that the kernels of one intersection stage write: `n` of them from `first` on,
 // per launch.
 struct IsectParts {
     int launches = 0;
-    uint32_t first[NKERNEL + 1], n[NKERNEL + 1];
+    uint32_t first[NKERNEL + 2], n[NKERNEL + 2];
 };
-// One intersection kernel over its tile range (the bitmap strategy: two kernels, when a.hub is set);
+// One intersection kernel over its tile range (the bitmap strategy: two or three kernels, when a.hub is set);
 // per-block partial counts go to partials (isect_partials_bytes() of workspace shared by the
 // kernels), their places are added to parts (may be null).
 void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hipStream_t s, IsectParts* parts = nullptr);

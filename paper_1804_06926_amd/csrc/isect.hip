@@ -58,7 +58,7 @@ using Segs = SegsT<SEG_MAX>;
 // The next tile for this block after its first (static) one: t0 + the shared
 // counter ker, which is zero when the launch starts. Called by the
 // whole block (barriers); the value is the same in every thread.
-constexpr int HUB_COUNTER = NKERNEL;   // the hub kernel's
+constexpr int HUB_COUNTER = NKERNEL, GRP_COUNTER = NKERNEL + 1;   // the hub and the group kernel's
 __device__ __forceinline__ uint32_t grab_tile(Ctrl* ctrl, int ker, uint32_t t0, uint32_t* s_tile) {
     __syncthreads();   // every thread has read the previous value
     if (threadIdx.x == 0) *s_tile = t0 + atomicAdd(&ctrl->tile_next[ker], 1u);
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
     uint32_t ntile = a.ctrl->tile_begin[KER_BITMAP + 1] - t_begin;
     // with the hub kernel beside it, this one takes the tiles that are left
     constexpr bool RANGES = MODE == BM_COUNT || MODE == BM_MIDDLE;
-    const bool ranges = RANGES && a.hub && a.hub->hub_pref[NBUCKET] != 0;
+    const bool ranges = RANGES && a.hub && a.hub->used != 0;
     if (ranges) ntile = a.hub->rest_pref[NBUCKET];
     for (uint32_t i = blockIdx.x; i < ntile; i = grab_tile(a.ctrl, KER_BITMAP, gridDim.x, &s_tile)) {
         const uint32_t nseg = load_tile(a, ranges ? range_tile(a.hub->rest_tile, a.hub->rest_pref, i) : t_begin + i, S);
@@ -370,8 +370,8 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
                 st_h[h] = len_h[h] = 0;
                 if (k < ne) {
                     const uint64_t ent = a.csc[e0 + k];   // tail start | tail end << 32
-                    st_h[h] = (uint32_t)ent;
-                    len_h[h] = (uint32_t)(ent >> 32) - st_h[h];
+                    st_h[h] = tail_start(ent);
+                    len_h[h] = tail_end(ent) - st_h[h];
                 }
             }
             // the table: once per vertex, or per window when the tails are clipped
@@ -629,7 +629,8 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
 // first or last chunk holds beside the tail is turned into HUB_NONE by mask
 // words from an LDS table. The next tile's descriptor and in-edges are loaded
 // while the current one is walked. Bound: the line traffic of the tails beyond
-// L2: 91 GB of counted traffic at R-MAT 24, 7.4 TB/s. Measured there: this
+// L2: 91 GB of counted traffic at R-MAT 24 with all its ranks (counts in all leave
+// the highest to the group kernel below), 7.4 TB/s. Measured so: this
 // kernel and the bitmap kernel for the remaining tiles 12.2 + 9.5 ms, the bitmap kernel
 // alone 30.1 ms; R-MAT 20 (tiles too short for the set-up to vanish) 0.65 + 0.19
 // against 0.89 ms. Steps in flight: 3 and 4 alike, 6 and 8 slower (23.2, 36.5 ms with the
@@ -641,7 +642,8 @@ constexpr int HB_D = 3;                   // steps in flight
 constexpr uint32_t HB_L = 8;              // lanes per tail
 constexpr uint32_t HB_R = WAVE / HB_L;    // tails walked together by a wave
 constexpr uint32_t HB_E = 8;              // elements per chunk
-constexpr int HB_PARTIAL0 = 3072;         // partial slots of the bitmap kernel's share from here on
+constexpr int HB_PARTIAL0 = 3072, HB_PARTIAL1 = 3584;   // partial slots of the bitmap kernel's share from here on
+                                                      // (the hub kernel's, the group kernel's)
 static_assert(CHUNK_MAX <= HB_NT, "one in-edge per lane");
 
 // Order of magnitude of a step count: 0, 1, 2, 3, then two classes per doubling, at most HB_CLS - 1.
@@ -655,12 +657,48 @@ __device__ __forceinline__ uint32_t step_class(uint32_t steps) {
 
 struct HubMasks {   // k first / last elements of a chunk set to ones
     uint4 head[HB_E + 1], tail[HB_E + 1];
+    // Whole block; a barrier follows before use.
+    __device__ void fill() {
+        if (threadIdx.x > HB_E) return;
+        const uint32_t k = threadIdx.x;
+        uint32_t h[4], t[4];
+        for (uint32_t q = 0; q < 4; ++q) {
+            h[q] = (2 * q < k ? 0xFFFFu : 0u) | (2 * q + 1 < k ? 0xFFFF0000u : 0u);
+            t[q] = (2 * q + k >= HB_E ? 0xFFFFu : 0u) | (2 * q + 1 + k >= HB_E ? 0xFFFF0000u : 0u);
+        }
+        head[k] = make_uint4(h[0], h[1], h[2], h[3]);
+        tail[k] = make_uint4(t[0], t[1], t[2], t[3]);
+    }
 };
+
+constexpr uint32_t GRP_OFF = HUB_SPAN - GRP_SPAN;   // the group kernel's ranks as 16-bit columns start here
+
+typedef unsigned short Half2 __attribute__((ext_vector_type(2)));
+
+// The word of column x in the group kernel's map. The lowest rank is in no
+// N+ of these vertices, so its word stays zero, and HUB_NONE has the same.
+__device__ __forceinline__ uint32_t grp_word(uint32_t x) { return x % GRP_SPAN; }
+static_assert(GRP_OFF % GRP_SPAN == HUB_NONE % GRP_SPAN && GRP_SPAN * 4 == 65536, "16-bit byte addresses");
+
+// Or over the eight lanes of a tail.
+__device__ __forceinline__ uint32_t or8(uint32_t x) {
+    static_assert(HB_L == 8, "eight lanes per tail");
+    x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, true);    // lane ^ 1
+    x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xF, 0xF, true);    // lane ^ 2
+    x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x141, 0xF, 0xF, true);   // lane -> 7 - lane
+    return x;
+}
 
 // Elements of this wave's tails that the map holds: S, E = start and end of
 // the lane's tail in the 16-bit columns (empty: S >= E).
+// GROUP: the map is a word per rank of the group kernel, with a bit per member of
+// group g that has the rank as an out-neighbour; a tail starts at its row's first member,
+// and an element counts the members that are in the row and have it. The row's members are its
+// first elements, at most GRP_N, all in the tail's first step.
+template <bool GROUP>
 __device__ __forceinline__ uint32_t walk_tails(const uint4* __restrict__ chunks, uint32_t S, uint32_t E,
-                                               const uint8_t* map, const HubMasks& M) {
+                                               const void* map, const HubMasks& M, uint32_t g) {
+    static_assert(GRP_N + HB_E - 1 <= HB_L * HB_E, "a group's members lie in the first step");
     const uint32_t ln = (uint32_t)lane_id(), gl = ln % HB_L, gi = ln / HB_L;
     // tails in order of length (descending classes), empty ones last
     const uint32_t nch = S < E ? (E - 1u) / HB_E + 1u - S / HB_E : 0u;
@@ -679,7 +717,8 @@ __device__ __forceinline__ uint32_t walk_tails(const uint4* __restrict__ chunks,
     E = (uint32_t)__builtin_amdgcn_ds_permute((int)(pos * 4u), (int)E);
     const uint32_t rounds = (live + HB_R - 1) / HB_R;
     // one cursor per lane over (round, chunk); all lanes advance together
-    uint32_t r = 0, s = 0, e = 0, c = 0, c1 = 0, issued = 0, hits = 0;
+    uint32_t r = 0, s = 0, e = 0, c = 0, c1 = 0, issued = 0, hits = 0, own = 0;
+    bool fresh = true;   // the cursor is at its tails' first step
     auto fetch = [&]() {
         const int from = (int)(((r * HB_R + gi) & (WAVE - 1)) * 4u);
         s = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)S);
@@ -689,14 +728,17 @@ __device__ __forceinline__ uint32_t walk_tails(const uint4* __restrict__ chunks,
     };
     uint4 x[HB_D];
     uint32_t hk[HB_D], tk[HB_D];
+    bool fs[HB_D];
     auto issue = [&](int q) {
         const bool on = c < c1;
         x[q] = chunks[on ? c : 0u];   // unconditional: lanes without a chunk read a valid one
         const int h = (int)(s - c * HB_E), t = (int)(c * HB_E + HB_E - e);
         hk[q] = on ? (uint32_t)(h < 0 ? 0 : h) : HB_E;
         tk[q] = on ? (uint32_t)(t < 0 ? 0 : t) : 0u;
+        fs[q] = fresh;
         if (r < rounds) ++issued;
-        if (__ballot(c + HB_L < c1)) c += HB_L;
+        fresh = !__ballot(c + HB_L < c1);
+        if (!fresh) c += HB_L;
         else { ++r; fetch(); }
     };
     fetch();
@@ -707,8 +749,32 @@ __device__ __forceinline__ uint32_t walk_tails(const uint4* __restrict__ chunks,
         for (int q = 0; q < HB_D; ++q) {
             const uint4 h = M.head[hk[q]], t = M.tail[tk[q]];
             const uint32_t w[4] = {x[q].x | h.x | t.x, x[q].y | h.y | t.y, x[q].z | h.z | t.z, x[q].w | h.w | t.w};
+            if (GROUP) {
+                if (fs[q]) {   // the row's members of the group
+                    const uint32_t g0 = GRP_OFF + g * GRP_N;
+                    uint32_t b = 0;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) hits += (uint32_t)map[w[k] & 0xFFFFu] + (uint32_t)map[w[k] >> 16];
+                    for (int k = 0; k < 4; ++k) {
+                        const uint32_t lo = (w[k] & 0xFFFFu) - g0, hi = (w[k] >> 16) - g0;
+                        b |= (lo < GRP_N ? 1u : 0u) << (lo % GRP_N);
+                        b |= (hi < GRP_N ? 1u : 0u) << (hi % GRP_N);
+                    }
+                    own = or8(b);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    // byte addresses of two words at once; the count adds in the bit count itself
+                    const uint32_t at = __builtin_bit_cast(uint32_t, __builtin_bit_cast(Half2, w[k]) << (Half2)2);
+                    const uint32_t m0 = *(const uint32_t*)((const char*)map + (at & 0xFFFFu)) & own;
+                    const uint32_t m1 = *(const uint32_t*)((const char*)map + (at >> 16)) & own;
+                    asm("v_bcnt_u32_b32 %0, %1, %0" : "+v"(hits) : "v"(m0));
+                    asm("v_bcnt_u32_b32 %0, %1, %0" : "+v"(hits) : "v"(m1));
+                }
+            } else {
+                const uint8_t* bytes = (const uint8_t*)map;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) hits += (uint32_t)bytes[w[k] & 0xFFFFu] + (uint32_t)bytes[w[k] >> 16];
+            }
             issue(q);
         }
     }
@@ -728,16 +794,7 @@ __global__ __launch_bounds__(HB_NT, 2 * HB_W / 4) void k_isect_hub(IsectArgs a, 
     }
     R.load(a.hub->hub_tile, a.hub->hub_pref);
     for (uint32_t i = threadIdx.x; i < (HUB_SPAN + 1) / 16; i += HB_NT) ((uint4*)map)[i] = make_uint4(0, 0, 0, 0);
-    if (threadIdx.x <= HB_E) {
-        const uint32_t k = threadIdx.x;
-        uint32_t h[4], t[4];
-        for (uint32_t q = 0; q < 4; ++q) {
-            h[q] = (2 * q < k ? 0xFFFFu : 0u) | (2 * q + 1 < k ? 0xFFFF0000u : 0u);
-            t[q] = (2 * q + k >= HB_E ? 0xFFFFu : 0u) | (2 * q + 1 + k >= HB_E ? 0xFFFF0000u : 0u);
-        }
-        M.head[k] = make_uint4(h[0], h[1], h[2], h[3]);
-        M.tail[k] = make_uint4(t[0], t[1], t[2], t[3]);
-    }
+    M.fill();
     __syncthreads();
     const uint32_t wv = (uint32_t)wave_id(), ln = (uint32_t)lane_id();
     const uint32_t ntile = R.pref[NBUCKET];
@@ -770,7 +827,7 @@ __global__ __launch_bounds__(HB_NT, 2 * HB_W / 4) void k_isect_hub(IsectArgs a, 
             b0n = a.off[dn.x];
             b1n = a.off[dn.x + 1];
         }
-        const uint32_t hits = walk_tails((const uint4*)a.col16, (uint32_t)ent, (uint32_t)(ent >> 32), map, M);
+        const uint32_t hits = walk_tails<false>((const uint4*)a.col16, tail_start(ent), tail_end(ent), map, M, 0u);
         acc += hits;
         if (MIDDLE) {   // one update per tile
             const uint64_t t = wave_sum_u64(hits);
@@ -797,6 +854,93 @@ __global__ __launch_bounds__(HB_NT, 2 * HB_W / 4) void k_isect_hub(IsectArgs a, 
     if (threadIdx.x == 0) {
         uint64_t t = 0;
         for (int q = 0; q < HB_W; ++q) t += red[q];
+        partials[blockIdx.x] = t;
+    }
+}
+
+// ------------------------------------------------------------------ hub group kernel
+// The hub kernel's work (counts in all) for the GRP_SPAN top-ranked vertices, GRP_N consecutive
+// ones at a time: a row that holds several members of a group is read once, from its
+// first member on, for all of them, instead of once per member (R-MAT 24: 0.49 of the
+// elements, 32.6 of 60.0 GB in lines). The map is a word per rank: bit k, where the
+// group's k-th vertex has the rank as an out-neighbour. The in-edges of a group are
+// contiguous, as its vertices are; those whose row has an earlier member are
+// marked (CSC_FOLLOWS) and skipped. A tile is a stretch of grp_edges of them, long
+// enough that setting the words of 32 rows (10^4 to 10^5 elements) is small beside it; a wave
+// takes 64 in-edges at a time, with no barrier between a tile's set-up and its end.
+// Measured with the hub kernel for the ranks below: R-MAT 24 5.0 + 4.6 ms against 12.2 ms of the
+// hub kernel alone, R-MAT 20 0.46 + 0.07 against 0.64. Bound at R-MAT 24: line traffic
+// beyond L2, 33.5 GB at 6.7 TB/s (the hub kernel: 32.8 GB at 7.1); at R-MAT 20 the
+// set-up of many short tiles. Bit counts that add to their accumulator and byte
+// addresses made two at a time took it from 5.5 to 5.0 ms.
+__global__ __launch_bounds__(HB_NT, 2 * HB_W / 4) void k_isect_group(IsectArgs a, uint64_t* partials) {
+    __shared__ __align__(16) uint32_t words[GRP_SPAN];
+    __shared__ HubMasks M;
+    __shared__ uint32_t s_pref[GRP_COUNT + 1], s_off[GRP_N + 1], s_tile;
+    __shared__ uint64_t red[HB_W];
+    const uint32_t ntile = a.hub->grp_pref[GRP_COUNT];
+    if (blockIdx.x >= ntile) {
+        if (threadIdx.x == 0) partials[blockIdx.x] = 0;
+        return;
+    }
+    for (uint32_t i = threadIdx.x; i <= GRP_COUNT; i += HB_NT) s_pref[i] = a.hub->grp_pref[i];
+    for (uint32_t i = threadIdx.x; i < GRP_SPAN / 4; i += HB_NT) ((uint4*)words)[i] = make_uint4(0, 0, 0, 0);
+    M.fill();
+    const uint32_t per = a.hub->grp_edges, first = a.first_rank;
+    const uint32_t wv = (uint32_t)wave_id(), ln = (uint32_t)lane_id();
+    uint64_t acc = 0;
+    __syncthreads();
+    for (uint32_t i = blockIdx.x; i < ntile;) {
+        uint32_t g = 0;   // the last group whose prefix is at most i
+#pragma unroll
+        for (uint32_t step = GRP_COUNT / 2; step > 0; step >>= 1)
+            if (s_pref[g + step] <= i) g += step;
+        const uint32_t v0 = first + g * GRP_N;
+        if (threadIdx.x <= GRP_N) s_off[threadIdx.x] = a.off[v0 + threadIdx.x];
+        const uint32_t e0 = a.inoff[v0] + (i - s_pref[g]) * per, ee = a.inoff[v0 + GRP_N];
+        const uint32_t e1 = ee - e0 < per ? ee : e0 + per, inc = a.hub->grp_inc[g];
+        auto entry_at = [&](uint32_t q) -> uint64_t { return q < e1 ? a.csc[q] : CSC_FOLLOWS; };
+        uint32_t q = e0 + wv * WAVE + ln;
+        uint64_t ent = entry_at(q);
+        __syncthreads();
+        // the words: eight elements per thread and step
+        const uint32_t b0 = s_off[0], b1 = s_off[GRP_N];
+        for (uint32_t j = (b0 / HB_E + threadIdx.x) * HB_E; j < b1; j += HB_NT * HB_E) {
+            const uint4 x = ((const uint4*)a.col16)[j / HB_E];
+            const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+            uint32_t row = 0;   // the last row that starts at or before j
+#pragma unroll
+            for (uint32_t step = GRP_N / 2; step > 0; step >>= 1)
+                if (s_off[row + step] <= j) row += step;
+#pragma unroll
+            for (uint32_t k = 0; k < HB_E; ++k) {
+                const uint32_t at = j + k;
+                if (at < b0 || at >= b1) continue;
+                while (s_off[row + 1] <= at) ++row;
+                const uint32_t y = (w[k / 2] >> (16 * (k & 1))) & 0xFFFFu;
+                if ((inc >> row) & 1u) atomicOr(&words[grp_word(y)], 1u << row);
+            }
+        }
+        const uint32_t inext = grab_tile(a.ctrl, GRP_COUNTER, gridDim.x, &s_tile);   // barriers: the words are complete
+        while (__ballot(q < e1)) {
+            const uint64_t now = ent;
+            q += HB_NT;
+            ent = entry_at(q);
+            const bool lead = !(now & CSC_FOLLOWS);
+            acc += walk_tails<true>((const uint4*)a.col16, lead ? tail_start(now) - 1u : 0u,
+                                    lead ? tail_end(now) : 0u, words, M, g);
+        }
+        __syncthreads();   // the words have been read
+        for (uint32_t k = threadIdx.x; k < GRP_SPAN / 4; k += HB_NT) ((uint4*)words)[k] = make_uint4(0, 0, 0, 0);
+        i = inext;
+        // the next tile's barrier stands between these stores and its own
+    }
+    acc = wave_sum_u64(acc);
+    if (ln == 0) red[wv] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t t = 0;
+        for (int k = 0; k < HB_W; ++k) t += red[k];
         partials[blockIdx.x] = t;
     }
 }
@@ -978,7 +1122,7 @@ __global__ __launch_bounds__(IS_NT, VERTEX ? 4 : (MERGE ? 7 : 6)) void k_isect_e
             uint32_t c = 0, e = 0, v = 0;
             if (q < ne) {
                 v = S.v[sg];
-                const uint32_t s = (uint32_t)ent, end = (uint32_t)(ent >> 32);
+                const uint32_t s = tail_start(ent), end = tail_end(ent);
                 e = s - 1u;
                 const uint32_t nb = s_boff[sg + 1] - s_boff[sg];
                 const uint32_t bo = a.off[v];
@@ -1092,6 +1236,15 @@ int isect_blocks_per_cu(int ker, int mode) {
 
 uint32_t isect_hot_first(uint32_t n) { return n > HOT_N ? n - HOT_N : 0u; }
 
+int isect_group_blocks() {
+    static int blocks = 0;
+    if (!blocks) {
+        const int b = num_cu() * resident_blocks((const void*)k_isect_group, HB_NT);
+        blocks = b < PARTIALS_PER_KERNEL - HB_PARTIAL1 ? b : PARTIALS_PER_KERNEL - HB_PARTIAL1;
+    }
+    return blocks;
+}
+
 size_t isect_partials_bytes() { return sizeof(uint64_t) * NKERNEL * PARTIALS_PER_KERNEL; }
 
 void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hipStream_t s, IsectParts* parts) {
@@ -1111,12 +1264,17 @@ void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hip
         static int per_cu = 0;
         if (!per_cu) per_cu = resident_blocks((const void*)k_isect_hub<false>, HB_NT);
         int hg = num_cu() * per_cu;
-        if (hg > PARTIALS_PER_KERNEL - HB_PARTIAL0) hg = PARTIALS_PER_KERNEL - HB_PARTIAL0;
+        if (hg > HB_PARTIAL1 - HB_PARTIAL0) hg = HB_PARTIAL1 - HB_PARTIAL0;
         note(HB_PARTIAL0, hg);
         if (a.per_middle)
             hipLaunchKernelGGL(k_isect_hub<true>, dim3(hg), dim3(HB_NT), 0, s, a, p + HB_PARTIAL0);
         else
             hipLaunchKernelGGL(k_isect_hub<false>, dim3(hg), dim3(HB_NT), 0, s, a, p + HB_PARTIAL0);
+        if (a.groups) {
+            const int gg = isect_group_blocks();
+            note(HB_PARTIAL1, gg);
+            hipLaunchKernelGGL(k_isect_group, dim3(gg), dim3(HB_NT), 0, s, a, p + HB_PARTIAL1);
+        }
     }
     switch (ker) {
         case KER_MERGE:

@@ -535,10 +535,13 @@ __global__ __launch_bounds__(NT) void k_unique_write(const uint64_t* __restrict_
 // such a vertex gets no bucket and no tile, so they are never read (testing
 // d+(v) here would cost a random gather per edge). A length that does not fit
 // the packed field is stored as all ones, and the row end of u is gathered for
-// that entry later. Packing saves that gather for the others.
+// that entry later. Packing saves that gather for the others. FOLLOWS: a bit between
+// e and the length says that the row's entry before e is in v's group of the
+// GRP_N-vertex groups from gfirst on.
+template <bool FOLLOWS>
 __global__ __launch_bounds__(NT) void k_csc_keys(const uint32_t* __restrict__ col, const uint32_t* __restrict__ src,
                                                  const uint32_t* __restrict__ off, Ctrl* ctrl, int32_t n,
-                                                 uint64_t* __restrict__ keys, int sh, int lbits,
+                                                 uint64_t* __restrict__ keys, int sh, int lbits, uint32_t gfirst,
                                                  uint32_t* __restrict__ counts, uint32_t ntiles, uint32_t tile_keys,
                                                  RadixDigit dg, uint32_t* __restrict__ inend) {
     // inend[0..n): cleared on the way, for k_csc_finish
@@ -558,6 +561,15 @@ __global__ __launch_bounds__(NT) void k_csc_keys(const uint32_t* __restrict__ co
             v[k] = e < m ? col[e] : 0u;
             u[k] = e < m ? src[e] : 0u;
         }
+        uint32_t vp[FOLLOWS ? OR_U : 1], up[FOLLOWS ? OR_U : 1];   // the edge before
+        if (FOLLOWS) {
+#pragma unroll
+            for (int k = 0; k < OR_U; ++k) {
+                const uint64_t e = e0 + (uint64_t)k * NT;
+                vp[k] = e > 0 && e < m ? col[e - 1] : 0u;
+                up[k] = e > 0 && e < m ? src[e - 1] : ~0u;
+            }
+        }
         uint32_t end[OR_U];
 #pragma unroll
         for (int k = 0; k < OR_U; ++k) end[k] = off[u[k] + 1];   // rows ascend with e: near-sequential
@@ -569,6 +581,9 @@ __global__ __launch_bounds__(NT) void k_csc_keys(const uint32_t* __restrict__ co
             uint64_t low = e;
             if (lbits > 0) {
                 const uint64_t len = work ? end[k] - (e + 1) : 0u;
+                if (FOLLOWS)
+                    low = low << 1 | (up[k] == u[k] && vp[k] >= gfirst && (vp[k] - gfirst) / GRP_N == (v[k] - gfirst) / GRP_N
+                                          ? 1u : 0u);
                 low = (low << lbits) | (len < esc ? len : esc);
             }
             const uint64_t key = ((uint64_t)(work ? v[k] : (uint32_t)(n - 1)) << sh) | low;
@@ -587,24 +602,26 @@ __global__ __launch_bounds__(NT) void k_csc_keys(const uint32_t* __restrict__ co
 // load. Packed keys carry the length; otherwise the row end of u is gathered.
 // Thread t takes keys 2t and 2t + 1 (16-byte loads and stores, coalesced
 // across the wave) and reads the key after them.
-__device__ __forceinline__ uint64_t csc_range(uint64_t key, uint64_t emask, uint64_t lmask, int lbits,
+__device__ __forceinline__ uint64_t csc_range(uint64_t key, uint64_t emask, uint64_t lmask, int lbits, int fbit,
                                               const uint32_t* __restrict__ src, const uint32_t* __restrict__ off) {
     uint32_t e, end;
+    uint64_t follows = 0;
     if (lbits > 0) {
-        e = (uint32_t)((key >> lbits) & emask);
+        if (fbit) follows = (key >> lbits) << 63;
+        e = (uint32_t)((key >> (lbits + fbit)) & emask);
         const uint64_t len = key & lmask;
         end = len != lmask ? e + 1u + (uint32_t)len : off[src[e] + 1];
     } else {
         e = (uint32_t)key;
         end = off[src[e] + 1];
     }
-    return (uint64_t)(e + 1u) | ((uint64_t)end << 32);
+    return (uint64_t)(e + 1u) | ((uint64_t)end << 32) | follows;
 }
 
 __global__ __launch_bounds__(NT) void k_csc_finish(const uint64_t* __restrict__ keys, uint64_t* __restrict__ out,
                                                    Ctrl* ctrl, int32_t n, uint32_t* __restrict__ inend, int sh,
                                                    const uint32_t* __restrict__ src,
-                                                   const uint32_t* __restrict__ off, int ebits, int lbits) {
+                                                   const uint32_t* __restrict__ off, int ebits, int lbits, int fbit) {
     const uint32_t m = ctrl->m;
     const uint32_t last = (uint32_t)(n - 1);   // the group of in-edges without work
     const uint64_t emask = (1ull << ebits) - 1ull, lmask = (1ull << lbits) - 1ull;
@@ -629,8 +646,8 @@ __global__ __launch_bounds__(NT) void k_csc_finish(const uint64_t* __restrict__ 
             inend[v1] = (uint32_t)(i0 + 2);
             if (v2 == last) ctrl->m_active = (uint32_t)(i0 + 2);
         }
-        const uint64_t r0 = v0 < last ? csc_range(k0, emask, lmask, lbits, src, off) : 0ull;
-        const uint64_t r1 = v1 < last ? csc_range(k1, emask, lmask, lbits, src, off) : 0ull;
+        const uint64_t r0 = v0 < last ? csc_range(k0, emask, lmask, lbits, fbit, src, off) : 0ull;
+        const uint64_t r1 = v1 < last ? csc_range(k1, emask, lmask, lbits, fbit, src, off) : 0ull;
         if (i0 + 2 <= m) {
             U64x2 w;
             w.a = r0;
@@ -747,7 +764,7 @@ __global__ __launch_bounds__(NBUCKET) void k_select(Ctrl* ctrl, int mode, const 
         bucket_features(ctrl, b, f);
         for (int i = 0; i < MLP_IN; ++i) ctrl->features[b][i] = f[i];
     }
-    if (hub) hub->first[b] = ~0u;   // set by k_emit_tiles
+    if (hub) hub->first[b] = hub->grp[b] = ~0u;   // set by k_emit_tiles
     int ch;
     if (mode == SEL_FORCE_MERGE) ch = KER_MERGE;
     else if (mode == SEL_FORCE_BSEARCH) ch = KER_BSEARCH;
@@ -856,7 +873,7 @@ __global__ __launch_bounds__(NT) void k_emit_tiles(const uint32_t* __restrict__ 
                                                    const uint32_t* __restrict__ inoff,
                                                    const uint32_t* __restrict__ tstart, int32_t n, Ctrl* ctrl,
                                                    uint4* __restrict__ tiles, uint64_t tile_cap,
-                                                   HubTab* __restrict__ hub) {
+                                                   HubTab* __restrict__ hub, uint32_t gfirst) {
     for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) {
         const uint32_t b = vbucket[vlist[i]];
         const int kk = b == BUCKET_NONE ? NKERNEL : ctrl->choice[b];
@@ -879,6 +896,8 @@ __global__ __launch_bounds__(NT) void k_emit_tiles(const uint32_t* __restrict__ 
                 if (hub && kk == KER_BITMAP && v >= hub_first((uint32_t)n) &&
                     ((uint32_t)i == ctrl->bstart[b] || vlist[i - 1] < hub_first((uint32_t)n)))
                     hub->first[b] = t0;
+                if (hub && kk == KER_BITMAP && v >= gfirst && ((uint32_t)i == ctrl->bstart[b] || vlist[i - 1] < gfirst))
+                    hub->grp[b] = t0;   // and the group kernel's a suffix of these
                 for (uint32_t t = t0; t < t1 && t < tile_cap; ++t) {
                     const uint32_t e0 = e_beg + (t - t0) * K;
                     tiles[t] = make_uint4(v, e0, (e0 + K < e_end ? e0 + K : e_end) - e0, 0u);
@@ -894,18 +913,26 @@ __global__ __launch_bounds__(NT) void k_emit_tiles(const uint32_t* __restrict__ 
 }
 
 // Tile ranges of the bitmap kernel and of the hub kernel, per bucket in slot
-// order (one thread per slot). The hub kernel gets tiles on graphs with about
+// order (one thread per slot), and the group kernel's tiles. The hub kernel gets tiles on graphs with about
 // HUB_MIN_TAILS tail elements or more: its columns, its launch and its longer
 // set-up per tile cost 50 us and more, which it makes up for around there (R-MAT
 // 20, 1.2e9 tail elements: 2.69 -> 2.66 ms; R-MAT 21, 3e9: 5.52 -> 5.27 ms; Chung-Lu of 40
 // million pairs, 0.5e9: 6.99 ms without, 7.02 ms with it).
 constexpr uint64_t HUB_MIN_TAILS = 1ull << 30;
+// In-edges per tile of the group kernel: GRP_TILES tiles per block, within limits (6 and 24 tiles
+// per block: R-MAT 24 43.4 and 43.1 ms against 43.1, R-MAT 20 2433 and 2480 us against 2432).
+constexpr uint32_t GRP_TILES = 12, GRP_EDGES_MIN = 2048, GRP_EDGES_MAX = 16384;
+static_assert(GRP_COUNT % NBUCKET == 0, "whole groups per thread");
 __global__ __launch_bounds__(NBUCKET) void k_hub_ranges(const Ctrl* ctrl, const uint32_t* __restrict__ tstart,
-                                                        HubTab* __restrict__ hub) {
+                                                        const uint8_t* __restrict__ vbucket,
+                                                        const uint32_t* __restrict__ inoff, uint32_t gfirst,
+                                                        uint32_t group_blocks, HubTab* __restrict__ hub) {
     __shared__ uint32_t s_bucket[NBUCKET];
     __shared__ uint32_t scratch[NBUCKET / WAVE];
     const uint32_t r = threadIdx.x;
+    __shared__ uint8_t s_single[NBUCKET];   // single-vertex tiles of the bitmap strategy
     s_bucket[ctrl->slot[r]] = r;
+    s_single[r] = r != (uint32_t)BUCKET_NONE && ctrl->choice[r] == KER_BITMAP && tile_group(ctrl, r) == 1u;
     __syncthreads();
     const uint32_t b = s_bucket[r];
     // tail elements of the graph, about: sum over u of d+(u)^2 / 2 from the buckets' means
@@ -919,6 +946,7 @@ __global__ __launch_bounds__(NBUCKET) void k_hub_ranges(const Ctrl* ctrl, const 
     if (nv && ctrl->choice[b] == KER_BITMAP) {
         t0 = tstart[ctrl->bstart[b]];
         t1 = tstart[ctrl->bend[b]];
+        if (use && group_blocks && hub->grp[b] != ~0u) t1 = hub->grp[b];
         h = use && hub->first[b] != ~0u ? hub->first[b] : t1;
     }
     uint32_t rest, hubs;
@@ -928,9 +956,37 @@ __global__ __launch_bounds__(NBUCKET) void k_hub_ranges(const Ctrl* ctrl, const 
     hub->rest_pref[r] = pr;
     hub->hub_tile[r] = h;
     hub->hub_pref[r] = ph;
+    // the group kernel: two groups per thread
+    constexpr uint32_t GPT = GRP_COUNT / NBUCKET;
+    uint32_t inc[GPT], edges[GPT], mine = 0, total, tiles, nt[GPT], sum = 0;
+    for (uint32_t k = 0; k < GPT; ++k) {
+        inc[k] = edges[k] = 0;
+        if (!use || !group_blocks) continue;
+        const uint32_t v0 = gfirst + (r * GPT + k) * GRP_N;
+        uint32_t w[GRP_N / 4];   // the group's buckets, at any alignment
+        __builtin_memcpy(w, vbucket + v0, GRP_N);
+#pragma unroll
+        for (uint32_t q = 0; q < GRP_N; ++q)
+            inc[k] |= s_single[(w[q / 4] >> (8 * (q & 3))) & 0xFFu] ? 1u << q : 0u;
+        edges[k] = inc[k] ? inoff[v0 + GRP_N] - inoff[v0] : 0u;
+        mine += edges[k];
+    }
+    (void)block_exclusive_scan<NBUCKET>(mine, scratch, &total);
+    uint32_t per = group_blocks ? total / (group_blocks * GRP_TILES) : 0u;
+    per = per < GRP_EDGES_MIN ? GRP_EDGES_MIN : (per > GRP_EDGES_MAX ? GRP_EDGES_MAX : per);
+    for (uint32_t k = 0; k < GPT; ++k) sum += nt[k] = (edges[k] + per - 1u) / per;
+    uint32_t pg = block_exclusive_scan<NBUCKET>(sum, scratch, &tiles);
+    for (uint32_t k = 0; k < GPT; ++k) {
+        hub->grp_inc[r * GPT + k] = inc[k];
+        hub->grp_pref[r * GPT + k] = pg;
+        pg += nt[k];
+    }
     if (r == 0) {
         hub->rest_pref[NBUCKET] = rest;
         hub->hub_pref[NBUCKET] = hubs;
+        hub->grp_pref[GRP_COUNT] = tiles;
+        hub->grp_edges = per;
+        hub->used = hubs + tiles;
     }
 }
 
@@ -939,7 +995,7 @@ __global__ __launch_bounds__(NBUCKET) void k_hub_ranges(const Ctrl* ctrl, const 
 // the capacity by at least the last group's padding: see hub_usable).
 __global__ __launch_bounds__(NT) void k_col16(const uint32_t* __restrict__ col, const Ctrl* ctrl, uint32_t base,
                                               const HubTab* __restrict__ hub, uint16_t* __restrict__ out) {
-    if (hub->hub_pref[NBUCKET] == 0) return;
+    if (hub->used == 0) return;
     const uint64_t m = ctrl->m;
     for (uint64_t i = ((uint64_t)blockIdx.x * NT + threadIdx.x) * 8; i < m; i += (uint64_t)gridDim.x * NT * 8) {
         uint32_t x[8];
@@ -1066,26 +1122,32 @@ __global__ void k_set_tile_range(Ctrl* ctrl, int ker, uint32_t t0, uint32_t t1) 
 
 // The intersection kernels' shared tile counters, zeroed before a relaunch.
 static void reset_tile_counters(Ctrl* ctrl, hipStream_t s) {
-    fill_u32(ctrl->tile_next, 0u, NKERNEL + 1, s);
+    fill_u32(ctrl->tile_next, 0u, NKERNEL + 2, s);
 }
 
 // Packed in-edge keys: v, e, and the tail length in the bits left over (at
 // most what the bound d+(u) <= sqrt(2E) needs; lengths that do not fit are
 // escaped). Without room for at least 6 length bits, e alone is kept.
+// follows: a bit above the length for CSC_FOLLOWS (fbit 1; 0 without room).
 struct CscPacking {
-    int sh, ebits, lbits;
+    int sh, ebits, lbits, fbit;
 };
 
-static CscPacking csc_packing(int64_t E, int32_t n) {
+static CscPacking csc_packing(int64_t E, int32_t n, bool follows) {
     const uint64_t twoE = 2ull * (uint64_t)E;
     uint64_t r = (uint64_t)sqrt((double)twoE);   // floor(sqrt(2E)), the bound on d+(u)
     while (r * r > twoE) --r;
     while ((r + 1) * (r + 1) <= twoE) ++r;
     const int eb = bits_for((uint64_t)E), vb = bits_for((uint64_t)n);
     int lb = bits_for(r + 2);   // lengths below r + 1, plus the escape value
-    if (lb > 64 - vb - eb) lb = 64 - vb - eb;
-    if (lb >= 6) return {eb + lb, eb, lb};
-    return {32, 32, 0};
+    const int room = 64 - vb - eb;
+    if (follows && room >= 7) {
+        if (lb > room - 1) lb = room - 1;
+        return {eb + 1 + lb, eb, lb, 1};
+    }
+    if (lb > room) lb = room;
+    if (lb >= 6) return {eb + lb, eb, lb, 0};
+    return {32, 32, 0, 0};
 }
 
 // ------------------------------------------------------------------ workspace layout
@@ -1166,6 +1228,8 @@ static IsectArgs isect_args(const RunArgs& r, const Layout& L, uint64_t* csc) {
     ia.clip = r.formulation != FORM_FILTERED ? 1u : 0u;
     ia.col16 = nullptr;
     ia.hub = nullptr;
+    ia.groups = false;
+    ia.first_rank = 0;
     return ia;
 }
 
@@ -1193,6 +1257,13 @@ static bool hub_usable(const RunArgs& r) {
            !r.per_edge_counts && !r.support && !r.list_out;
 }
 
+// The group kernel takes part where only the count is asked for, all HUB_SPAN columns
+// exist, and the packed in-edge keys have room for its mark.
+static bool groups_wanted(const RunArgs& r) {
+    return hub_usable(r) && !r.per_middle && r.n >= (int32_t)HUB_SPAN && r.E < (1ll << 31);
+}
+static bool groups_usable(const RunArgs& r) { return groups_wanted(r) && csc_packing(r.E, r.n, true).fbit; }
+
 // Its tables take the degree count's bucket starts, dead since the degree stage.
 static HubTab* hub_tab(const RunArgs& r, const Layout& L) {
     static_assert(sizeof(HubTab) <= 4 * ((1u << DEG_MAX_BUCKET_BITS) + 4), "hub tables fit the bucket starts");
@@ -1205,8 +1276,11 @@ static void prepare_hub(const RunArgs& r, const Layout& L, const uint64_t* csc, 
     if (!hub) return;
     char* ws = (char*)r.ws;
     uint16_t* col16 = (uint16_t*)(csc == (const uint64_t*)(ws + L.keysA) ? ws + L.keysB : ws + L.keysA);
+    ia.groups = groups_usable(r);
+    ia.first_rank = ia.groups ? grp_first((uint32_t)r.n) : 0u;
     hipLaunchKernelGGL(k_hub_ranges, dim3(1), dim3(NBUCKET), 0, r.stream, ia.ctrl, (const uint32_t*)(ws + L.tstart),
-                       hub);
+                       (const uint8_t*)(ws + L.vbucket), ia.inoff, ia.first_rank,
+                       ia.groups ? (uint32_t)isect_group_blocks() : 0u, hub);
     hipLaunchKernelGGL(k_col16, dim3(grid_for((size_t)r.E / 8 + 1)), dim3(NT), 0, r.stream, ia.col, ia.ctrl,
                        hub_first((uint32_t)r.n), hub, col16);
     ia.col16 = col16;
@@ -1479,17 +1553,19 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         // in-edge groups: ids 0 .. n - 1 (n - 1 = no work). Each in-edge carries its
         // own edge index and tail, so the order inside a group is free: the
         // sort's first pass only partitions.
-        const CscPacking pk = csc_packing(E, n);
-        hipLaunchKernelGGL(k_csc_keys, dim3(e_tiles < 16384u ? e_tiles : 16384u), dim3(NT), 0, s, col, src, off,
-                           ctrl, n, other, pk.sh, pk.lbits, radix_first_counts(radix_tmp), e_tiles, e_tile,
-                           radix_first_digit(pk.sh, pk.sh + nbv), rowend);
+        const CscPacking pk = csc_packing(E, n, groups_wanted(r));
+        auto csc_keys = pk.fbit ? k_csc_keys<true> : k_csc_keys<false>;
+        hipLaunchKernelGGL(csc_keys, dim3(e_tiles < 16384u ? e_tiles : 16384u), dim3(NT), 0, s, col, src, off,
+                           ctrl, n, other, pk.sh, pk.lbits, pk.fbit ? grp_first((uint32_t)n) : 0u,
+                           radix_first_counts(radix_tmp), e_tiles, e_tile, radix_first_digit(pk.sh, pk.sh + nbv),
+                           rowend);
         const int alt2 = radix_sort_u64(other, sorted, nullptr, nullptr, &ctrl->m, (size_t)E, pk.sh, pk.sh + nbv,
                                         radix_tmp, s, true, true, &ctrl->err);
         // bounds and tail ranges in one pass, into the buffer the sort left free
         const uint64_t* ckeys = alt2 ? sorted : other;
         csc = alt2 ? other : sorted;
         hipLaunchKernelGGL(k_csc_finish, dim3(grid_for(((size_t)E + 1) / 2)), dim3(NT), 0, s, ckeys,
-                           csc, ctrl, n, rowend, pk.sh, src, off, pk.ebits, pk.lbits);
+                           csc, ctrl, n, rowend, pk.sh, src, off, pk.ebits, pk.lbits, pk.fbit);
         scan_offsets_max_u32(rowend, inoff, (size_t)n, scan_tmp, s);
     } else {
         // ---- all in-edges grouped by v; the symmetric adjacency; the streamed ranges
@@ -1530,7 +1606,8 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
     }
     scan_exclusive_sum_u32(tstart, tstart, (size_t)n + 1, scan_tmp, s);
     hipLaunchKernelGGL(k_emit_tiles, dim3(grid_for((size_t)n)), dim3(NT), 0, s, vlist, vbucket, inoff, tstart, n,
-                       ctrl, tiles, (uint64_t)L.tile_cap, hub_tab(r, L));
+                       ctrl, tiles, (uint64_t)L.tile_cap, hub_tab(r, L),
+                       groups_usable(r) ? grp_first((uint32_t)n) : ~0u);
     if (r.per_edge_counts) fill_u32(r.per_edge_counts, 0u, (size_t)E, s);
     if (r.support) fill_u32(r.support, 0u, (size_t)E, s);
     if (r.per_vertex || r.per_middle || r.clustering) fill_u64(pv, 0ull, (size_t)n, s);
