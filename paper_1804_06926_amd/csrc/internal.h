@@ -179,8 +179,11 @@ struct HubTab {
     uint32_t rest_tile[NBUCKET], rest_pref[NBUCKET + 1];
     uint32_t hub_tile[NBUCKET], hub_pref[NBUCKET + 1];
     uint32_t grp_inc[GRP_COUNT], grp_pref[GRP_COUNT + 1], grp_edges;
-    uint32_t used;                    // tiles of the hub and the group kernel
+    uint32_t wave_pos[NBUCKET], wave_pref[NBUCKET + 1];   // the wave kernel's: positions of the vertex list
+    uint32_t used;                    // tiles of the hub and the group kernel, vertices of the wave kernel
 };
+// The wave kernel (the bitmap strategy, a wave per vertex) takes ranks below this.
+constexpr uint32_t WV_SLOTS = 2048, WV_TAG = 0x7FFF, WV_RANKS = WV_TAG * WV_SLOTS;
 // An in-edge entry (tail start | tail end << 32) whose row holds an earlier member of
 // the same group (only where the group kernel may run).
 constexpr uint64_t CSC_FOLLOWS = 1ull << 63;

@@ -43,6 +43,7 @@ struct IsectArgs {
     const uint16_t* col16;
     const HubTab* hub;
     bool groups;           // the group kernel runs too (it counts in all only)
+    bool waves;            // so does the wave kernel
     uint32_t first_rank;   // the lowest rank of its groups
 };
 
@@ -57,9 +58,9 @@ size_t isect_partials_bytes();
 // per launch.
 struct IsectParts {
     int launches = 0;
-    uint32_t first[NKERNEL + 2], n[NKERNEL + 2];
+    uint32_t first[NKERNEL + 3], n[NKERNEL + 3];
 };
-// One intersection kernel over its tile range (the bitmap strategy: two or three kernels, when a.hub is set);
+// One intersection kernel over its tile range (the bitmap strategy: up to four kernels, when a.hub is set);
 // per-block partial counts go to partials (isect_partials_bytes() of workspace shared by the
 // kernels), their places are added to parts (may be null).
 void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hipStream_t s, IsectParts* parts = nullptr);

@@ -330,20 +330,29 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
     IsectArgs a, uint64_t* partials) {
     constexpr bool VERTEX = MODE == BM_VERTEX, SUPPORT = MODE == BM_SUPPORT;
     constexpr bool CLIP = MODE == BM_CLIP;
+    // Counts alone take the windows from the top of the middle list down, each as far as its
+    // highest element not yet in one, and after each keep of every tail only what lies
+    // below the window (s_cut). Ranks ascend with the degree, so nearly all of a tail lies in the
+    // first window; walking whole tails once per window read R-MAT 24's remaining 6.9e9 tail
+    // elements 12.2e9 times (with it, beside the wave kernel, 39.0 -> 38.5 ms).
+    constexpr bool SHRINK = MODE == BM_COUNT || MODE == BM_MIDDLE;
+    constexpr int WORDS = SHRINK ? BM_WORDS - CHUNK_MAX : BM_WORDS;   // the same LDS with s_cut
+    constexpr uint32_t BITS = (uint32_t)WORDS * 32u;
     constexpr bool need_cnt = MODE != BM_COUNT && MODE != BM_MIDDLE && !CLIP;
     __shared__ uint32_t s_hot[VERTEX ? HOT_N : 1];
     __shared__ uint32_t s_wc[SUPPORT ? NV_MAX : 1];       // hits per element of N+(v)
-    __shared__ uint16_t s_first[SUPPORT ? BM_WORDS : 1];  // position in N+(v) of a word's first element
+    __shared__ uint16_t s_first[SUPPORT ? WORDS : 1];  // position in N+(v) of a word's first element
     const Hot hot = {VERTEX ? s_hot : nullptr, a.hot_first};
     if (VERTEX) hot.clear();
-    __shared__ uint32_t bm[BM_WORDS + 1];        // + one always-zero word for out-of-window positions
+    __shared__ uint32_t bm[WORDS + 1];        // + one always-zero word for out-of-window positions
     __shared__ uint16_t s_wst[WT_MAX];           // entry holding the first item of each window of a chunk
     __shared__ uint32_t s_pref[CHUNK_MAX + 1];
     __shared__ uint32_t s_cnt[need_cnt ? CHUNK_MAX : 1];
+    __shared__ uint32_t s_cut[SHRINK ? CHUNK_MAX : 1];   // one past an entry's last item below the window, or 0
     __shared__ uint32_t s_base[CHUNK_MAX + 1];   // entry nt is read (unused) by lanes past the end
     __shared__ uint8_t s_flag[IS_NT / WAVE][UNROLL][WAVE];    // entry-start marks, one slot per item offset
     __shared__ SegsT<SEG_MAX_BITMAP> S;
-    for (int i = threadIdx.x; i <= BM_WORDS; i += IS_NT) bm[i] = 0;
+    for (int i = threadIdx.x; i <= WORDS; i += IS_NT) bm[i] = 0;
     for (int i = threadIdx.x; i < (IS_NT / WAVE) * UNROLL * WAVE; i += IS_NT) (&s_flag[0][0][0])[i] = 0;
     uint64_t acc = 0;
     __shared__ uint32_t s_tile;
@@ -379,7 +388,7 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
             if (!CLIP) nt = entry_table<IS_NT, EH, need_cnt>(st_h, len_h, s_pref, s_base, s_cnt, S.scratch, nl, L);
             const uint32_t lo = a.col[b0], hi = a.col[b1 - 1];
             const uint32_t base = lo & ~31u;
-            const uint32_t nwin = (hi - base) / BM_BITS + 1;
+            const uint32_t nwin = (hi - base) / BITS + 1;
             const bool gather = SUPPORT && nb <= (uint32_t)NV_MAX;
             if (gather)
                 for (uint32_t j = threadIdx.x; j < nb; j += IS_NT) s_wc[j] = 0u;
@@ -393,11 +402,22 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
                     cv_h[h] = len_h[h] ? (uint64_t)col_at<NARROW>(a.col, st_h[h]) : ~0ull;
             }
             uint32_t mnext = 0;   // clipped: first element of the middle list not yet in a window
-            for (uint32_t win = 0; win < nwin; ++win) {
-                const uint32_t wlo = base + win * BM_BITS;
+            uint32_t left = nb;   // SHRINK: elements of the middle list in no window yet
+            for (uint32_t win = 0; SHRINK || win < nwin; ++win) {
+                uint32_t wlo = base + win * BITS;
                 uint32_t j0 = 0, j1 = nb;   // elements of the middle list set in this window
+                bool more = false;          // SHRINK: a window follows
+                if (SHRINK) {
+                    const uint32_t top = win ? a.col[b0 + left - 1u] : hi;
+                    wlo = top >= BITS ? top - (BITS - 1u) : 0u;
+                    j1 = left;
+                    if (lo < wlo) j0 = wave_first_at_least<NARROW>(a.col, b0, b0 + left, wlo) - b0;
+                    more = j0 > 0;
+                    if (more)
+                        for (uint32_t k = threadIdx.x; k < nt; k += IS_NT) s_cut[k] = 0;
+                }
                 if (CLIP) {
-                    const uint64_t whi = (uint64_t)wlo + BM_BITS;
+                    const uint64_t whi = (uint64_t)wlo + BITS;
                     j0 = mnext;
                     j1 = wave_first_at_least<NARROW>(a.col, b0 + j0, b1, whi) - b0;
                     mnext = j1;
@@ -424,7 +444,7 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
                 }
                 for (uint32_t j = j0 + threadIdx.x; j < j1; j += IS_NT) {
                     const uint32_t x = a.col[b0 + j] - wlo;
-                    if (x < BM_BITS) {
+                    if (x < BITS) {
                         atomicOr(&bm[x >> 5], 1u << (x & 31u));
                         if (gather && (j == 0 || (a.col[b0 + j - 1] - wlo) >> 5 != x >> 5))
                             s_first[x >> 5] = (uint16_t)j;
@@ -526,18 +546,32 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
                             for (int j = 0; j < UNROLL; ++j) xs[j] = col_at<NARROW>(a.col, ad[j]);
     #pragma unroll
                             for (int j = 0; j < UNROLL; ++j)
-                                xs[j] = (W + j * WAVE + ln < q1) ? xs[j] - wlo : 0xFFFFFFFFu;
+                                xs[j] = (W + j * WAVE + ln < q1) ? xs[j] - wlo : 0x7FFFFFFFu;
                         }
                         // membership: bit positions past the window map to the spare
-                        // always-zero word bm[BM_WORDS]
+                        // always-zero word bm[WORDS]
                         uint32_t wd[UNROLL];
 #pragma unroll
-                        for (int j = 0; j < UNROLL; ++j) wd[j] = bm[(xs[j] < BM_BITS ? xs[j] : BM_BITS) >> 5];
+                        for (int j = 0; j < UNROLL; ++j) wd[j] = bm[(xs[j] < BITS ? xs[j] : BITS) >> 5];
                         uint32_t hits = 0;
 #pragma unroll
                         for (int j = 0; j < UNROLL; ++j) hits += __builtin_amdgcn_ubfe(wd[j], xs[j], 1u);
                         acc += hits;
                         if (MODE == BM_MIDDLE) seg_sum += hits;
+                        if (SHRINK && more) {
+                            // an entry's items below the window are its first ones: the last of
+                            // them in this wave's 64 items marks the cut
+#pragma unroll
+                            for (int j = 0; j < UNROLL; ++j) {
+                                const bool below = (int32_t)xs[j] < 0;
+                                const uint64_t B = __ballot(below);
+                                if (!B) continue;
+                                const uint32_t kn = (uint32_t)__shfl_down((int)ks[j], 1, WAVE);
+                                const bool next = ((B >> 1) >> ln) & 1ull;   // never for lane 63
+                                if (below && !(next && kn == ks[j]))
+                                    atomicMax(&s_cut[ks[j]], W + (uint32_t)j * WAVE + ln + 1u);
+                            }
+                        }
                         if (!need_cnt) continue;
                         const bool long_round = W + WAVE * UNROLL <= lim;
 #pragma unroll
@@ -575,9 +609,25 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
                 __syncthreads();
                 for (uint32_t j = j0 + threadIdx.x; j < j1; j += IS_NT) {
                     const uint32_t x = a.col[b0 + j] - wlo;
-                    if (x < BM_BITS) bm[x >> 5] = 0u;
+                    if (x < BITS) bm[x >> 5] = 0u;
                 }
                 __syncthreads();
+                if (SHRINK) {
+                    if (!more) break;
+                    left = j0;
+                    uint32_t cs_h[EH], cl_h[EH];
+#pragma unroll
+                    for (int h = 0; h < EH; ++h) {
+                        const uint32_t k = EH * threadIdx.x + (uint32_t)h;
+                        cs_h[h] = cl_h[h] = 0;
+                        if (k < nt && s_cut[k] > s_pref[k]) {
+                            cl_h[h] = s_cut[k] - s_pref[k];
+                            cs_h[h] = s_base[k] + s_pref[k];
+                        }
+                    }
+                    nt = entry_table<IS_NT, EH, false>(cs_h, cl_h, s_pref, s_base, s_cnt, S.scratch, nl, L);
+                    if (L == 0) break;   // the same for the whole block
+                }
             }
             if (gather) {
                 for (uint32_t j = threadIdx.x; j < nb; j += IS_NT) {
@@ -642,8 +692,8 @@ constexpr int HB_D = 3;                   // steps in flight
 constexpr uint32_t HB_L = 8;              // lanes per tail
 constexpr uint32_t HB_R = WAVE / HB_L;    // tails walked together by a wave
 constexpr uint32_t HB_E = 8;              // elements per chunk
-constexpr int HB_PARTIAL0 = 3072, HB_PARTIAL1 = 3584;   // partial slots of the bitmap kernel's share from here on
-                                                      // (the hub kernel's, the group kernel's)
+// partial slots of the bitmap kernel's share from here on: the wave, the hub and the group kernel's
+constexpr int WV_PARTIAL0 = 1536, HB_PARTIAL0 = 3072, HB_PARTIAL1 = 3584;
 static_assert(CHUNK_MAX <= HB_NT, "one in-edge per lane");
 
 // Order of magnitude of a step count: 0, 1, 2, 3, then two classes per doubling, at most HB_CLS - 1.
@@ -943,6 +993,190 @@ __global__ __launch_bounds__(HB_NT, 2 * HB_W / 4) void k_isect_group(IsectArgs a
         for (int k = 0; k < HB_W; ++k) t += red[k];
         partials[blockIdx.x] = t;
     }
+}
+
+// ------------------------------------------------------------------ wave kernel
+// The bitmap strategy for vertices of few in-edges (several of them to a tile of the
+// bitmap kernel; counts in all or per middle vertex): a wave per vertex and no barrier, as
+// there a block's time goes to the chain of set-up loads, barriers and windows
+// of one vertex after the other. N+(v) is a table of 15-bit tags (rank / WV_SLOTS) at
+// slot rank % WV_SLOTS, so that one probe answers for ranks of any distance and there
+// are no windows. A rank whose slot is taken goes to a small open table of whole
+// ranks, and the slot's top bit says so: a probe that meets another tag with that
+// bit set looks there. N+(v) is taken in parts where that table would fill up.
+// Eight lanes walk a tail together, a 16-byte chunk per lane and step.
+// R-MAT 24: the bitmap kernel's remaining 9.6 ms -> 3.6 ms for it and 1.7 here (11.5 GB at
+// 6.5 TB/s; the bitmap kernel now 26 GB at 7.2, the traffic limit); a batch of
+// Chung-Lu graphs 3.0 -> 1.4 + 0.6 ms. Which vertices: those of fewer than 1024 in-edges in
+// buckets without a hub tile (fewer than 128, 256, 512, 1024, 2048, 8192: R-MAT 24 38.6,
+// 38.5, 38.4, 38.4, 38.4, 38.5 ms, the batch 22.6, 22.2, 22.2, 22.0, 21.9, 22.0). The part
+// of such a bucket below the hub ranks was slower here (38.8 ms): middle lists of
+// up to 1000 elements, in several parts.
+constexpr int WV_NT = 256, WV_W = WV_NT / WAVE, WV_D = 3;
+constexpr uint32_t WV_OVF = 256, WV_E = 4;   // whole ranks; elements per chunk
+constexpr uint32_t WV_FLAG = 0x8000u;
+
+struct WaveSet {
+    uint16_t tag[WV_SLOTS];
+    uint32_t ovf[WV_OVF];
+};
+__device__ __forceinline__ void wave_order() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
+__device__ __forceinline__ uint32_t ovf_slot(uint32_t x) { return (x / WV_SLOTS * 37u + x) % WV_OVF; }
+
+// Elements of this wave's tails that the set holds; S, E as in walk_tails, in the columns.
+__device__ __forceinline__ uint32_t walk_set(const uint4* __restrict__ chunks, uint32_t S, uint32_t E,
+                                             const WaveSet& set) {
+    const uint32_t ln = (uint32_t)lane_id(), gl = ln % HB_L, gi = ln / HB_L;
+    const uint32_t nch = S < E ? (E - 1u) / WV_E + 1u - S / WV_E : 0u;
+    const uint32_t cls = step_class((nch + HB_L - 1) / HB_L);
+    uint32_t pos = 0, base = 0, live = 0;
+#pragma unroll
+    for (int c = HB_CLS - 1; c >= 0; --c) {
+        const uint64_t B = __ballot(cls == (uint32_t)c);
+        const uint32_t below =
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(B >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)B, 0u));
+        if (cls == (uint32_t)c) pos = base + below;
+        if (c == 0) live = base;
+        base += (uint32_t)__popcll(B);
+    }
+    S = (uint32_t)__builtin_amdgcn_ds_permute((int)(pos * 4u), (int)S);
+    E = (uint32_t)__builtin_amdgcn_ds_permute((int)(pos * 4u), (int)E);
+    const uint32_t rounds = (live + HB_R - 1) / HB_R;
+    uint32_t r = 0, s = 0, e = 0, c = 0, c1 = 0, issued = 0, hits = 0;
+    auto fetch = [&]() {
+        const int from = (int)(((r * HB_R + gi) & (WAVE - 1)) * 4u);
+        s = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)S);
+        e = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)E);
+        c = s / WV_E + gl;
+        c1 = (r < rounds && s < e) ? (e - 1u) / WV_E + 1u : 0u;
+    };
+    uint4 x[WV_D];
+    uint32_t at[WV_D], len[WV_D];   // of the chunk's first element in the tail (modular); the tail's length
+    auto issue = [&](int q) {
+        const bool on = c < c1;
+        x[q] = chunks[on ? c : 0u];   // unconditional: lanes without a chunk read a valid one
+        at[q] = c * WV_E - s;
+        len[q] = on ? e - s : 0u;
+        if (r < rounds) ++issued;
+        if (__ballot(c + HB_L < c1)) c += HB_L;
+        else { ++r; fetch(); }
+    };
+    fetch();
+#pragma unroll
+    for (int q = 0; q < WV_D; ++q) issue(q);
+    for (uint32_t done = 0; done < issued; done += WV_D) {
+#pragma unroll
+        for (int q = 0; q < WV_D; ++q) {
+            const uint32_t w[WV_E] = {x[q].x, x[q].y, x[q].z, x[q].w};
+            uint32_t y[WV_E];
+#pragma unroll
+            for (uint32_t k = 0; k < WV_E; ++k) y[k] = set.tag[w[k] % WV_SLOTS];
+            bool other = false;
+#pragma unroll
+            for (uint32_t k = 0; k < WV_E; ++k) {
+                const bool in = at[q] + k < len[q];
+                y[k] = in ? y[k] ^ (w[k] / WV_SLOTS) : 1u;
+                hits += (y[k] & WV_TAG) == 0u ? 1u : 0u;
+                other |= y[k] > WV_FLAG;   // another tag, and the slot has overflowed
+            }
+            if (__ballot(other)) {
+#pragma unroll
+                for (uint32_t k = 0; k < WV_E; ++k) {
+                    if (y[k] <= WV_FLAG) continue;
+                    uint32_t h = ovf_slot(w[k]), o;
+                    while ((o = set.ovf[h]) != ~0u && o != w[k]) h = (h + 1u) % WV_OVF;
+                    hits += o == w[k] ? 1u : 0u;
+                }
+            }
+            issue(q);
+        }
+    }
+    return hits;
+}
+
+template <bool MIDDLE>
+__global__ __launch_bounds__(WV_NT, 6) void k_isect_wave(IsectArgs a, uint64_t* partials) {
+    __shared__ __align__(16) WaveSet sets[WV_W];
+    __shared__ uint32_t s_pos[NBUCKET], s_pref[NBUCKET + 1];
+    const uint32_t total = a.hub->wave_pref[NBUCKET];
+    for (uint32_t i = threadIdx.x; i < (uint32_t)NBUCKET; i += WV_NT) s_pos[i] = a.hub->wave_pos[i];
+    for (uint32_t i = threadIdx.x; i <= (uint32_t)NBUCKET; i += WV_NT) s_pref[i] = a.hub->wave_pref[i];
+    __syncthreads();
+    const uint32_t ln = (uint32_t)lane_id();
+    WaveSet& set = sets[wave_id()];
+    const uint32_t stride = gridDim.x * WV_W;
+    uint32_t i = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * WV_W + (uint32_t)wave_id()));
+    auto vertex = [&](uint32_t q) -> uint32_t {   // of place q of the ranges
+        if (q >= total) return 0u;
+        uint32_t r = 0;
+#pragma unroll
+        for (int k = 0; k < NBUCKET / WAVE; ++k) r += (uint32_t)__popcll(__ballot(s_pref[k * WAVE + ln] <= q));
+        return a.vlist[s_pos[r - 1u] + (q - s_pref[r - 1u])];
+    };
+    for (uint32_t k = ln; k < WV_OVF; k += WAVE) set.ovf[k] = ~0u;
+    uint64_t acc = 0;
+    uint32_t v = vertex(i), vn = vertex(i + stride);
+    uint32_t b0 = a.off[v], b1 = a.off[v + 1], e0 = a.inoff[v], e1 = a.inoff[v + 1];
+    for (; i < total; i += stride) {
+        // the next vertex's bounds and the one after it, in flight during this one
+        const uint32_t nb0 = a.off[vn], nb1 = a.off[vn + 1], ne0 = a.inoff[vn], ne1 = a.inoff[vn + 1];
+        const uint32_t vnn = vertex(i + 2u * stride);
+        uint64_t ent = e0 + ln < e1 ? a.csc[e0 + ln] : 0ull;
+        uint32_t hits = 0;
+        for (uint32_t b = b0; b < b1;) {   // parts of N+(v)
+            for (uint32_t k = ln; k < WV_SLOTS * 2 / 16; k += WAVE)
+                ((uint4*)set.tag)[k] = make_uint4(0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu);
+            uint32_t over = 0;
+            do {
+                const uint32_t x = b + ln < b1 ? a.col[b + ln] : ~0u;
+                const bool on = x != ~0u;
+                const uint32_t sl = x % WV_SLOTS, tg = x / WV_SLOTS;
+                wave_order();
+                const bool free = on && set.tag[sl] == WV_TAG;
+                wave_order();
+                if (free) set.tag[sl] = (uint16_t)tg;
+                wave_order();
+                const uint32_t now = set.tag[sl];
+                const bool lost = on && !(free && now == tg);   // ranks are distinct: one lane per slot has its tag there
+                wave_order();
+                if (lost) {
+                    set.tag[sl] = (uint16_t)(now | WV_FLAG);
+                    uint32_t h = ovf_slot(x);
+                    while (atomicCAS(&set.ovf[h], ~0u, x) != ~0u) h = (h + 1u) % WV_OVF;
+                }
+                over += (uint32_t)__popcll(__ballot(lost));
+                b += WAVE;
+            } while (b < b1 && over <= WV_OVF / 2);   // a step adds at most 64
+            wave_order();
+            for (uint32_t q = e0;;) {
+                hits += walk_set((const uint4*)a.col, tail_start(ent), tail_end(ent), set);
+                if (e1 - e0 <= (uint32_t)WAVE) break;
+                q += WAVE;
+                if (q >= e1) {
+                    ent = a.csc[e0 + ln];
+                    break;
+                }
+                ent = q + ln < e1 ? a.csc[q + ln] : 0ull;
+            }
+            if (over) {
+                wave_order();
+                for (uint32_t k = ln; k < WV_OVF; k += WAVE) set.ovf[k] = ~0u;
+            }
+            wave_order();
+        }
+        acc += hits;
+        if (MIDDLE) {
+            const uint64_t t = wave_sum_u64(hits);
+            if (ln == 0 && t) a.per_middle[v] += t;   // this wave has all of v
+        }
+        v = vn;
+        vn = vnn;
+        b0 = nb0;
+        b1 = nb1;
+        e0 = ne0;
+        e1 = ne1;
+    }
+    block_partial(acc, partials);
 }
 
 // ------------------------------------------------------------------ shared helpers for edge-centric kernels
@@ -1251,7 +1485,7 @@ void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hip
     const int mode = ker == KER_BITMAP ? bitmap_mode(a) : (a.per_vertex ? BM_VERTEX : BM_COUNT);
     if (grid <= 0) grid = num_cu() * isect_blocks_per_cu(ker, mode);
     const bool hub = ker == KER_BITMAP && a.hub;
-    const int cap = hub ? HB_PARTIAL0 : PARTIALS_PER_KERNEL;
+    const int cap = hub ? WV_PARTIAL0 : PARTIALS_PER_KERNEL;
     if (grid > cap) grid = cap;
     uint64_t* p = partials + (size_t)ker * PARTIALS_PER_KERNEL;
     auto note = [&](uint32_t first, int n) {   // every block of a launch writes its partial
@@ -1270,6 +1504,17 @@ void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hip
             hipLaunchKernelGGL(k_isect_hub<true>, dim3(hg), dim3(HB_NT), 0, s, a, p + HB_PARTIAL0);
         else
             hipLaunchKernelGGL(k_isect_hub<false>, dim3(hg), dim3(HB_NT), 0, s, a, p + HB_PARTIAL0);
+        if (a.waves) {
+            static int wave_cu[2] = {0, 0};
+            const int md = a.per_middle ? 1 : 0;
+            if (!wave_cu[md])
+                wave_cu[md] = resident_blocks(md ? (const void*)k_isect_wave<true> : (const void*)k_isect_wave<false>, WV_NT);
+            int wg = num_cu() * wave_cu[md];
+            if (wg > HB_PARTIAL0 - WV_PARTIAL0) wg = HB_PARTIAL0 - WV_PARTIAL0;
+            note(WV_PARTIAL0, wg);
+            if (md) hipLaunchKernelGGL(k_isect_wave<true>, dim3(wg), dim3(WV_NT), 0, s, a, p + WV_PARTIAL0);
+            else hipLaunchKernelGGL(k_isect_wave<false>, dim3(wg), dim3(WV_NT), 0, s, a, p + WV_PARTIAL0);
+        }
         if (a.groups) {
             const int gg = isect_group_blocks();
             note(HB_PARTIAL1, gg);

@@ -919,6 +919,9 @@ __global__ __launch_bounds__(NT) void k_emit_tiles(const uint32_t* __restrict__ 
 // 20, 1.2e9 tail elements: 2.69 -> 2.66 ms; R-MAT 21, 3e9: 5.52 -> 5.27 ms; Chung-Lu of 40
 // million pairs, 0.5e9: 6.99 ms without, 7.02 ms with it).
 constexpr uint64_t HUB_MIN_TAILS = 1ull << 30;
+// The wave kernel takes the buckets of in-degree class WAVE_LI and below that have no
+// hub tile (its comment has the figures).
+constexpr uint32_t WAVE_LI = 9;
 // In-edges per tile of the group kernel: GRP_TILES tiles per block, within limits (6 and 24 tiles
 // per block: R-MAT 24 43.4 and 43.1 ms against 43.1, R-MAT 20 2433 and 2480 us against 2432).
 constexpr uint32_t GRP_TILES = 12, GRP_EDGES_MIN = 2048, GRP_EDGES_MAX = 16384;
@@ -926,7 +929,7 @@ static_assert(GRP_COUNT % NBUCKET == 0, "whole groups per thread");
 __global__ __launch_bounds__(NBUCKET) void k_hub_ranges(const Ctrl* ctrl, const uint32_t* __restrict__ tstart,
                                                         const uint8_t* __restrict__ vbucket,
                                                         const uint32_t* __restrict__ inoff, uint32_t gfirst,
-                                                        uint32_t group_blocks, HubTab* __restrict__ hub) {
+                                                        uint32_t group_blocks, int waves, HubTab* __restrict__ hub) {
     __shared__ uint32_t s_bucket[NBUCKET];
     __shared__ uint32_t scratch[NBUCKET / WAVE];
     const uint32_t r = threadIdx.x;
@@ -943,12 +946,22 @@ __global__ __launch_bounds__(NBUCKET) void k_hub_ranges(const Ctrl* ctrl, const 
     (void)block_exclusive_scan<NBUCKET>((uint64_t)(nv ? 0.5 * out * out / (double)nv : 0.0), scratch64, &tails);
     const bool use = tails >= HUB_MIN_TAILS;   // the same in every thread
     uint32_t t0 = 0, t1 = 0, h = 0;
+    uint32_t nwv = 0;   // vertices for the wave kernel
     if (nv && ctrl->choice[b] == KER_BITMAP) {
         t0 = tstart[ctrl->bstart[b]];
         t1 = tstart[ctrl->bend[b]];
         if (use && group_blocks && hub->grp[b] != ~0u) t1 = hub->grp[b];
-        h = use && hub->first[b] != ~0u ? hub->first[b] : t1;
+        const bool has = use && hub->first[b] != ~0u;
+        h = has ? hub->first[b] : t1;
+        if (waves && (b >> 4) <= WAVE_LI && !has) {
+            nwv = (uint32_t)nv;
+            h = t1 = t0;
+        }
     }
+    uint32_t nwave;
+    const uint32_t pw = block_exclusive_scan<NBUCKET>(nwv, scratch, &nwave);
+    hub->wave_pos[r] = ctrl->bstart[b];
+    hub->wave_pref[r] = pw;
     uint32_t rest, hubs;
     const uint32_t pr = block_exclusive_scan<NBUCKET>(h - t0, scratch, &rest);
     const uint32_t ph = block_exclusive_scan<NBUCKET>(t1 - h, scratch, &hubs);
@@ -986,7 +999,8 @@ __global__ __launch_bounds__(NBUCKET) void k_hub_ranges(const Ctrl* ctrl, const 
         hub->hub_pref[NBUCKET] = hubs;
         hub->grp_pref[GRP_COUNT] = tiles;
         hub->grp_edges = per;
-        hub->used = hubs + tiles;
+        hub->wave_pref[NBUCKET] = nwave;
+        hub->used = hubs + tiles + nwave;
     }
 }
 
@@ -995,7 +1009,7 @@ __global__ __launch_bounds__(NBUCKET) void k_hub_ranges(const Ctrl* ctrl, const 
 // the capacity by at least the last group's padding: see hub_usable).
 __global__ __launch_bounds__(NT) void k_col16(const uint32_t* __restrict__ col, const Ctrl* ctrl, uint32_t base,
                                               const HubTab* __restrict__ hub, uint16_t* __restrict__ out) {
-    if (hub->used == 0) return;
+    if (hub->hub_pref[NBUCKET] == 0 && hub->grp_pref[GRP_COUNT] == 0) return;
     const uint64_t m = ctrl->m;
     for (uint64_t i = ((uint64_t)blockIdx.x * NT + threadIdx.x) * 8; i < m; i += (uint64_t)gridDim.x * NT * 8) {
         uint32_t x[8];
@@ -1228,7 +1242,7 @@ static IsectArgs isect_args(const RunArgs& r, const Layout& L, uint64_t* csc) {
     ia.clip = r.formulation != FORM_FILTERED ? 1u : 0u;
     ia.col16 = nullptr;
     ia.hub = nullptr;
-    ia.groups = false;
+    ia.groups = ia.waves = false;
     ia.first_rank = 0;
     return ia;
 }
@@ -1277,10 +1291,11 @@ static void prepare_hub(const RunArgs& r, const Layout& L, const uint64_t* csc, 
     char* ws = (char*)r.ws;
     uint16_t* col16 = (uint16_t*)(csc == (const uint64_t*)(ws + L.keysA) ? ws + L.keysB : ws + L.keysA);
     ia.groups = groups_usable(r);
+    ia.waves = (uint32_t)r.n <= WV_RANKS;
     ia.first_rank = ia.groups ? grp_first((uint32_t)r.n) : 0u;
     hipLaunchKernelGGL(k_hub_ranges, dim3(1), dim3(NBUCKET), 0, r.stream, ia.ctrl, (const uint32_t*)(ws + L.tstart),
                        (const uint8_t*)(ws + L.vbucket), ia.inoff, ia.first_rank,
-                       ia.groups ? (uint32_t)isect_group_blocks() : 0u, hub);
+                       ia.groups ? (uint32_t)isect_group_blocks() : 0u, ia.waves ? 1 : 0, hub);
     hipLaunchKernelGGL(k_col16, dim3(grid_for((size_t)r.E / 8 + 1)), dim3(NT), 0, r.stream, ia.col, ia.ctrl,
                        hub_first((uint32_t)r.n), hub, col16);
     ia.col16 = col16;
