@@ -14,12 +14,11 @@
 // a run leaves unchanged, so the in-place writes race with nothing. The block
 // reads its tile once and keeps the low bits in LDS, with the overflow of its
 // last run. By length:
-//   - up to SR_SHORT: the runs starting in one 64-position window, up to the
-//     first longer one, are sorted together by a bitonic network across the wave
-//     (64 or 128 slots, each holding its run's index in the window above its low
-//     bits, which keeps the runs apart);
+//   - up to SR_SHORT: consecutive runs, as many as fit 64 positions, are sorted
+//     together by a bitonic network across the wave (64 slots, each holding its
+//     run's index among them above its low bits, which keeps the runs apart);
 //   - up to SR_MED: one wave, a bitonic network over the low bits held in
-//     registers (the next power of two, up to 32 per lane);
+//     registers (the next power of two, up to 16 per lane);
 //   - up to SR_BLOCK: the whole block, the same network over four waves, whose
 //     cross-wave steps exchange through LDS;
 //   - longer (only input with many repeated pairs has such rows): the whole
@@ -35,10 +34,8 @@ constexpr int SR_NT = 256;
 constexpr int SR_NW = SR_NT / WAVE;
 constexpr uint32_t SR_TILE = 4096;                 // positions per block
 constexpr uint32_t SR_PER = SR_TILE / SR_NT;       // consecutive positions per thread in the scan for starts
-constexpr uint32_t SR_WIN = 64;                    // positions per window of short runs
-constexpr uint32_t SR_NWIN = SR_TILE / SR_WIN;
 constexpr uint32_t SR_SHORT = 64;
-constexpr uint32_t SR_MED = 2048;                  // one wave, at most 32 values per lane
+constexpr uint32_t SR_MED = 1024;                  // one wave, at most 16 values per lane
 constexpr uint32_t SR_BLOCK = 4096;                // the block, 16 values per lane
 constexpr uint32_t SR_MAXMED = SR_TILE / (SR_SHORT + 1) + 1;   // medium runs that can start in one tile
 constexpr uint32_t SR_MAXLONG = SR_TILE / (SR_MED + 1) + 1;   // runs past SR_MED that can start in one tile
@@ -140,6 +137,16 @@ __device__ __forceinline__ void ce(T& a, T& b) {   // ascending compare-exchange
     b = hi;
 }
 
+// The smaller of a and b where c is 0, the larger where it is all ones: v_med3_u32, one
+// instruction where a compare, an xor of the mask and a select took three
+// (what bounds the kernel is the count of these: with it and the batches of 64 positions,
+// R-MAT 24 2.19 -> 1.88 ms, and 1.71 with five blocks per CU for four).
+__device__ __forceinline__ uint32_t pick(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_elementwise_max(__builtin_elementwise_min(a, b),
+                                     __builtin_elementwise_min(__builtin_elementwise_max(a, b), c));
+}
+__device__ __forceinline__ uint64_t pick(uint64_t a, uint64_t b, uint64_t c) { return (a < b) == (c == 0) ? a : b; }
+
 // ---- bitonic sorting networks in registers, all compare-exchanges ascending
 // (each phase k starts with a flip step that pairs e with e ^ (k - 1), then
 // halves with e ^ j, j = k/4 .. 1). A wave holds 64P values, P per lane,
@@ -154,12 +161,12 @@ __device__ __forceinline__ void half_clean(T (&x)[P]) {
                 if ((r & J) == 0) ce(x[r], x[r | J]);
         } else {
             constexpr int M = J / P;
-            const bool lower = (lane_id() & M) == 0;
+            const T upper = (lane_id() & M) ? ~T(0) : T(0);
 #pragma unroll
             for (int r = 0; r < P; ++r) {
                 T a, b;
                 lane_pair<M>(x[r], a, b);
-                x[r] = (a < b) == lower ? a : b;
+                x[r] = pick(a, b, upper);
             }
         }
         half_clean<T, P, J / 2>(x);
@@ -173,12 +180,12 @@ __device__ __forceinline__ void flip(T (&x)[P]) {
         for (int r = 0; r < P; ++r)
             if ((r & (K / 2)) == 0) ce(x[r], x[r ^ (K - 1)]);
     } else {   // partner: lane l ^ (K/P - 1), register P - 1 - r
-        const bool lower = (lane_id() & (K / (2 * P))) == 0;
+        const T upper = (lane_id() & (K / (2 * P))) ? ~T(0) : T(0);
         T y[P];
 #pragma unroll
         for (int r = 0; r < P; ++r) y[r] = lane_mirror<K / P - 1>(x[P - 1 - r]);
 #pragma unroll
-        for (int r = 0; r < P; ++r) x[r] = (x[r] < y[r]) == lower ? x[r] : y[r];
+        for (int r = 0; r < P; ++r) x[r] = pick(x[r], y[r], upper);
     }
 }
 
@@ -202,51 +209,26 @@ __device__ __forceinline__ void sort_wave(T (&x)[P]) {
 // bank conflicts.
 __host__ __device__ constexpr uint32_t sk(uint32_t p) { return p + (p >> 6); }
 
-// The short runs of one window, slots [0, S) = tile positions [sp0, sp0 + S),
-// S <= 127, P slots per lane (1 or 2): each slot's low bits with the index of
-// its run inside the span above them (T = uint32_t when shift <= 25: at most
-// 127 runs, 7 bits), sorted by the network; each position keeps its own high
-// bits.
-template <typename T, int P>
+// Short runs, slots [0, S) = tile positions [sp0, sp0 + S), S <= 64: each
+// slot's low bits with the index of its run among them above (T = uint32_t
+// when shift <= 26: at most 64 runs, 6 bits), sorted by the network; each
+// position keeps its own high bits.
+template <typename T>
 __device__ __forceinline__ uint32_t sort_window(uint64_t* keys, const uint32_t* v, const uint16_t* flag,
                                                 uint32_t sp0, uint32_t S, int sh) {
-    const uint32_t l = (uint32_t)lane_id();
+    const uint32_t l = (uint32_t)lane_id(), p = sp0 + l;
     const int cs = sizeof(T) == 4 ? sh : 32;
     const uint64_t lmask = (1ull << sh) - 1ull;
-    const uint64_t below = lanes_below();
-    uint64_t o[P];
-    T x[P];
-    uint32_t before = 0;   // run starts in this lane's earlier slots
-    bool st[P];
-#pragma unroll
-    for (int r = 0; r < P; ++r) {
-        const uint32_t s = l * P + r, p = sp0 + s;
-        o[r] = s < S ? keys[p] : 0ull;   // the high bits: loads in flight under the network
-        st[r] = s < S && ((flag[p >> 4] >> (p & 15)) & 1u);
-    }
-    uint32_t prior = 0;    // run starts in the slots of the lanes below
-#pragma unroll
-    for (int r = 0; r < P; ++r) prior += (uint32_t)__popcll(__ballot(st[r]) & below);
-#pragma unroll
-    for (int r = 0; r < P; ++r) {
-        const uint32_t s = l * P + r;
-        before += st[r] ? 1u : 0u;
-        const T ri = (T)(prior + before - 1u);   // slot 0 starts a run
-        x[r] = s < S ? (T)((ri << cs) | (T)v[sk(sp0 + s)]) : ~T(0);
-    }
-    sort_wave<T, P>(x);
-    // the slots whose value differs from the slot before (the run index is part
-    // of it), counted across the wave
-    T prev = __shfl_up(x[P - 1], 1, WAVE);
-    uint32_t kept = 0;
-#pragma unroll
-    for (int r = 0; r < P; ++r) {
-        const uint32_t s = l * P + r;
-        if (s < S) keys[sp0 + s] = (o[r] & ~lmask) | ((uint64_t)x[r] & lmask);
-        kept += (uint32_t)__popcll(__ballot(s < S && (s == 0 || x[r] != prev)));
-        prev = x[r];
-    }
-    return kept;
+    const bool on = l < S;
+    const uint64_t o = on ? keys[p] : 0ull;   // the high bits: the load in flight under the network
+    const bool st = on && ((flag[p >> 4] >> (p & 15)) & 1u);
+    const T ri = (T)((uint32_t)__popcll(__ballot(st) & lanes_below()) + (st ? 1u : 0u) - 1u);   // slot 0 starts a run
+    T x[1] = {on ? (T)((ri << cs) | (T)v[sk(p)]) : ~T(0)};
+    sort_wave<T, 1>(x);
+    if (on) keys[p] = (o & ~lmask) | ((uint64_t)x[0] & lmask);
+    // the slots whose value differs from the slot before (the run index is part of it)
+    const T prev = __shfl_up(x[0], 1, WAVE);
+    return (uint32_t)__popcll(__ballot(on && (l == 0 || x[0] != prev)));
 }
 
 // One wave: the run's low bits v[sk(st) ..] (L of them, L <= 64 * P) sorted in
@@ -368,18 +350,18 @@ constexpr uint32_t SR_NFLAG = SR_TILE / 16 + 8;  // run-start bits, 16 positions
 // its skewed index sk(p)
 constexpr uint32_t SR_VMAX = SR_SPAN > SR_BLOCK ? SR_SPAN : SR_BLOCK;
 constexpr uint32_t SR_LDS = sk(SR_VMAX - 1) + 1;
+static_assert(SR_LDS >= SR_NW * 256, "the digit counters of the long runs fit");
 static_assert(sk(SR_SPAN - 1) < SR_LDS && sk(SR_BLOCK - 1) < SR_LDS, "skewed LDS index past the array");
 
-__global__ __launch_bounds__(SR_NT, 4) void k_sort_runs(SortRunsArgs a) {
+__global__ __launch_bounds__(SR_NT, 5) void k_sort_runs(SortRunsArgs a) {
     __shared__ uint32_t s_v[SR_LDS];                   // low bits of the keys, tile-relative position p at sk(p)
     __shared__ uint16_t s_bnd[SR_TILE];                 // run starts in the tile, ascending
     __shared__ uint16_t s_flag[SR_NFLAG];
-    __shared__ uint32_t s_wf[SR_NWIN + 1];              // first run index per window
+    __shared__ uint32_t s_wf[SR_NW + 1];                // first run index per wave's quarter of the tile
     __shared__ uint16_t s_med[SR_MAXMED];
     __shared__ uint32_t s_long[SR_MAXLONG];
     __shared__ uint32_t s_scan[SR_NW];
     __shared__ uint32_t s_nbnd, s_lastend, s_skippos, s_nmed, s_nlong, s_medctr;
-    __shared__ uint32_t s_cnt[SR_NW][256];
     __shared__ uint32_t s_kept[8];                      // kept keys per chunk c0 .. c0 + 7
 
     const uint32_t t0 = (gridDim.x - 1 - blockIdx.x) * SR_TILE;   // the last tiles, whose runs are longest, first
@@ -447,9 +429,9 @@ __global__ __launch_bounds__(SR_NT, 4) void k_sort_runs(SortRunsArgs a) {
         s_flag[threadIdx.x] = (uint16_t)flags;
         uint32_t total;
         uint32_t o = block_exclusive_scan<SR_NT>((uint32_t)__popc(flags), s_scan, &total);
-        if ((threadIdx.x & 3) == 0) s_wf[threadIdx.x >> 2] = o;
+        if (l == 0) s_wf[w] = o;
         if (threadIdx.x == 0) {
-            s_wf[SR_NWIN] = total;
+            s_wf[SR_NW] = total;
             s_nbnd = total;
         }
 #pragma unroll
@@ -499,39 +481,31 @@ __global__ __launch_bounds__(SR_NT, 4) void k_sort_runs(SortRunsArgs a) {
         else s_long[atomicAdd(&s_nlong, 1u)] = i;
     }
     __syncthreads();
-    // ---- short runs, window by window
-    for (uint32_t win = w; win < SR_NWIN; win += SR_NW) {
-        const uint32_t r0 = s_wf[win], r1 = s_wf[win + 1];
-        if (r0 == r1) continue;
-        const uint32_t r = r0 + l;
-        const bool has = r < r1;
-        uint32_t L = 0;
-        bool bad = false;
-        if (has) {
-            const uint32_t st = s_bnd[r];
-            L = run_end(r) - st;
-            bad = L > SR_SHORT || st == skippos;
+    // ---- short runs, as many as fit 64 positions at a time; a wave has those that start in its quarter of the tile
+    for (uint32_t r = s_wf[w], r1 = s_wf[w + 1]; r < r1;) {
+        const uint32_t sp0 = s_bnd[r], i = r + l;
+        const bool has = i < r1;
+        const uint32_t st = has ? s_bnd[i] : 0u, end = has ? run_end(i) : 0u;
+        const bool ok = has && end - st <= SR_SHORT && st != skippos;
+        const uint64_t no = ~__ballot(ok);
+        if (no & 1ull) {   // runs for other phases
+            const uint64_t any = __ballot(ok || !has);
+            r += any ? (uint32_t)__ffsll((unsigned long long)any) - 1u : (uint32_t)WAVE;
+            continue;
         }
-        const uint64_t mb = __ballot(bad);
-        const uint32_t cut = mb ? (uint32_t)__ffsll((unsigned long long)mb) - 1u : r1 - r0;
-        if (cut == 0) continue;
-        const uint32_t sp0 = s_bnd[r0];
-        if (__ballot(has && (uint32_t)l < cut && L >= 2) == 0) {   // single keys only: nothing to sort
+        const uint64_t out = ~__ballot(ok && end - sp0 <= (uint32_t)WAVE);
+        const uint32_t cut = out ? (uint32_t)__ffsll((unsigned long long)out) - 1u : (uint32_t)WAVE;   // at least 1
+        r += cut;
+        if (__ballot((uint32_t)l < cut && end - st >= 2) == 0) {   // single keys only: nothing to sort
             if (a.kept)
                 wave_kept(sp0, cut, cut, [&] {
                     if ((uint32_t)l < cut) add_kept(sp0 + l, 1u);
                 });
             continue;
         }
-        const uint32_t S = run_end(r0 + cut - 1) - sp0;   // at most 127
-        uint32_t kept;
-        if (sh <= 25) {
-            if (S <= 64) kept = sort_window<uint32_t, 1>(keys, s_v, s_flag, sp0, S, sh);
-            else kept = sort_window<uint32_t, 2>(keys, s_v, s_flag, sp0, S, sh);
-        } else {
-            if (S <= 64) kept = sort_window<uint64_t, 1>(keys, s_v, s_flag, sp0, S, sh);
-            else kept = sort_window<uint64_t, 2>(keys, s_v, s_flag, sp0, S, sh);
-        }
+        const uint32_t S = (uint32_t)__builtin_amdgcn_readlane((int)end, (int)cut - 1) - sp0;
+        const uint32_t kept = sh <= 26 ? sort_window<uint32_t>(keys, s_v, s_flag, sp0, S, sh)
+                                       : sort_window<uint64_t>(keys, s_v, s_flag, sp0, S, sh);
         if (a.kept)
             wave_kept(sp0, S, kept, [&] {   // a chunk boundary inside the span: position by position
                 for (uint32_t q = l; q < S; q += WAVE) {
@@ -554,8 +528,7 @@ __global__ __launch_bounds__(SR_NT, 4) void k_sort_runs(SortRunsArgs a) {
             if (L <= 128) wave_sort_run<2>(s_v, st, L);
             else if (L <= 256) wave_sort_run<4>(s_v, st, L);
             else if (L <= 512) wave_sort_run<8>(s_v, st, L);
-            else if (L <= 1024) wave_sort_run<16>(s_v, st, L);
-            else wave_sort_run<32>(s_v, st, L);
+            else wave_sort_run<16>(s_v, st, L);
             __builtin_amdgcn_wave_barrier();
             uint32_t kept = 0;
             for (uint32_t p0 = 0; p0 < L; p0 += WAVE) {
@@ -591,7 +564,8 @@ __global__ __launch_bounds__(SR_NT, 4) void k_sort_runs(SortRunsArgs a) {
             }
             __syncthreads();
         } else {
-            block_sort_run(run, (uint32_t*)(a.tmp + t0 + st), L, a, s_cnt, s_scan);
+            block_sort_run(run, (uint32_t*)(a.tmp + t0 + st), L, a, (uint32_t(*)[256])s_v, s_scan);   // s_v is free
+            __syncthreads();
             if (a.kept)
                 for (uint32_t p = threadIdx.x; p < L; p += SR_NT)
                     if (p == 0 || run[p] != run[p - 1]) add_kept(st + p, 1u);
