@@ -103,8 +103,12 @@ RadixDigit radix_first_digit(int bit_lo, int bit_hi);
 // The first pass's count table inside temp: counts[d * ntiles + tile], 256
 // rows, ntiles = ceil(cap / radix_tile_keys(cap, key bytes)).
 uint32_t* radix_first_counts(void* temp);
-// After a sort of one pass (not a look-back one): the keys per digit, 256 counts.
-const uint32_t* radix_digit_totals(void* temp, size_t cap, int key_bytes);
+// The 2E ids of E pairs (loops and pairs with an invalid id as two sentinels) grouped
+// by the digit dg, in `out` (half: the low 16 bits of each). The count table
+// radix_first_counts(temp) holds the digits per tile of
+// radix_tile_keys(2E, 4) ids. Returns the ids per digit, 256 counts in temp (radix_temp_bytes(2E)).
+const uint32_t* partition_endpoints(const int2* edges, size_t E, int32_t n, uint32_t sentinel, RadixDigit dg, bool half,
+                                    void* out, void* temp, hipStream_t s);
 
 // ---- runsort.hip
 // Keys grouped by key >> shift (ascending; 1 <= shift <= 32) are sorted by the

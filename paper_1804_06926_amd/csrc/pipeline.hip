@@ -102,7 +102,7 @@ __global__ __launch_bounds__(NT) void k_endpoints(const int2* __restrict__ edges
             bad |= !in_range;
             const bool ok = in_range && e.x != e.y;
             const uint32_t a = ok ? (uint32_t)e.x : sentinel, b = ok ? (uint32_t)e.y : sentinel;
-            ((uint2*)keys)[i] = make_uint2(a, b);
+            if (keys) ((uint2*)keys)[i] = make_uint2(a, b);
             sent += ok ? 0u : 2u;
             if (counts) {
                 tc.add((a >> dg.shift) & dg.mask);
@@ -162,8 +162,8 @@ __global__ __launch_bounds__(NT) void k_bucket_sizes(const uint32_t* __restrict_
 // 0.35 -> 0.13 ms, of 148 million 6.15 -> 2.78 ms). Taking a wave's lanes that share
 // an id as one add instead was slower everywhere but in the last. The
 // 2^15-counter histogram leaves room for one block per CU, so that size runs 1024 threads.
-template <int CW, int NTB>
-__global__ __launch_bounds__(NTB) void k_bucket_count(const uint32_t* __restrict__ ep,
+template <typename EP, int CW, int NTB>
+__global__ __launch_bounds__(NTB) void k_bucket_count(const EP* __restrict__ ep,
                                                       const uint32_t* __restrict__ tot, uint32_t len_all, int bw,
                                                       uint32_t parts, uint32_t nb, uint32_t chunk, int32_t n,
                                                       uint32_t* __restrict__ deg) {
@@ -203,18 +203,23 @@ __global__ __launch_bounds__(NTB) void k_bucket_count(const uint32_t* __restrict
     const uint32_t b = s_bucket, s0 = s_start, len = s_size;
     const uint32_t a0 = s0 + (uint32_t)(((uint64_t)len * s_stretch) / s_stretches);
     const uint32_t a1 = s0 + (uint32_t)(((uint64_t)len * (s_stretch + 1u)) / s_stretches);
-    constexpr int U = 8;
-    for (uint32_t i0 = a0; i0 < a1; i0 += NTB * U) {
-        uint32_t x[U];
+    // 16-byte chunks of the stretch, PER ids each, U loads in flight together
+    constexpr uint32_t PER = 16 / sizeof(EP), U = 2;
+    const uint32_t c1 = (a1 + PER - 1u) / PER;
+    for (uint32_t c0 = a0 / PER + threadIdx.x; c0 < c1; c0 += NTB * U) {
+        uint4 x[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) {   // loads in flight together
-            const uint32_t i = i0 + k * NTB + threadIdx.x;
-            x[k] = i < a1 ? ep[i] : 0xFFFFFFFFu;
-        }
+        for (uint32_t k = 0; k < U; ++k) x[k] = ((const uint4*)ep)[c0 + k * NTB < c1 ? c0 + k * NTB : c0];
 #pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const uint32_t loc = x[k] & bmask;
-            if (x[k] != 0xFFFFFFFFu && (loc >> cw) == pt) atomicAdd(&h[loc & hmask], 1u);
+        for (uint32_t k = 0; k < U; ++k) {
+            const uint32_t at = (c0 + k * NTB) * PER;
+            const uint32_t w[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
+#pragma unroll
+            for (uint32_t q = 0; q < PER; ++q) {
+                const uint32_t id = sizeof(EP) == 2 ? (w[q / 2] >> (16 * (q & 1))) & 0xFFFFu : w[q % 4];
+                const uint32_t loc = id & bmask;
+                if (at + q >= a0 && at + q < a1 && (loc >> cw) == pt) atomicAdd(&h[loc & hmask], 1u);
+            }
         }
     }
     __syncthreads();
@@ -230,25 +235,21 @@ __global__ __launch_bounds__(NTB) void k_bucket_count(const uint32_t* __restrict
 // Endpoints per stretch: one and a half times the mean of 256 buckets (or of the buckets, where
 // they are more), so that ordinary buckets are one stretch and few buckets
 // still give enough blocks; at least 8192.
-static void launch_bucket_count(const uint32_t* ep, const uint32_t* tot, int bw, uint32_t nb, uint64_t len,
-                                int32_t n, uint32_t* deg, hipStream_t s) {
+template <typename EP>
+static void launch_bucket_count(const EP* ep, const uint32_t* tot, int bw, uint32_t nb, uint64_t len, int32_t n,
+                                uint32_t* deg, hipStream_t s) {
     const int cw = bw < DEG_MAX_CW ? bw : DEG_MAX_CW;
     const uint32_t parts = 1u << (bw - cw);
     const uint64_t want = 3 * len / (2 * (uint64_t)(nb > 256u ? nb : 256u));
     const uint32_t chunk = (uint32_t)(want > 8192 ? want : 8192);
     const dim3 grid((unsigned)(parts * (nb + len / chunk + 1)));   // at least the stretches
-    if (cw <= 12)
-        hipLaunchKernelGGL((k_bucket_count<12, NT>), grid, dim3(NT), 0, s, ep, tot, (uint32_t)len, bw, parts, nb, chunk, n,
-                           deg);
-    else if (cw == 13)
-        hipLaunchKernelGGL((k_bucket_count<13, NT>), grid, dim3(NT), 0, s, ep, tot, (uint32_t)len, bw, parts, nb, chunk, n,
-                           deg);
-    else if (cw == 14)   // ids past 25 bits: 2^14 counters (64 KB), 1024 threads (8 blocks ran 2 waves per SIMD)
-        hipLaunchKernelGGL((k_bucket_count<14, 1024>), grid, dim3(1024), 0, s, ep, tot, (uint32_t)len, bw, parts, nb, chunk, n,
-                           deg);
-    else
-        hipLaunchKernelGGL((k_bucket_count<DEG_MAX_CW, 1024>), grid, dim3(1024), 0, s, ep, tot, (uint32_t)len, bw, parts, nb,
-                           chunk, n, deg);
+    auto go = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, ep, tot, (uint32_t)len, bw, parts, nb, chunk, n, deg);
+    };
+    if (cw <= 12) go(k_bucket_count<EP, 12, NT>, NT);
+    else if (cw == 13) go(k_bucket_count<EP, 13, NT>, NT);
+    else if (cw == 14) go(k_bucket_count<EP, 14, 1024>, 1024);   // 2^14 counters (64 KB): 8 blocks ran 2 waves per SIMD
+    else go(k_bucket_count<EP, DEG_MAX_CW, 1024>, 1024);
 }
 
 // dend[v] = one past the last occurrence of v among the sorted endpoints.
@@ -1421,6 +1422,9 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         uint32_t* ep = (uint32_t*)keysA;       // 2E uint32 fit in E uint64
         uint32_t* ep_alt = (uint32_t*)keysB;
         // the endpoint sort's first digit is counted by k_endpoints as it writes the keys
+        // one partition pass is enough for most: it then reads the pairs itself and
+        // k_endpoints only counts (with ids of 24 bits and fewer it writes 16-bit ones)
+        const bool direct = bucketed && vbits > bw && vbits - bw <= 8;
         const uint32_t ep_tile = radix_tile_keys((size_t)(2 * E), 4);
         const uint32_t ep_tiles = (uint32_t)(((uint64_t)(2 * E) + ep_tile - 1) / ep_tile);
         const bool ep_sort = !bucketed || vbits > bw;
@@ -1439,10 +1443,17 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         const unsigned eg = p1_tiles < DEG_EP_BLOCKS ? p1_tiles : DEG_EP_BLOCKS;
         if (p2_tot) fill_u32(p2_tot, 0u, 256, s);
         hipLaunchKernelGGL(k_endpoints, dim3(eg), dim3(NT), 0, s, edges, (uint64_t)E, n,
-                           bucketed ? (uint32_t)(n - 1) : (uint32_t)n, ep, ctrl, partial,
+                           bucketed ? (uint32_t)(n - 1) : (uint32_t)n, direct ? nullptr : ep, ctrl, partial,
                            ep_sort ? radix_first_counts(radix_tmp) : nullptr, ep_tiles, ep_tile, ep_dg, p1_counts,
                            p1_f, RadixDigit{vbits - ORIENT_PART_BITS, (1u << ORIENT_PART_BITS) - 1u}, p2_tot, deg);
-        if (bucketed) {
+        if (direct) {
+            const bool half = bw <= 16;
+            const uint32_t* tot = partition_endpoints(edges, (size_t)E, n, (uint32_t)(n - 1), ep_dg, half, ep, radix_tmp, s);
+            const uint32_t nb = 1u << (vbits - bw);
+            if (half) launch_bucket_count((const uint16_t*)ep, tot, bw, nb, (uint64_t)(2 * E), n, deg, s);
+            else launch_bucket_count(ep, tot, bw, nb, (uint64_t)(2 * E), n, deg, s);
+            nsent_blocks = eg;
+        } else if (bucketed) {
             // partition by bits [bw, vbits), then count per bucket
             const uint32_t nb = 1u << (vbits - bw);
             int a0 = 0;
@@ -1455,8 +1466,6 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
                 hipLaunchKernelGGL(k_bucket_sizes, dim3(grid_for((size_t)nb)), dim3(NT), 0, s, a0 ? ep_alt : ep,
                                    (uint32_t)(2 * E), bw, nb, sizes);
                 tot = sizes;
-            } else if (vbits > bw) {
-                tot = radix_digit_totals(radix_tmp, (size_t)(2 * E), 4);
             }
             launch_bucket_count(a0 ? ep_alt : ep, tot, bw, nb, (uint64_t)(2 * E), n, deg, s);
             nsent_blocks = eg;
