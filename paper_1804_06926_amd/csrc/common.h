@@ -83,22 +83,35 @@ __device__ __forceinline__ T block_exclusive_scan(T v, T* scratch, T* total = nu
 // First-pass digit counts of a radix sort, gathered by the kernel that writes
 // the keys: a block of 256 threads writes tile t (the sort's tile of consecutive keys)
 // and adds each key's first digit here; flush() stores the tile's column of
-// the count table (256 digit rows) and clears the counters.
-struct TileCounts {
-    uint32_t w[4][256];   // one histogram per wave (256 threads)
+// the count table (D digit rows) and clears the counters.
+template <int D>
+struct TileCountsT {
+    uint32_t w[4][D];   // one histogram per wave (256 threads)
     __device__ void clear() {
-        for (int i = threadIdx.x; i < 4 * 256; i += 256) (&w[0][0])[i] = 0;
+        for (int i = threadIdx.x; i < 4 * D; i += 256) (&w[0][0])[i] = 0;
     }
     __device__ void add(uint32_t digit) { atomicAdd(&w[threadIdx.x >> 6][digit], 1u); }
+    // The same, one add for the wave's active lanes when they share the digit (adds to
+    // one counter take a turn each; pairs of a batch come graph by graph, in ranges of
+    // ids: 1.86 -> 1.42 ms for the endpoint counts of 75 million).
+    __device__ void add_shared(uint32_t digit) {
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)digit);
+        const uint64_t on = __ballot(true), same = __ballot(digit == d0);
+        if (on != same) atomicAdd(&w[threadIdx.x >> 6][digit], 1u);
+        else if ((on & lanes_below()) == 0) atomicAdd(&w[threadIdx.x >> 6][d0], (uint32_t)__popcll(on));
+    }
+    __device__ uint32_t sum(uint32_t d) const { return w[0][d] + w[1][d] + w[2][d] + w[3][d]; }
     // Whole block; barriers.
     __device__ void flush(uint32_t* counts, uint32_t ntiles, uint32_t tile) {
         __syncthreads();
-        const uint32_t d = threadIdx.x;
-        counts[(size_t)d * ntiles + tile] = w[0][d] + w[1][d] + w[2][d] + w[3][d];
-        w[0][d] = w[1][d] = w[2][d] = w[3][d] = 0;
+        for (uint32_t d = threadIdx.x; d < (uint32_t)D; d += 256) {
+            counts[(size_t)d * ntiles + tile] = sum(d);
+            w[0][d] = w[1][d] = w[2][d] = w[3][d] = 0;
+        }
         __syncthreads();
     }
 };
+using TileCounts = TileCountsT<256>;
 
 // Ceiling of log2 for x >= 1 (number of bits needed to hold values < x).
 __host__ __device__ __forceinline__ int bits_for(uint64_t x) {

@@ -104,11 +104,13 @@ RadixDigit radix_first_digit(int bit_lo, int bit_hi);
 // rows, ntiles = ceil(cap / radix_tile_keys(cap, key bytes)).
 uint32_t* radix_first_counts(void* temp);
 // The 2E ids of E pairs (loops and pairs with an invalid id as two sentinels) grouped
-// by the digit dg, in `out` (half: the low 16 bits of each). The count table
-// radix_first_counts(temp) holds the digits per tile of
-// radix_tile_keys(2E, 4) ids. Returns the ids per digit, 256 counts in temp (radix_temp_bytes(2E)).
-const uint32_t* partition_endpoints(const int2* edges, size_t E, int32_t n, uint32_t sentinel, RadixDigit dg, bool half,
-                                    void* out, void* temp, hipStream_t s);
+// by the digit dg (shift at most 16), the low 16 bits of each in `out`. The count table
+// radix_first_counts(temp) holds the digits (256 or 512 rows)
+// per tile of endpoint_tile(2E, digits) ids. Returns the ids per digit, in temp
+// (radix_temp_bytes(max(2E, n))).
+uint32_t endpoint_tile(size_t ids, uint32_t digits);
+const uint32_t* partition_endpoints(const int2* edges, size_t E, int32_t n, uint32_t sentinel, RadixDigit dg, uint16_t* out,
+                                    void* temp, hipStream_t s);
 
 // ---- runsort.hip
 // Keys grouped by key >> shift (ascending; 1 <= shift <= 32) are sorted by the

@@ -58,6 +58,7 @@ constexpr int DEG_MAX_CW = 15;        // LDS histogram of at most 2^15 counters 
 constexpr int DEG_MAX_BUCKET_BITS = 13;   // up to 8192 buckets (ids below 2^27)
 constexpr unsigned DEG_EP_BLOCKS = 1024;
 
+template <int D>
 __global__ __launch_bounds__(NT) void k_endpoints(const int2* __restrict__ edges, uint64_t E, int32_t n,
                                                   uint32_t sentinel, uint32_t* __restrict__ keys, Ctrl* ctrl,
                                                   uint32_t* __restrict__ nsent, uint32_t* __restrict__ counts,
@@ -76,7 +77,8 @@ __global__ __launch_bounds__(NT) void k_endpoints(const int2* __restrict__ edges
     const uint32_t EPT = tile_keys / 2;
     const uint32_t pntiles = (ntiles + pf - 1) / pf;
     __shared__ uint32_t red[NT / WAVE];
-    __shared__ TileCounts tc, tp, tq;
+    __shared__ TileCountsT<D> tc;
+    __shared__ TileCounts tp, tq;
     tc.clear();
     if (pcounts) tp.clear();
     if (p2tot) tq.clear();
@@ -105,11 +107,11 @@ __global__ __launch_bounds__(NT) void k_endpoints(const int2* __restrict__ edges
             if (keys) ((uint2*)keys)[i] = make_uint2(a, b);
             sent += ok ? 0u : 2u;
             if (counts) {
-                tc.add((a >> dg.shift) & dg.mask);
-                tc.add((b >> dg.shift) & dg.mask);
+                tc.add_shared((a >> dg.shift) & dg.mask);
+                tc.add_shared((b >> dg.shift) & dg.mask);
             }
-            if (pcounts) tp.add(((uint32_t)e.x >> pdg.shift) & pdg.mask);
-            if (p2tot) tq.add(((uint32_t)e.y >> pdg.shift) & pdg.mask);
+            if (pcounts) tp.add_shared(((uint32_t)e.x >> pdg.shift) & pdg.mask);
+            if (p2tot) tq.add_shared(((uint32_t)e.y >> pdg.shift) & pdg.mask);
         }
       }
         if (counts) tc.flush(counts, ntiles, tile);
@@ -118,7 +120,7 @@ __global__ __launch_bounds__(NT) void k_endpoints(const int2* __restrict__ edges
     }
     if (p2tot) {
         __syncthreads();
-        const uint32_t t = tq.w[0][threadIdx.x] + tq.w[1][threadIdx.x] + tq.w[2][threadIdx.x] + tq.w[3][threadIdx.x];
+        const uint32_t t = tq.sum(threadIdx.x);
         if (t) atomicAdd(&p2tot[threadIdx.x], t);
     }
     if (__ballot(bad) && lane_id() == 0) atomicOr(&ctrl->err, 1u);
@@ -1415,7 +1417,7 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
     // then looks back instead of running a histogram pass
     uint32_t* p2_tot =
         orient_part && radix_tile_keys((size_t)E, 8) == 8192u ? (uint32_t*)(ws + L.lb_aux) : nullptr;
-    const int bw = vbits <= 20 ? (vbits < 12 ? vbits : 12) : (vbits <= 25 ? vbits - 8 : DEG_MAX_BW);
+    const int bw = vbits <= 20 ? (vbits < 12 ? vbits : 12) : (vbits <= 24 ? vbits - 8 : (vbits == 25 ? 16 : DEG_MAX_BW));
     const bool bucketed = vbits - bw <= DEG_MAX_BUCKET_BITS;
     uint32_t nsent_blocks = 0;   // blocks of k_endpoints that recorded sentinel endpoints
     {
@@ -1423,12 +1425,15 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         uint32_t* ep_alt = (uint32_t*)keysB;
         // the endpoint sort's first digit is counted by k_endpoints as it writes the keys
         // one partition pass is enough for most: it then reads the pairs itself and
-        // k_endpoints only counts (with ids of 24 bits and fewer it writes 16-bit ones)
-        const bool direct = bucketed && vbits > bw && vbits - bw <= 8;
-        const uint32_t ep_tile = radix_tile_keys((size_t)(2 * E), 4);
+        // k_endpoints only counts. Ids of 25 bits take 512 groups, so that the low half of an id
+        // is enough there too (degree stage with 256 groups and whole ids against it: Chung-Lu of
+        // 148 million pairs 2.37 and 1.93 ms, R-MAT of 160 million 2.19 and 1.84)
+        const bool direct = bucketed && vbits > bw && vbits - bw <= 9;
+        const uint32_t ep_digits = 1u << (vbits - bw);
+        const uint32_t ep_tile = direct ? endpoint_tile((size_t)(2 * E), ep_digits) : radix_tile_keys((size_t)(2 * E), 4);
         const uint32_t ep_tiles = (uint32_t)(((uint64_t)(2 * E) + ep_tile - 1) / ep_tile);
         const bool ep_sort = !bucketed || vbits > bw;
-        const RadixDigit ep_dg = bucketed ? radix_first_digit(bw, vbits) : radix_first_digit(0, bits_for((uint64_t)n + 1));
+        const RadixDigit ep_dg = direct ? RadixDigit{bw, ep_digits - 1u} : bucketed ? radix_first_digit(bw, vbits) : radix_first_digit(0, bits_for((uint64_t)n + 1));
         // past 2^21 vertices the orientation's first partition pass (pairs by the high bits
         // of the first id) takes its digit counts from here too, kept in the column array
         // until then; its tiles hold one or two endpoint tiles' pairs
@@ -1442,16 +1447,15 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         const uint32_t p1_tiles = (ep_tiles + p1_f - 1) / p1_f;
         const unsigned eg = p1_tiles < DEG_EP_BLOCKS ? p1_tiles : DEG_EP_BLOCKS;
         if (p2_tot) fill_u32(p2_tot, 0u, 256, s);
-        hipLaunchKernelGGL(k_endpoints, dim3(eg), dim3(NT), 0, s, edges, (uint64_t)E, n,
+        hipLaunchKernelGGL((direct && ep_digits > 256u ? k_endpoints<512> : k_endpoints<256>), dim3(eg), dim3(NT), 0, s,
+                           edges, (uint64_t)E, n,
                            bucketed ? (uint32_t)(n - 1) : (uint32_t)n, direct ? nullptr : ep, ctrl, partial,
                            ep_sort ? radix_first_counts(radix_tmp) : nullptr, ep_tiles, ep_tile, ep_dg, p1_counts,
                            p1_f, RadixDigit{vbits - ORIENT_PART_BITS, (1u << ORIENT_PART_BITS) - 1u}, p2_tot, deg);
         if (direct) {
-            const bool half = bw <= 16;
-            const uint32_t* tot = partition_endpoints(edges, (size_t)E, n, (uint32_t)(n - 1), ep_dg, half, ep, radix_tmp, s);
-            const uint32_t nb = 1u << (vbits - bw);
-            if (half) launch_bucket_count((const uint16_t*)ep, tot, bw, nb, (uint64_t)(2 * E), n, deg, s);
-            else launch_bucket_count(ep, tot, bw, nb, (uint64_t)(2 * E), n, deg, s);
+            const uint32_t* tot = partition_endpoints(edges, (size_t)E, n, (uint32_t)(n - 1), ep_dg, (uint16_t*)ep,
+                                                      radix_tmp, s);
+            launch_bucket_count((const uint16_t*)ep, tot, bw, ep_digits, (uint64_t)(2 * E), n, deg, s);
             nsent_blocks = eg;
         } else if (bucketed) {
             // partition by bits [bw, vbits), then count per bucket

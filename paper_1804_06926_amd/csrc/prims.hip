@@ -765,29 +765,29 @@ uint32_t* radix_err_word(void* temp, size_t cap) {
 
 // ---- endpoint partition: the 2E ids of E pairs grouped by the bits [shift, shift + bits),
 // straight from the pairs (a loop or an invalid pair counts as two sentinels),
-// from the per-tile counts that a kernel reading the pairs has taken. With OUT
-// 16 bits wide an id's low half is written: its group says the rest. Bound by traffic
+// from the per-tile counts that a kernel reading the pairs has taken. The low
+// half of an id is written: its group says the rest (shift <= 16). Bound by traffic
 // and the LDS adds. Against a kernel that writes the ids, a radix pass over them and
 // 32-bit ids for the count after it (degree stage): R-MAT 24 3.72 -> 2.58 ms, R-MAT 20
 // 0.27 -> 0.18 ms, Chung-Lu of 148 million pairs (25-bit ids, 32 bits each) 2.75 -> 2.38 ms.
 // Tiles of 16384 ids: 2.71, 0.18, 2.45 ms.
 constexpr int EP_NT = 512, EP_NW = EP_NT / WAVE;
-template <typename OUT, int PAIRS>
+template <int PAIRS, int DIG>
 __global__ __launch_bounds__(EP_NT) void k_endpoint_scatter(const int2* __restrict__ edges, uint32_t E, int32_t n,
                                                             uint32_t sentinel, int shift, uint32_t dmask,
                                                             const uint32_t* __restrict__ offs, uint32_t ntiles,
                                                             const uint32_t* __restrict__ digit_tot,
-                                                            OUT* __restrict__ out) {
+                                                            uint16_t* __restrict__ out) {
     constexpr uint32_t TILE = 2u * PAIRS * EP_NT;
-    __shared__ uint32_t wcnt[EP_NW][256];
-    __shared__ uint32_t gofs[256];
+    __shared__ uint32_t wcnt[EP_NW][DIG];
+    __shared__ uint32_t gofs[DIG];
     __shared__ uint32_t scratch[EP_NW];
     __shared__ uint32_t skey[TILE];
-    for (int i = threadIdx.x; i < EP_NW * 256; i += EP_NT) (&wcnt[0][0])[i] = 0;
+    for (int i = threadIdx.x; i < EP_NW * DIG; i += EP_NT) (&wcnt[0][0])[i] = 0;
     __syncthreads();
     const int w = wave_id();
     const uint32_t p0 = blockIdx.x * (PAIRS * EP_NT) + threadIdx.x;
-    uint32_t k[2 * PAIRS], loc[2 * PAIRS];   // digit | (rank within (wave, digit)) << 8
+    uint32_t k[2 * PAIRS], loc[2 * PAIRS];   // digit | (rank within (wave, digit)) << 16
     {
         int2 e[PAIRS];
 #pragma unroll
@@ -803,12 +803,21 @@ __global__ __launch_bounds__(EP_NT) void k_endpoint_scatter(const int2* __restri
     for (int q = 0; q < 2 * PAIRS; ++q) {
         const bool valid = p0 + (q / 2) * EP_NT < E;
         const uint32_t d = (k[q] >> shift) & dmask;
-        const uint32_t r = atomicAdd(&wcnt[w][valid ? d : 0u], valid ? 1u : 0u);
-        loc[q] = d | (r << 8);
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+        uint32_t r;
+        if (__ballot(!valid || d != d0) == 0) {   // one add for a wave of one digit
+            uint32_t at = 0;
+            if (lane_id() == 0) at = atomicAdd(&wcnt[w][d0], (uint32_t)WAVE);
+            r = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)lane_id();
+        } else {
+            r = atomicAdd(&wcnt[w][valid ? d : 0u], valid ? 1u : 0u);
+        }
+        loc[q] = d | (r << 16);
     }
     __syncthreads();
     {   // wcnt[q][d]: the tile position of wave q's first key of digit d; gofs as in k_radix_scatter
-        const bool own = threadIdx.x < 256;
+        static_assert(DIG <= EP_NT, "a thread per digit");
+        const bool own = threadIdx.x < DIG;
         const int d = own ? (int)threadIdx.x : 0;
         uint32_t run = 0;
         if (own) {
@@ -831,10 +840,10 @@ __global__ __launch_bounds__(EP_NT) void k_endpoint_scatter(const int2* __restri
     {
         uint32_t pb[2 * PAIRS];
 #pragma unroll
-        for (int q = 0; q < 2 * PAIRS; ++q) pb[q] = wcnt[w][loc[q] & 255u];
+        for (int q = 0; q < 2 * PAIRS; ++q) pb[q] = wcnt[w][loc[q] & 0xFFFFu];
 #pragma unroll
         for (int q = 0; q < 2 * PAIRS; ++q)
-            if (p0 + (q / 2) * EP_NT < E) skey[pb[q] + (loc[q] >> 8)] = k[q];
+            if (p0 + (q / 2) * EP_NT < E) skey[pb[q] + (loc[q] >> 16)] = k[q];
     }
     __syncthreads();
     const uint32_t left = 2u * E - blockIdx.x * TILE, cnt = left < TILE ? left : TILE;
@@ -843,33 +852,33 @@ __global__ __launch_bounds__(EP_NT) void k_endpoint_scatter(const int2* __restri
         const uint32_t i = i0 + threadIdx.x;
         if (i < cnt) {
             const uint32_t x = skey[i];
-            out[gofs[(x >> shift) & dmask] + i] = (OUT)x;
+            out[gofs[(x >> shift) & dmask] + i] = (uint16_t)x;
         }
     }
 }
 
-template <typename OUT, int PAIRS>
-static void endpoint_scatter(const int2* edges, uint32_t E, int32_t n, uint32_t sentinel, RadixDigit dg,
-                             uint32_t ntiles, const uint32_t* offs, const uint32_t* tot, void* out, hipStream_t s) {
-    hipLaunchKernelGGL((k_endpoint_scatter<OUT, PAIRS>), dim3(ntiles), dim3(EP_NT), 0, s, edges, E, n, sentinel,
-                       dg.shift, dg.mask, offs, ntiles, tot, (OUT*)out);
+uint32_t endpoint_tile(size_t ids, uint32_t digits) {
+    const uint32_t t = radix_tile_keys(ids, 4);
+    return digits > 256 && ids >= (size_t)1 << 23 ? 8192u : t;   // twice the rows: the table keeps its room
 }
 
-const uint32_t* partition_endpoints(const int2* edges, size_t E, int32_t n, uint32_t sentinel, RadixDigit dg, bool half,
-                                    void* out, void* temp, hipStream_t s) {
-    const uint32_t tile = radix_tile_keys(2 * E, 4);
+const uint32_t* partition_endpoints(const int2* edges, size_t E, int32_t n, uint32_t sentinel, RadixDigit dg, uint16_t* out,
+                                    void* temp, hipStream_t s) {
+    const uint32_t digits = dg.mask < 256 ? 256 : 512, tile = endpoint_tile(2 * E, dg.mask + 1);
     const uint32_t ntiles = (uint32_t)((2 * E + tile - 1) / tile);
     uint32_t* hist = (uint32_t*)temp;
-    uint32_t* tot = (uint32_t*)((char*)temp + align_up(sizeof(uint32_t) * 256 * (ntiles + 1), 256));
+    uint32_t* tot = (uint32_t*)((char*)temp + align_up(sizeof(uint32_t) * digits * (ntiles + 1), 256));
     uint32_t* seg_tot = (uint32_t*)((char*)tot + align_up(scan_temp_bytes(), 256));
+    static_assert(sizeof(uint32_t) * 512 <= 4096, "the totals fit the scan's room");
     const uint32_t nseg = (uint32_t)rs_nseg(ntiles);
-    hipLaunchKernelGGL(k_radix_rowscan, dim3(256, nseg), dim3(RS_NT), 0, s, hist, ntiles, tot, seg_tot);
+    hipLaunchKernelGGL(k_radix_rowscan, dim3(digits, nseg), dim3(RS_NT), 0, s, hist, ntiles, tot, seg_tot);
     if (nseg > 1)
-        hipLaunchKernelGGL(k_radix_rowfix, dim3(256, nseg), dim3(RS_NT), 0, s, hist, ntiles, seg_tot, tot);
+        hipLaunchKernelGGL(k_radix_rowfix, dim3(digits, nseg), dim3(RS_NT), 0, s, hist, ntiles, seg_tot, tot);
     auto go = [&](auto pairs) {
         constexpr int P = decltype(pairs)::value;
-        if (half) endpoint_scatter<uint16_t, P>(edges, (uint32_t)E, n, sentinel, dg, ntiles, hist, tot, out, s);
-        else endpoint_scatter<uint32_t, P>(edges, (uint32_t)E, n, sentinel, dg, ntiles, hist, tot, out, s);
+        hipLaunchKernelGGL((digits == 512 ? k_endpoint_scatter<P, 512> : k_endpoint_scatter<P, 256>), dim3(ntiles),
+                           dim3(EP_NT), 0, s, edges, (uint32_t)E, n, sentinel, dg.shift, dg.mask, hist, ntiles, tot,
+                           out);
     };
     if (tile == 8192u) go(std::integral_constant<int, 8>());
     else if (tile == 4096u) go(std::integral_constant<int, 4>());

@@ -16,8 +16,9 @@ SIZES = [(4097, 1), (4097, 16384), (65537, 1023), (65537, 2_097_151), (1 << 20, 
          (1 << 24, 1025), ((1 << 24) + 1, 2049), (1 << 24, 16_777_217), (1 << 25, 4097)]
 
 
-@pytest.mark.parametrize("n,pairs", SIZES)
-def test_ranks(tc, n, pairs):
+@pytest.mark.parametrize("order", ["random", "sorted"])
+@pytest.mark.parametrize("n,pairs", SIZES + [((1 << 24) + 1, 4_194_305)])
+def test_ranks(tc, n, pairs, order):
     import torch
     g = torch.Generator(device="cuda")
     g.manual_seed(n + pairs)
@@ -25,6 +26,9 @@ def test_ranks(tc, n, pairs):
     r = torch.rand(pairs, generator=g, device="cuda")
     e[r < 0.2, 0] = n - 1       # the vertex that takes the loops' endpoints until they are subtracted
     e[r > 0.9, 1] = e[r > 0.9, 0]
+    if order == "sorted":   # whole waves of one digit
+        e = e[torch.argsort(e[:, 0])].contiguous()
+        e[:, 1] = torch.minimum(e[:, 0] + 1 + e[:, 1] % 97, torch.tensor(n - 1, device="cuda", dtype=torch.int32))
     deg = torch.bincount(e[e[:, 0] != e[:, 1]].flatten().long(), minlength=n)
     want = torch.empty(n, dtype=torch.int64, device="cuda")
     want[torch.argsort(deg, stable=True)] = torch.arange(n, device="cuda")
