@@ -1180,6 +1180,14 @@ __global__ __launch_bounds__(WV_NT, 6) void k_isect_wave(IsectArgs a, uint64_t* 
 }
 
 // ------------------------------------------------------------------ shared helpers for edge-centric kernels
+// Outputs of a launch: none that is written per triangle (T, per edge, per middle
+// vertex); any; t[v] through LDS counters.
+enum { EM_COUNT = 0, EM_ANY = 1, EM_VERTEX = 2 };
+// A tail of up to this many times N+(v) is searched in N+(v), which is mostly in
+// LDS; where every in-edge took the shorter of its two lists, a wave ran both searches
+// one after the other (1, 2, 4, 8: random geometric graph of 2^23 vertices 16.1, 14.7, 14.6,
+// 14.6 ms; R-MAT 24 36.0, 35.7, 35.6, 35.6; a batch 19.9, 19.5, 19.5, 19.5).
+constexpr uint32_t SEARCH_LONGER = 4;
 // Number of elements of A taken in the first d outputs of the merge of A and
 // B, A first on ties (merge-path split, Green et al. / Odeh et al.).
 __device__ __forceinline__ uint32_t merge_split(const uint32_t* A, uint32_t na, const uint32_t* B, uint32_t nb,
@@ -1207,9 +1215,12 @@ __device__ __forceinline__ uint32_t find_seg(const Segs& S, uint32_t nseg, uint3
 
 // Elements X[q] (q = gl, gl + g, ...) of one list searched in the ascending
 // list Y (ny > 0) by a group of g lanes: four elements per lane at a time, as
-// four interleaved branch-free lower bounds (halving the range each step),
-// so that every step issues four independent loads. Returns the matches; a
-// match at X[q] = Y[p] is edge ex0 + q and edge ey0 + p.
+// four interleaved branch-free searches for the last element not above (halving the range
+// each step), so that every step issues four independent loads. Returns the matches; a
+// match at X[q] = Y[p] is edge ex0 + q and edge ey0 + p. Bound by its instructions:
+// without the outputs' branches, with one read after the search instead of two, the geometric
+// graph's call went from 16.9 to 16.1 ms.
+template <int MODE>
 __device__ __forceinline__ uint32_t search_list(const IsectArgs& a, const Hot& hot, const uint32_t* X, uint32_t nx,
                                                 const uint32_t* Y, uint32_t ny, uint32_t g, uint32_t gl,
                                                 uint32_t ex0, uint32_t ey0, uint32_t ein) {
@@ -1229,24 +1240,21 @@ __device__ __forceinline__ uint32_t search_list(const IsectArgs& a, const Hot& h
 #pragma unroll
             for (int u = 0; u < 4; ++u) yv[u] = Y[bs[u] + half];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) bs[u] = yv[u] < xv[u] ? bs[u] + half : bs[u];
+            for (int u = 0; u < 4; ++u) bs[u] = yv[u] <= xv[u] ? bs[u] + half : bs[u];
             len -= half;
         }
-        // bs = last position below x (or 0): the lower bound is bs or bs + 1
-        uint32_t y0[4], y1[4], lb[4];
+        uint32_t y0[4];   // bs = last position not above x, or 0
 #pragma unroll
         for (int u = 0; u < 4; ++u) y0[u] = Y[bs[u]];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            lb[u] = bs[u] + (y0[u] < xv[u] ? 1u : 0u);
-            y1[u] = Y[lb[u] < ny ? lb[u] : ny - 1u];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
             const uint32_t q = q0 + (uint32_t)u * g;
-            if (q < nx && lb[u] < ny && y1[u] == xv[u]) {
+            const bool is = q < nx && y0[u] == xv[u];
+            if (MODE == EM_COUNT) {
+                c += is ? 1u : 0u;
+            } else if (is) {
                 ++c;
-                hit(a, hot, xv[u], ex0 + q, ey0 + lb[u], ein);
+                hit(a, hot, xv[u], ex0 + q, ey0 + bs[u], ein);
             }
         }
     }
@@ -1256,7 +1264,7 @@ __device__ __forceinline__ uint32_t search_list(const IsectArgs& a, const Hot& h
 // One in-edge by a group of g lanes: merge path (MERGE) or binary search.
 // ea0, eb0: CSR positions of A[0] (the tail) and B[0] (N+(v)); the in-edge
 // itself sits just before its tail, at ea0 - 1.
-template <bool MERGE>
+template <bool MERGE, int MODE>
 __device__ __forceinline__ uint32_t isect_edge(const IsectArgs& a, const Hot& hot, const uint32_t* A, uint32_t na, const uint32_t* B,
                                                uint32_t nb, uint32_t g, uint32_t gl, uint32_t ea0, uint32_t eb0) {
     uint32_t c = 0;
@@ -1283,20 +1291,22 @@ __device__ __forceinline__ uint32_t isect_edge(const IsectArgs& a, const Hot& ho
                 while (j < nb && B[j] < av[u]) ++j;
                 if (j < nb && B[j] == av[u]) {
                     ++c;
-                    hit(a, hot, av[u], ea0 + i + u, eb0 + j, ea0 - 1u);
+                    if (MODE != EM_COUNT) hit(a, hot, av[u], ea0 + i + u, eb0 + j, ea0 - 1u);
                 }
             }
         }
-    } else if (na <= nb) {
-        c = search_list(a, hot, A, na, B, nb, g, gl, ea0, eb0, ea0 - 1u);   // tail elements searched in N+(v)
+    } else if (na <= SEARCH_LONGER * nb) {
+        c = search_list<MODE>(a, hot, A, na, B, nb, g, gl, ea0, eb0, ea0 - 1u);   // tail elements searched in N+(v)
     } else {
-        c = search_list(a, hot, B, nb, A, na, g, gl, eb0, ea0, ea0 - 1u);   // N+(v) searched in the tail
+        c = search_list<MODE>(a, hot, B, nb, A, na, g, gl, eb0, ea0, ea0 - 1u);   // N+(v) searched in the tail
     }
     return c;
 }
 
-template <bool MERGE, bool VERTEX>
-__global__ __launch_bounds__(IS_NT, VERTEX ? 4 : (MERGE ? 7 : 6)) void k_isect_edges(IsectArgs a, uint64_t* partials) {
+template <bool MERGE, int MODE>
+__global__ __launch_bounds__(IS_NT, MODE == EM_VERTEX ? 4 : (MERGE ? 7 : 6)) void k_isect_edges(IsectArgs a,
+                                                                                              uint64_t* partials) {
+    constexpr bool VERTEX = MODE == EM_VERTEX;
     __shared__ uint32_t s_hot[VERTEX ? HOT_N : 1];
     const Hot hot = {VERTEX ? s_hot : nullptr, a.hot_first};
     if (VERTEX) hot.clear();   // the first tile's barriers follow
@@ -1361,14 +1371,14 @@ __global__ __launch_bounds__(IS_NT, VERTEX ? 4 : (MERGE ? 7 : 6)) void k_isect_e
                 const uint32_t nb = s_boff[sg + 1] - s_boff[sg];
                 const uint32_t bo = a.off[v];
                 // two call sites, so that each knows whether N+(v) is in LDS or in global memory
-                if (staged) c = isect_edge<MERGE>(a, hot, a.col + s, end - s, sb + s_boff[sg], nb, g, gl, s, bo);
-                else c = isect_edge<MERGE>(a, hot, a.col + s, end - s, a.col + bo, nb, g, gl, s, bo);
+                if (staged) c = isect_edge<MERGE, MODE>(a, hot, a.col + s, end - s, sb + s_boff[sg], nb, g, gl, s, bo);
+                else c = isect_edge<MERGE, MODE>(a, hot, a.col + s, end - s, a.col + bo, nb, g, gl, s, bo);
             }
             // reduce within the group of g lanes (g divides the wave)
             for (uint32_t o = g >> 1; o > 0; o >>= 1) c += __shfl_xor(c, (int)o, WAVE);
             if (q < ne && gl == 0) {
                 acc += c;
-                edge_done(a, hot, e, v, c);
+                if (MODE != EM_COUNT || a.per_edge || a.per_middle) edge_done(a, hot, e, v, c);
             }
         }
         __syncthreads();
@@ -1459,9 +1469,9 @@ int isect_blocks_per_cu(int ker, int mode) {
     int& c = cache[ker][mode];
     if (!c) {
         const bool vertex = mode == BM_VERTEX;
-        const void* fn = ker == KER_MERGE ? (const void*)k_isect_edges<true, false>
-                         : ker == KER_BSEARCH ? (vertex ? (const void*)k_isect_edges<false, true>
-                                                        : (const void*)k_isect_edges<false, false>)
+        const void* fn = ker == KER_MERGE ? (const void*)k_isect_edges<true, EM_ANY>
+                         : ker == KER_BSEARCH ? (vertex ? (const void*)k_isect_edges<false, EM_VERTEX>
+                                                        : (const void*)k_isect_edges<false, EM_ANY>)
                                               : bitmap_fn(mode, true);
         c = resident_blocks(fn);
     }
@@ -1488,6 +1498,7 @@ void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hip
     const int cap = hub ? WV_PARTIAL0 : PARTIALS_PER_KERNEL;
     if (grid > cap) grid = cap;
     uint64_t* p = partials + (size_t)ker * PARTIALS_PER_KERNEL;
+    const bool plain = !a.support && !a.per_vertex && !a.list_out;
     auto note = [&](uint32_t first, int n) {   // every block of a launch writes its partial
         if (!parts) return;
         parts->first[parts->launches] = (uint32_t)(p - partials) + first;
@@ -1523,11 +1534,13 @@ void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hip
     }
     switch (ker) {
         case KER_MERGE:
-            hipLaunchKernelGGL((k_isect_edges<true, false>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            if (plain) hipLaunchKernelGGL((k_isect_edges<true, EM_COUNT>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            else hipLaunchKernelGGL((k_isect_edges<true, EM_ANY>), dim3(grid), dim3(IS_NT), 0, s, a, p);
             break;
         case KER_BSEARCH:
-            if (a.per_vertex) hipLaunchKernelGGL((k_isect_edges<false, true>), dim3(grid), dim3(IS_NT), 0, s, a, p);
-            else hipLaunchKernelGGL((k_isect_edges<false, false>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            if (plain) hipLaunchKernelGGL((k_isect_edges<false, EM_COUNT>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            else if (a.per_vertex) hipLaunchKernelGGL((k_isect_edges<false, EM_VERTEX>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            else hipLaunchKernelGGL((k_isect_edges<false, EM_ANY>), dim3(grid), dim3(IS_NT), 0, s, a, p);
             break;
         default: {
             const bool nw = a.col_narrow != 0;
