@@ -101,12 +101,13 @@ struct TileCountsT {
         else if ((on & lanes_below()) == 0) atomicAdd(&w[threadIdx.x >> 6][d0], (uint32_t)__popcll(on));
     }
     __device__ uint32_t sum(uint32_t d) const { return w[0][d] + w[1][d] + w[2][d] + w[3][d]; }
+    __device__ void reset(uint32_t d) { w[0][d] = w[1][d] = w[2][d] = w[3][d] = 0; }
     // Whole block; barriers.
     __device__ void flush(uint32_t* counts, uint32_t ntiles, uint32_t tile) {
         __syncthreads();
         for (uint32_t d = threadIdx.x; d < (uint32_t)D; d += 256) {
             counts[(size_t)d * ntiles + tile] = sum(d);
-            w[0][d] = w[1][d] = w[2][d] = w[3][d] = 0;
+            reset(d);
         }
         __syncthreads();
     }
