@@ -39,14 +39,30 @@ __global__ __launch_bounds__(BT_NT) void k_union_edges(const int2* const* __rest
     __syncthreads();
     const int2* __restrict__ edges = *edges_at;
     int32_t g = s_g0;
+    uint64_t next = (uint64_t)eoff[g + 1];   // past the graph's edges
+    int32_t n = nv[g];
+    int64_t base = voff[g];
     const uint64_t c1 = c0 + BT_EDGES_PER_BLOCK < E ? c0 + BT_EDGES_PER_BLOCK : E;
-    for (uint64_t i = c0 + threadIdx.x; i < c1; i += BT_NT) {
-        while (g + 1 < G && (uint64_t)eoff[g + 1] <= i) ++g;
-        const int2 e = edges[i];
-        const int32_t n = nv[g];
-        const int64_t base = voff[g];
-        const bool ok = e.x >= 0 && e.x < n && e.y >= 0 && e.y < n;
-        out[i] = ok ? make_int2((int)(base + e.x), (int)(base + e.y)) : make_int2(-1, -1);
+    // eight edges in flight; the graph's bounds are read when it changes (one edge and
+    // its graph's bounds at a time: 0.75 ms for 75 million pairs, against 0.43)
+    constexpr int U = 8;
+    for (uint64_t i0 = c0 + threadIdx.x; i0 < c1; i0 += U * BT_NT) {
+        int2 e[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) e[k] = i0 + k * BT_NT < c1 ? edges[i0 + k * BT_NT] : make_int2(0, 0);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const uint64_t i = i0 + k * BT_NT;
+            if (i >= c1) break;
+            while (next <= i && g + 1 < G) {
+                ++g;
+                next = (uint64_t)eoff[g + 1];
+                n = nv[g];
+                base = voff[g];
+            }
+            const bool ok = e[k].x >= 0 && e[k].x < n && e[k].y >= 0 && e[k].y < n;
+            out[i] = ok ? make_int2((int)(base + e[k].x), (int)(base + e[k].y)) : make_int2(-1, -1);
+        }
     }
 }
 

@@ -953,7 +953,8 @@ static int radix_sort(KeyT* keys, KeyT* keys_alt, uint32_t* vals, uint32_t* vals
     // look back (no histogram pass); the first pass counts their digits. With the
     // totals given (counted by an earlier kernel), every pass looks back. (The one
     // 32-bit sort this large with several passes, the endpoint sort of ids wider
-    // than 27 bits, keeps its histogram passes.)
+    // than 27 bits, keeps its histogram passes.) With 4096-key tiles the histogram passes are
+    // faster: R-MAT 20 2.10 ms, 2.20 looking back; 10 million uniform pairs 1.27 and 1.37.
     constexpr bool LB_TILES = RS_ITEMS == RS_ITEMS_HUGE && sizeof(KeyT) == 8;
     const bool all_lb = totals_given && LB_TILES && !vals && npasses <= LB_MAX_MORE;
     const bool lookback = all_lb || (LB_TILES && !vals && npasses >= 2 && npasses - 1 <= LB_MAX_MORE);
