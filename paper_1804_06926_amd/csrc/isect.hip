@@ -918,10 +918,10 @@ __global__ __launch_bounds__(HB_NT, 2 * HB_W / 4) void k_isect_hub(IsectArgs a, 
 // marked (CSC_FOLLOWS) and skipped. A tile is a stretch of grp_edges of them, long
 // enough that setting the words of 32 rows (10^4 to 10^5 elements) is small beside it; a wave
 // takes 64 in-edges at a time, with no barrier between a tile's set-up and its end.
-// Measured with the hub kernel for the ranks below: R-MAT 24 5.0 + 4.6 ms against 12.2 ms of the
-// hub kernel alone, R-MAT 20 0.46 + 0.07 against 0.64. Bound at R-MAT 24: line traffic
-// beyond L2, 33.5 GB at 6.7 TB/s (the hub kernel: 32.8 GB at 7.1); at R-MAT 20 the
-// set-up of many short tiles. Bit counts that add to their accumulator and byte
+// Measured with the hub kernel for the ranks below: R-MAT 24 4.9 + 4.6 ms against 12.2 ms of the
+// hub kernel alone, R-MAT 20 0.44 + 0.07 against 0.64. Bound at R-MAT 24: line traffic
+// beyond L2, 33.5 GB at 6.9 TB/s (the hub kernel: 32.8 GB at 7.1); at R-MAT 20 the
+// set-up of many short tiles (rows set one step of loads at a time, tiles from 2048 in-edges: 0.46). Bit counts that add to their accumulator and byte
 // addresses made two at a time took it from 5.5 to 5.0 ms.
 __global__ __launch_bounds__(HB_NT, 2 * HB_W / 4) void k_isect_group(IsectArgs a, uint64_t* partials) {
     __shared__ __align__(16) uint32_t words[GRP_SPAN];
@@ -953,22 +953,31 @@ __global__ __launch_bounds__(HB_NT, 2 * HB_W / 4) void k_isect_group(IsectArgs a
         uint32_t q = e0 + wv * WAVE + ln;
         uint64_t ent = entry_at(q);
         __syncthreads();
-        // the words: eight elements per thread and step
+        // the words: eight elements per thread and step, two steps in flight
         const uint32_t b0 = s_off[0], b1 = s_off[GRP_N];
-        for (uint32_t j = (b0 / HB_E + threadIdx.x) * HB_E; j < b1; j += HB_NT * HB_E) {
-            const uint4 x = ((const uint4*)a.col16)[j / HB_E];
-            const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-            uint32_t row = 0;   // the last row that starts at or before j
+        const uint32_t c1 = (b1 + HB_E - 1u) / HB_E;
+        for (uint32_t c = b0 / HB_E + threadIdx.x; c < c1; c += 2 * HB_NT) {
+            uint4 x[2];
 #pragma unroll
-            for (uint32_t step = GRP_N / 2; step > 0; step >>= 1)
-                if (s_off[row + step] <= j) row += step;
+            for (uint32_t u = 0; u < 2; ++u) x[u] = ((const uint4*)a.col16)[c + u * HB_NT < c1 ? c + u * HB_NT : c];
 #pragma unroll
-            for (uint32_t k = 0; k < HB_E; ++k) {
-                const uint32_t at = j + k;
-                if (at < b0 || at >= b1) continue;
-                while (s_off[row + 1] <= at) ++row;
-                const uint32_t y = (w[k / 2] >> (16 * (k & 1))) & 0xFFFFu;
-                if ((inc >> row) & 1u) atomicOr(&words[grp_word(y)], 1u << row);
+            for (uint32_t u = 0; u < 2; ++u) {
+                const uint32_t j = (c + u * HB_NT) * HB_E;
+                if (j >= b1) break;
+                const uint32_t w[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+                uint32_t row = 0;   // the last row that starts at or before j
+#pragma unroll
+                for (uint32_t step = GRP_N / 2; step > 0; step >>= 1)
+                    if (s_off[row + step] <= j) row += step;
+                uint32_t end = s_off[row + 1];
+#pragma unroll
+                for (uint32_t k = 0; k < HB_E; ++k) {
+                    const uint32_t at = j + k;
+                    if (at < b0 || at >= b1) continue;
+                    while (end <= at) end = s_off[++row + 1];
+                    const uint32_t y = (w[k / 2] >> (16 * (k & 1))) & 0xFFFFu;
+                    if ((inc >> row) & 1u) atomicOr(&words[grp_word(y)], 1u << row);
+                }
             }
         }
         const uint32_t inext = grab_tile(a.ctrl, GRP_COUNTER, gridDim.x, &s_tile);   // barriers: the words are complete

@@ -967,8 +967,9 @@ constexpr uint64_t HUB_MIN_TAILS = 1ull << 30;
 // hub tile (its comment has the figures).
 constexpr uint32_t WAVE_LI = 9;
 // In-edges per tile of the group kernel: GRP_TILES tiles per block, within limits (6 and 24 tiles
-// per block: R-MAT 24 43.4 and 43.1 ms against 43.1, R-MAT 20 2433 and 2480 us against 2432).
-constexpr uint32_t GRP_TILES = 12, GRP_EDGES_MIN = 2048, GRP_EDGES_MAX = 16384;
+// per block: R-MAT 24 43.4 and 43.1 ms against 43.1; R-MAT 20 with tiles of 4000, 2000 and 1000
+// in-edges 2433, 2432 and 2480 us, and with shorter set-ups 2085 us from 4096, 2103 from 2048).
+constexpr uint32_t GRP_TILES = 12, GRP_EDGES_MIN = 4096, GRP_EDGES_MAX = 16384;
 static_assert(GRP_COUNT % NBUCKET == 0, "whole groups per thread");
 __global__ __launch_bounds__(NBUCKET) void k_hub_ranges(const Ctrl* ctrl, const uint32_t* __restrict__ tstart,
                                                         const uint8_t* __restrict__ vbucket,
