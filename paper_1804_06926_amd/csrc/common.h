@@ -93,7 +93,7 @@ struct TileCountsT {
     __device__ void add(uint32_t digit) { atomicAdd(&w[threadIdx.x >> 6][digit], 1u); }
     // The same, one add for the wave's active lanes when they share the digit (adds to
     // one counter take a turn each; pairs of a batch come graph by graph, in ranges of
-    // ids: 1.86 -> 1.42 ms for the endpoint counts of 75 million).
+    // ids: 1.86 -> 1.42 ms for the endpoint counts of 148 million).
     __device__ void add_shared(uint32_t digit) {
         const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)digit);
         const uint64_t on = __ballot(true), same = __ballot(digit == d0);

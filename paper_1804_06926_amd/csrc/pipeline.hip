@@ -60,7 +60,7 @@ constexpr unsigned DEG_EP_BLOCKS = 1024;
 
 // FOLD: the orientation's digits are the upper bits of the endpoint sort's, so its counts
 // are sums of those of the first and of the second ids, counted apart: two LDS
-// adds per pair instead of four (a batch of 75 million pairs 1.42 -> 0.79 ms; R-MAT 24,
+// adds per pair instead of four (a batch of 148 million pairs 1.42 -> 0.79 ms; R-MAT 24,
 // whose ids spread over the counters, 0.72 ms either way).
 // The pairs counted as sentinels are corrected one by one.
 template <int D, bool FOLD>
