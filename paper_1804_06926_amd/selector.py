@@ -28,7 +28,9 @@ import numpy as np
 from . import _lib
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-DEFAULT_WEIGHTS = os.path.join(HERE, "selector_weights.json")
+# The networks trained on the present kernels' times (selector_weights.json holds the ones
+# trained before the group and wave kernels, for whoever has them in use).
+DEFAULT_WEIGHTS = os.path.join(HERE, "selector_networks.json")
 KERNELS = ("merge", "bsearch", "bitmap")
 
 

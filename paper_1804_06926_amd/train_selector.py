@@ -2,7 +2,7 @@
 
 Training graphs: R-MAT scales 18-22 (edge factor 16) and Chung-Lu graphs
 (power-law exponent 2.1), all seeded apart from the benchmark and test graphs;
-with --with-rgg also random geometric graphs of 2^17-2^21 vertices.
+with --with-rgg also random geometric graphs of 2^17-2^22 vertices.
 Held-out graphs: R-MAT scale 24 and a random geometric graph on 2^23 vertices
 (average degree 32).
 
@@ -16,8 +16,8 @@ per-graph regret of the learned choice, of the heuristic and of every single
 strategy, and the end-to-end step time of the learned and heuristic modes
 (alternating blocks, with the spread of the per-block ratio).
 
-    python -m paper_1804_06926_amd.train_selector --out selector_weights.json --report report.json
-    python -m paper_1804_06926_amd.train_selector --evaluate selector_weights.json --report report.json
+    python -m paper_1804_06926_amd.train_selector --out selector_networks.json --report report.json
+    python -m paper_1804_06926_amd.train_selector --evaluate selector_networks.json --report report.json
 """
 from __future__ import annotations
 
@@ -51,10 +51,10 @@ def training_graphs(quick: bool, with_rgg: bool = False):
         return
     # mesh-like graphs: without them the network never sees buckets where merge
     # path beats binary search by a wide margin (sizes and seeds distinct from
-    # the held-out random geometric graphs); one large size, since the edge
+    # the held-out random geometric graphs); two large sizes, since the edge
     # kernels' tile size, and with it their relative speed, grows with a
     # bucket's in-edges
-    rsizes = (1 << 15, 1 << 16) if quick else (1 << 17, 1 << 18, 1 << 19, 1 << 21)
+    rsizes = (1 << 15, 1 << 16) if quick else (1 << 17, 1 << 18, 1 << 19, 1 << 21, 1 << 22)
     for i, n in enumerate(rsizes):
         for j, deg in enumerate((16.0, 32.0)):
             yield f"rgg_n{n}_d{int(deg)}_seed{301 + 2 * i + j}", graphgen.rgg(n, deg, seed=301 + 2 * i + j), n
