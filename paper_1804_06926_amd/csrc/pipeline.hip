@@ -29,6 +29,8 @@
 #include "isect.h"
 #include "mlp.h"
 #include "pipeline.h"
+
+#include <algorithm>
 #include "tiles.h"
 
 namespace tcx {
@@ -760,20 +762,46 @@ __global__ __launch_bounds__(NT) void k_sym_build(uint64_t* __restrict__ keys, c
 }
 
 // ------------------------------------------------------------------ buckets
-__global__ __launch_bounds__(NT) void k_vbucket(const uint32_t* __restrict__ off, const uint32_t* __restrict__ col,
+// Each block adds its sums to the same few words, about 20 ns after one another, so
+// there are few and large blocks, and four vertices per thread are in flight for the
+// gathers of the lists' ends (2048 blocks of 256, one vertex at a time: 35 us for a million
+// vertices of a uniform graph and 27 at R-MAT 20, now 18 and 14). Small graphs, whose
+// blocks are few anyway, take small ones (R-MAT 16: the call 428 us with large ones, 424).
+constexpr int VB_NT = 1024, VB_BLOCKS = 512, VB_SMALL = 1 << 19;
+__global__ __launch_bounds__(VB_NT) void k_vbucket(const uint32_t* __restrict__ off, const uint32_t* __restrict__ col,
                                                 const uint32_t* __restrict__ inoff, int32_t n,
                                                 uint8_t* __restrict__ vbucket, Ctrl* ctrl) {
     __shared__ BucketSums S;
-    S.clear(NT);
+    const int nt = (int)blockDim.x;
+    S.clear(nt);
     __syncthreads();
-    for (int64_t v = (int64_t)blockIdx.x * NT + threadIdx.x; v < n; v += (int64_t)gridDim.x * NT) {
-        const uint32_t din = inoff[v + 1] - inoff[v], dout = off[v + 1] - off[v];
-        const uint32_t b = bucket_of(din, dout);
-        vbucket[v] = (uint8_t)b;
-        if (b != BUCKET_NONE) S.add(din, dout, col[off[v]], col[off[v + 1] - 1]);
+    constexpr int U = 4;   // vertices in flight per thread
+    for (int64_t v0 = (int64_t)blockIdx.x * nt + threadIdx.x; v0 < n; v0 += (int64_t)gridDim.x * nt * U) {
+        uint32_t din[U], o0[U], o1[U], lo[U], hi[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int64_t v = v0 + (int64_t)k * gridDim.x * nt, w = v < n ? v : v0;
+            din[k] = inoff[w + 1] - inoff[w];
+            o0[k] = off[w];
+            o1[k] = off[w + 1];
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const bool work = din[k] > 0 && o1[k] > o0[k];
+            lo[k] = work ? col[o0[k]] : 0u;
+            hi[k] = work ? col[o1[k] - 1u] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int64_t v = v0 + (int64_t)k * gridDim.x * nt;
+            if (v >= n) break;
+            const uint32_t b = bucket_of(din[k], o1[k] - o0[k]);
+            vbucket[v] = (uint8_t)b;
+            if (b != BUCKET_NONE) S.add(din[k], o1[k] - o0[k], lo[k], hi[k]);
+        }
     }
     __syncthreads();
-    S.flush(ctrl, NT);
+    S.flush(ctrl, nt);
 }
 
 // ------------------------------------------------------------------ selection
@@ -1662,7 +1690,10 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
     mark(6);
     // ---- buckets + selection
     const uint32_t* mcol = (r.formulation == FORM_FULL || r.formulation == FORM_MATRIX) ? sym_col(r, L) : col;
-    hipLaunchKernelGGL(k_vbucket, dim3(grid_for((size_t)n, 2048)), dim3(NT), 0, s, moff, mcol, inoff, n, vbucket,
+    hipLaunchKernelGGL(k_vbucket,
+                       dim3(n < VB_SMALL ? grid_for((size_t)n)
+                                         : (unsigned)std::min<int64_t>(((int64_t)n + VB_NT - 1) / VB_NT, VB_BLOCKS)),
+                       dim3(n < VB_SMALL ? NT : VB_NT), 0, s, moff, mcol, inoff, n, vbucket,
                        ctrl);
     select_buckets(r, ctrl, hub_tab(r, L));
     mark(7);
