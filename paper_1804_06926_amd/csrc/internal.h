@@ -190,10 +190,14 @@ struct HubTab {
 };
 // The wave kernel (the bitmap strategy, a wave per vertex) takes ranks below this.
 constexpr uint32_t WV_SLOTS = 2048, WV_TAG = 0x7FFF, WV_RANKS = WV_TAG * WV_SLOTS;
-// An in-edge entry (tail start | tail end << 32) whose row holds an earlier member of
-// the same group (only where the group kernel may run).
+// An in-edge entry: tail start | tail end << 32. In the filtered form both are positions in the
+// oriented columns, below 2^31, and the top bit says that the entry's row holds an earlier member
+// of the same group (set only where the group kernel may run). The other formulations'
+// entries are whole rows, up to 2m < 2^32 in the symmetric adjacency: all 32 bits are the end.
 constexpr uint64_t CSC_FOLLOWS = 1ull << 63;
 __host__ __device__ inline uint32_t tail_start(uint64_t entry) { return (uint32_t)entry; }
-__host__ __device__ inline uint32_t tail_end(uint64_t entry) { return (uint32_t)(entry >> 32) & 0x7FFFFFFFu; }
+__host__ __device__ inline uint32_t tail_end(uint64_t entry, bool whole_rows = false) {
+    return (uint32_t)(entry >> 32) & (whole_rows ? 0xFFFFFFFFu : 0x7FFFFFFFu);
+}
 
 }  // namespace tcx

@@ -380,7 +380,7 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
                 if (k < ne) {
                     const uint64_t ent = a.csc[e0 + k];   // tail start | tail end << 32
                     st_h[h] = tail_start(ent);
-                    len_h[h] = tail_end(ent) - st_h[h];
+                    len_h[h] = tail_end(ent, CLIP) - st_h[h];
                 }
             }
             // the table: once per vertex, or per window when the tails are clipped
@@ -1375,7 +1375,7 @@ __global__ __launch_bounds__(IS_NT, MODE == EM_VERTEX ? 4 : (MERGE ? 7 : 6)) voi
             uint32_t c = 0, e = 0, v = 0;
             if (q < ne) {
                 v = S.v[sg];
-                const uint32_t s = tail_start(ent), end = tail_end(ent);
+                const uint32_t s = tail_start(ent), end = tail_end(ent, a.clip != 0);
                 e = s - 1u;
                 const uint32_t nb = s_boff[sg + 1] - s_boff[sg];
                 const uint32_t bo = a.off[v];
