@@ -109,6 +109,10 @@ uint32_t* radix_first_counts(void* temp);
 // per tile of endpoint_tile(2E, digits) ids. Returns the ids per digit, in temp
 // (radix_temp_bytes(max(2E, n))).
 uint32_t endpoint_tile(size_t ids, uint32_t digits);
+// Stretches of at most `chunk` endpoints of a group of `size`, which can be nearly 2^32 (without size + chunk).
+__host__ __device__ inline uint32_t stretches(uint32_t size, uint32_t chunk) {
+    return size / chunk + (size % chunk ? 1u : 0u);
+}
 const uint32_t* partition_endpoints(const int2* edges, size_t E, int32_t n, uint32_t sentinel, RadixDigit dg, uint16_t* out,
                                     void* temp, hipStream_t s);
 

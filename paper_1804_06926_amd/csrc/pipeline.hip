@@ -222,7 +222,7 @@ __global__ __launch_bounds__(NTB) void k_bucket_count(const EP* __restrict__ ep,
         uint32_t cnt = 0, size = 0, total;
         for (uint32_t q = q0; q < q0 + per && q < nb; ++q) {
             const uint32_t c = tot ? tot[q] : len_all;
-            cnt += (c + chunk - 1u) / chunk;
+            cnt += stretches(c, chunk);
             size += c;
         }
         uint32_t at = block_exclusive_scan<NTB>(cnt, scratch, &total);
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(NTB) void k_bucket_count(const EP* __restrict__ ep,
         if (slot >= total) return;   // the same for the whole block
         if (slot >= at && slot < at + cnt)
             for (uint32_t q = q0;; ++q) {
-                const uint32_t sz = tot ? tot[q] : len_all, c = (sz + chunk - 1u) / chunk;
+                const uint32_t sz = tot ? tot[q] : len_all, c = stretches(sz, chunk);
                 if (slot < at + c) {
                     s_bucket = q;
                     s_start = pos;

@@ -40,3 +40,13 @@ def test_entry_ends(tmp_path, form, ends):
     for end in ends:
         want += [max(end - 400, 0), end] * (1 if form == "true" else 2)
     assert got == want
+
+
+def test_stretches_of_a_bucket(tmp_path):
+    """Stretches of a bucket of endpoints: the exact quotient rounded up, up to all 2E endpoints of the largest
+    edge list in one bucket and the stretch length that it gets."""
+    largest = 2 * M_MAX
+    sizes = [0, 1, 8191, 8192, 8193, 1 << 31, largest - 1, largest]
+    chunks = [8192, 8193, 3 * largest // 512, 3 * largest // (2 * 8192)]
+    body = "".join(f'printf("%u\\n", stretches({s}u, {c}u));\n' for s in sizes for c in chunks)
+    assert [int(x) for x in run_host(tmp_path, body, ["internal.h"])] == [-(-s // c) for s in sizes for c in chunks]
