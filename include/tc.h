@@ -84,8 +84,13 @@ tc_status tc_destroy(tc_ctx* ctx);
 /* Bytes of device workspace for a call with these sizes. The value depends
  * only on the arguments, and one workspace serves every call with equal or
  * smaller sizes (a small graph's bit matrix can make its size exceed a larger graph's:
- * in a workspace without room for it, it is counted without the matrix). */
+ * in a workspace without room for it, it is counted without the matrix).
+ * tc_workspace_size_min is the same without the matrix: the least that every
+ * call with these sizes accepts, which never falls as a size grows, and all that
+ * the calls without a matrix use (per-edge outputs, the CSR, forced strategies,
+ * stage times, the timing calls for training). */
 tc_status tc_workspace_size(int64_t num_edges, int32_t num_vertices, const tc_options* opts, size_t* bytes);
+tc_status tc_workspace_size_min(int64_t num_edges, int32_t num_vertices, const tc_options* opts, size_t* bytes);
 
 /*
  * Exact triangle count T of the undirected simple graph denoted by the edge

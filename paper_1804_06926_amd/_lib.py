@@ -47,6 +47,7 @@ def _load():
     lib.tc_create.argtypes = [ctypes.POINTER(vp), ctypes.c_int, vp]
     lib.tc_destroy.argtypes = [vp]
     lib.tc_workspace_size.argtypes = [i64, i32, ctypes.POINTER(Options), ctypes.POINTER(sz)]
+    lib.tc_workspace_size_min.argtypes = lib.tc_workspace_size.argtypes
     lib.tc_count_triangles.argtypes = [vp, vp, i64, i32, vp, sz, ctypes.POINTER(Options),
                                        ctypes.POINTER(ctypes.c_uint64), vp]
     lib.tc_count_triangles_async.argtypes = [vp, vp, i64, i32, vp, sz, ctypes.POINTER(Options), vp, vp]
@@ -75,7 +76,8 @@ def _load():
     lib.tc_stage_name.restype = ctypes.c_char_p
     lib.tc_last_error.argtypes = [vp]
     lib.tc_last_error.restype = ctypes.c_char_p
-    for f in ("tc_create", "tc_destroy", "tc_workspace_size", "tc_count_triangles", "tc_count_triangles_async",
+    for f in ("tc_create", "tc_destroy", "tc_workspace_size", "tc_workspace_size_min", "tc_count_triangles",
+              "tc_count_triangles_async",
               "tc_clustering", "tc_edge_support", "tc_list_workspace_size", "tc_list_triangles",
               "tc_edge_counts",
               "tc_build_csr", "tc_radix_sort_u64", "tc_radix_partition_u64", "tc_sort_runs_u64"):
@@ -128,6 +130,22 @@ def workspace_size(num_edges: int, num_vertices: int, select: int = SELECT_HEURI
     st = _load().tc_workspace_size(num_edges, num_vertices, ctypes.byref(o), ctypes.byref(out))
     _check(st, None)
     return int(out.value)
+
+
+def _workspace_size_min(num_edges: int, num_vertices: int, select: int = SELECT_HEURISTIC) -> int:
+    out = ctypes.c_size_t()
+    o = _options(select, False)
+    st = _load().tc_workspace_size_min(num_edges, num_vertices, ctypes.byref(o), ctypes.byref(out))
+    _check(st, None)
+    return int(out.value)
+
+
+def _count_workspace(idx: int, num_edges: int, num_vertices: int, select: int, workspace):
+    """For the calls that count small graphs on a bit matrix (no strategy forced) where the workspace holds it:
+    one of our own does, a given one need not."""
+    matrix = workspace is None and select in (SELECT_HEURISTIC, SELECT_LEARNED)
+    size = workspace_size if matrix else _workspace_size_min
+    return _workspace(idx, size(num_edges, num_vertices, select), workspace)
 
 
 def _workspace(idx: int, nbytes: int, workspace=None):
@@ -183,8 +201,7 @@ def count_triangles(edges, num_vertices: int, per_vertex: bool = False, select: 
     ctx, idx = _ctx(e.device)
     E = e.shape[0]
     o = _options(select, timing)
-    nbytes = workspace_size(E, num_vertices, select)
-    ws = _workspace(idx, nbytes, workspace)
+    ws = _count_workspace(idx, E, num_vertices, select, workspace)
     # t[v] < 2^63, so the uint64 results are held in an int64 tensor
     pv = torch.empty(num_vertices, dtype=torch.int64, device=e.device) if per_vertex else None
     count = ctypes.c_uint64()
@@ -223,7 +240,10 @@ def count_triangles_formulation(edges, num_vertices: int, formulation: str = "fu
     lib = _load()
     nb = ctypes.c_size_t()
     _check(lib.tc_formulation_workspace_size(E, num_vertices, ctypes.byref(o), f, ctypes.byref(nb)), None)
-    ws = _workspace(idx, nb.value, workspace)
+    nbytes = nb.value
+    if workspace is not None or formulation != "filtered":   # no bit matrix
+        nbytes -= workspace_size(E, num_vertices, select) - _workspace_size_min(E, num_vertices, select)
+    ws = _workspace(idx, nbytes, workspace)
     count, total = ctypes.c_uint64(), ctypes.c_uint64()
     st = lib.tc_count_triangles_formulation(ctx, e.data_ptr() if E else None, E, num_vertices, ws.data_ptr(),
                                             ws.numel(), ctypes.byref(o), f, ctypes.byref(count), ctypes.byref(total))
@@ -248,7 +268,7 @@ def count_triangles_async(edges, num_vertices: int, result=None, per_vertex=None
     ctx, idx = _ctx(e.device)
     E = e.shape[0]
     o = _options(select, False)
-    ws = _workspace(idx, workspace_size(E, num_vertices, select), workspace)
+    ws = _count_workspace(idx, E, num_vertices, select, workspace)
     if result is None:
         result = torch.empty(2, dtype=torch.int64, device=e.device)
     if per_vertex is not None and (per_vertex.dtype != torch.int64 or per_vertex.numel() < num_vertices):
@@ -303,7 +323,7 @@ def clustering(edges, num_vertices: int, per_vertex: bool = False, select: int =
     ctx, idx = _ctx(e.device)
     E = e.shape[0]
     o = _options(select, False)
-    ws = _workspace(idx, workspace_size(E, num_vertices, select), workspace)
+    ws = _count_workspace(idx, E, num_vertices, select, workspace)
     coeff = torch.empty(max(num_vertices, 1), dtype=torch.float64, device=e.device)[:num_vertices]
     pv = torch.empty(num_vertices, dtype=torch.int64, device=e.device) if per_vertex else None
     T, W, tr = ctypes.c_uint64(), ctypes.c_uint64(), ctypes.c_double()
@@ -350,7 +370,7 @@ def edge_support(edges, num_vertices: int, select: int = SELECT_HEURISTIC, works
     ctx, idx = _ctx(e.device)
     E = e.shape[0]
     o = _options(select, False)
-    ws = _workspace(idx, workspace_size(E, num_vertices, select), workspace)
+    ws = _workspace(idx, _workspace_size_min(E, num_vertices, select), workspace)
     pairs = torch.empty((max(E, 1), 2), dtype=torch.int32, device=e.device)
     sup = torch.empty(max(E, 1), dtype=torch.int32, device=e.device)
     m = ctypes.c_int64()
@@ -370,7 +390,7 @@ def edge_counts(edges, num_vertices: int, select: int = SELECT_HEURISTIC, worksp
     ctx, idx = _ctx(e.device)
     E = e.shape[0]
     o = _options(select, False)
-    ws = _workspace(idx, workspace_size(E, num_vertices, select), workspace)
+    ws = _workspace(idx, _workspace_size_min(E, num_vertices, select), workspace)
     pairs = torch.empty((max(E, 1), 2), dtype=torch.int32, device=e.device)
     counts = torch.empty(max(E, 1), dtype=torch.int32, device=e.device)   # uint32 counts < 2^31
     m = ctypes.c_int64()
@@ -390,7 +410,7 @@ def build_csr(edges, num_vertices: int, workspace=None):
     ctx, idx = _ctx(e.device)
     E = e.shape[0]
     o = _options(SELECT_HEURISTIC, False)
-    ws = _workspace(idx, workspace_size(E, num_vertices), workspace)
+    ws = _workspace(idx, _workspace_size_min(E, num_vertices), workspace)
     rank = torch.empty(max(num_vertices, 1), dtype=torch.int32, device=e.device)
     off = torch.empty(num_vertices + 1, dtype=torch.int64, device=e.device)
     col = torch.empty(max(E, 1), dtype=torch.int32, device=e.device)
@@ -623,7 +643,7 @@ def profile_buckets(edges, num_vertices: int, repeats: int = 5, workspace=None):
     e = _edges_arg(edges)
     ctx, idx = _ctx(e.device)
     E = e.shape[0]
-    ws = _workspace(idx, workspace_size(E, num_vertices), workspace)
+    ws = _workspace(idx, _workspace_size_min(E, num_vertices), workspace)
     ms = np.zeros((3, 256), dtype=np.float32)
     feat = np.zeros((256, SELECTOR_NUM_FEATURES), dtype=np.float32)
     _check(_sel_lib().tc_profile_buckets(ctx, e.data_ptr() if E else None, E, num_vertices, ws.data_ptr(),
@@ -640,7 +660,7 @@ def profile_choices(edges, num_vertices: int, choice, chunk=None, repeats: int =
     e = _edges_arg(edges)
     ctx, idx = _ctx(e.device)
     E = e.shape[0]
-    ws = _workspace(idx, workspace_size(E, num_vertices), workspace)
+    ws = _workspace(idx, _workspace_size_min(E, num_vertices), workspace)
     ch = np.ascontiguousarray(choice, dtype=np.uint8)
     if ch.shape != (256,):
         raise ValueError("choice must have 256 entries")
@@ -734,7 +754,7 @@ def profile_selected(edges, num_vertices: int, select: int = SELECT_HEURISTIC, r
     e = _edges_arg(edges)
     ctx, idx = _ctx(e.device)
     E = e.shape[0]
-    ws = _workspace(idx, workspace_size(E, num_vertices), workspace)
+    ws = _workspace(idx, _workspace_size_min(E, num_vertices), workspace)
     ms = np.zeros(256, dtype=np.float32)
     o = _options(select, False)
     _check(_batch_lib().tc_profile_selected(ctx, e.data_ptr() if E else None, E, num_vertices, ws.data_ptr(),

@@ -291,6 +291,12 @@ tc_status tc_workspace_size(int64_t num_edges, int32_t num_vertices, const tc_op
     return TC_OK;
 }
 
+tc_status tc_workspace_size_min(int64_t num_edges, int32_t num_vertices, const tc_options* opts, size_t* bytes) {
+    const tc_status st = tc_workspace_size(num_edges, num_vertices, opts, bytes);
+    if (st == TC_OK) *bytes = tcx::make_layout(num_edges, num_vertices).total;
+    return st;
+}
+
 tc_status tc_count_triangles(tc_ctx* ctx, const int32_t* d_edges, int64_t num_edges, int32_t num_vertices,
                              void* d_workspace, size_t workspace_bytes, const tc_options* opts, uint64_t* h_count,
                              uint64_t* d_per_vertex) {
