@@ -306,7 +306,7 @@ __global__ __launch_bounds__(NT) void k_endpoint_bounds(const uint32_t* __restri
     }
 }
 
-// Key (min(degree, RANK_CAP), id), sorted on its upper half: two passes. The few
+// Key (min(degree, RANK_CAP), id), sorted on its upper half: two passes. The
 // vertices of degree RANK_CAP or more (at most 2E / RANK_CAP) share the last
 // place there and are ordered by k_rank. (Sorting whole degrees took three or four
 // passes, for bits that a handful of hubs have; the rank stage with two, and with the first
@@ -356,36 +356,58 @@ __global__ __launch_bounds__(NT) void k_vertex_keys(uint32_t* __restrict__ deg, 
 }
 
 // rank[v] = position of v; inv its inverse. Vertices of degree RANK_CAP or more stand
-// last, by id: each finds its place by comparing (degree, id) with the
-// others. Also clears rowend[0..n) and part[0..npart) for the stages to come.
+// last, by id: each finds its place by comparing (degree, id) with all of them, which the
+// block passes through LDS 256 at a time. They are few in a simple graph with hubs, but up to
+// 2E / RANK_CAP where pairs repeat: one thread gathering their degrees one by one took
+// the rank stage of 3,000, 8,000 and 30,000 vertices that are all of them (2^27, 3e8 and 1e9 pairs,
+// CSR in 11, 27 and 98 ms) 0.24, 0.58 and 2.08 ms, this takes 0.07, 0.13 and 0.37; sorting whole
+// degrees would take 0.06, and 0.18 ms more at R-MAT 24. Also clears rowend[0..n) and
+// part[0..npart) for the stages to come.
 template <bool OFFSETS>
 __global__ __launch_bounds__(NT) void k_rank(const uint64_t* __restrict__ sorted, int32_t n,
                                              const uint32_t* __restrict__ deg, uint32_t* __restrict__ rank,
                                              uint32_t* __restrict__ inv, uint32_t* __restrict__ rowend,
                                              uint32_t* __restrict__ part, uint32_t npart) {
+    __shared__ uint64_t s_key[NT];
     for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < npart; i += gridDim.x * NT) part[i] = 0;
-    for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) {
-        const uint64_t key = sorted[i];
+    for (int64_t i0 = (int64_t)blockIdx.x * NT; i0 < n; i0 += (int64_t)gridDim.x * NT) {
+        const int64_t i = i0 + threadIdx.x;
+        const uint32_t last = (uint32_t)(i0 + NT < n ? i0 + NT : n) - 1u;
+        const uint64_t key = sorted[i < n ? i : last];
         const uint32_t v = (uint32_t)key;
         uint32_t pos = (uint32_t)i;
-        if ((uint32_t)(key >> 32) == RANK_CAP) {
-            uint32_t lo = 0, hi = (uint32_t)i;   // first of the capped keys
+        if ((uint32_t)(sorted[last] >> 32) == RANK_CAP) {   // the same for the whole block
+            uint32_t lo = 0, hi = last;   // first of the capped keys
             while (lo < hi) {
                 const uint32_t mid = lo + (hi - lo) / 2;
                 if ((uint32_t)(sorted[mid] >> 32) < RANK_CAP) lo = mid + 1;
                 else hi = mid;
             }
-            pos = lo;
-            const uint32_t d = degree_at<OFFSETS>(deg, v);
-#pragma unroll 4
-            for (uint32_t j = lo; j < (uint32_t)n; ++j) {
-                const uint32_t u = (uint32_t)sorted[j], du = degree_at<OFFSETS>(deg, u);
-                pos += (du < d || (du == d && u < v)) ? 1u : 0u;
+            const bool capped = (uint32_t)(key >> 32) == RANK_CAP;
+            const uint64_t me = capped ? ((uint64_t)degree_at<OFFSETS>(deg, v) << 32) | v : 0ull;
+            // a step's degrees and the ids after it are in flight while the step before is compared
+            auto id_at = [&](uint32_t j) -> uint32_t { return j < (uint32_t)n ? (uint32_t)sorted[j] : ~0u; };
+            auto key_of = [&](uint32_t u) -> uint64_t {
+                return u != ~0u ? ((uint64_t)degree_at<OFFSETS>(deg, u) << 32) | u : ~0ull;
+            };
+            uint32_t before = 0, u = id_at(lo + NT + threadIdx.x);
+            uint64_t other = key_of(id_at(lo + threadIdx.x));
+            for (uint32_t j0 = lo; j0 < (uint32_t)n; j0 += NT) {
+                __syncthreads();   // the keys before have been compared
+                s_key[threadIdx.x] = other;
+                __syncthreads();
+                other = key_of(u);
+                u = id_at(j0 + 2 * NT + threadIdx.x);
+#pragma unroll 16
+                for (int q = 0; q < NT; ++q) before += s_key[q] < me ? 1u : 0u;
             }
+            if (capped) pos = lo + before;
         }
-        rank[v] = pos;
-        inv[pos] = v;
-        rowend[i] = 0;
+        if (i < n) {
+            rank[v] = pos;
+            inv[pos] = v;
+            rowend[i] = 0;
+        }
     }
 }
 
