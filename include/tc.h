@@ -247,8 +247,8 @@ tc_status tc_count_triangles_formulation(tc_ctx* ctx, const int32_t* d_edges, in
  * every triangle lies inside one graph, and each is attributed to its graph
  * through its middle vertex, so h_counts[g] (host, uint64) is exact.
  * By default the whole device work of a call is captured once as a HIP graph
- * and replayed on later calls with the same sizes, edge pointer, workspace
- * and selection mode (TC_F_NO_GRAPH launches directly). If the context's
+ * and replayed on later calls with the same sizes, workspace and selection
+ * mode, with a tile network or without (TC_F_NO_GRAPH launches directly). If the context's
  * stream is the null stream, the work runs on a stream owned by the context.
  * Workspace: tc_batch_workspace_size(total pairs, total vertices, graphs).
  * An id outside its own graph's range yields TC_ERR_VERTEX_RANGE.

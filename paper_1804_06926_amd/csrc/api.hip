@@ -51,6 +51,7 @@ struct tc_ctx {
     struct {   // sizes and workspace of the captured batch (the edge list is read through the workspace)
         int64_t E, N;
         int32_t G, select;
+        int tile;   // the tile network is among its launches
         const void* ws;
     } graph_key = {};
     uint64_t* h_counts_pinned = nullptr;
@@ -676,9 +677,10 @@ tc_status tc_count_triangles_batch(tc_ctx* ctx, const int32_t* d_edges, const in
     ra.group_override = ctx->d_group;
     ra.grid_override = ctx->grid_override;
     tcx::BatchArgs ba = {d_edges, E, N, num_graphs};
+    const int tile = sel == TC_SELECT_LEARNED && ctx->tile_ready;
     const bool same = ctx->graph_exec && ctx->graph_key.E == E && ctx->graph_key.N == N &&
                       ctx->graph_key.G == num_graphs && ctx->graph_key.select == sel &&
-                      ctx->graph_key.ws == d_workspace;
+                      ctx->graph_key.tile == tile && ctx->graph_key.ws == d_workspace;
     if (capture && !same) {
         if (ctx->graph_exec) (void)hipGraphExecDestroy(ctx->graph_exec);
         if (ctx->graph) (void)hipGraphDestroy(ctx->graph);
@@ -691,7 +693,7 @@ tc_status tc_count_triangles_batch(tc_ctx* ctx, const int32_t* d_edges, const in
         if (le != hipSuccess) e = le;
         if (e == hipSuccess) e = hipGraphInstantiate(&ctx->graph_exec, ctx->graph, nullptr, nullptr, 0);
         if (e != hipSuccess) return hip_fail(ctx, e, "capture batch");
-        ctx->graph_key = {E, N, num_graphs, sel, d_workspace};
+        ctx->graph_key = {E, N, num_graphs, sel, tile, d_workspace};
     }
     if (capture) e = hipGraphLaunch(ctx->graph_exec, s);
     else e = tcx::run_batch(ba, ra);
