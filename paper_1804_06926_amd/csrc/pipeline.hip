@@ -14,7 +14,8 @@
 //             symmetric adjacency beside the filtered CSR)
 //   bucket    per middle vertex v: (in-edges with work, |N+(v)|) -> bucket
 //   select    choose the intersection strategy and tile shape per bucket
-//   group     order vertices by (strategy, bucket); emit tiles
+//   group     order vertices by (strategy, bucket); emit tiles (and, for counts of large
+//             graphs, the hub kernels' tile ranges and 16-bit columns)
 //   isect     the three intersection kernels, each over its tile range
 //   finish    map per-vertex / per-edge outputs back to original ids
 // No stage relies on atomics to one address: compaction and grouping go
@@ -1737,14 +1738,14 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
     if (r.per_edge_counts) fill_u32(r.per_edge_counts, 0u, (size_t)E, s);
     if (r.support) fill_u32(r.support, 0u, (size_t)E, s);
     if (r.per_vertex || r.per_middle || r.clustering) fill_u64(pv, 0ull, (size_t)n, s);
+    IsectArgs ia = isect_args(r, L, csc);
+    if (!r.stop_before_isect) prepare_hub(r, L, csc, ia);
     mark(8);
     if (r.stop_before_isect) {
         out->ctrl_dev = ctrl;
         return hipGetLastError();
     }
     // ---- intersections
-    IsectArgs ia = isect_args(r, L, csc);
-    prepare_hub(r, L, csc, ia);
     uint64_t* partials = (uint64_t*)(ws + L.isect_partials);
     const int order[NKERNEL] = {KER_MERGE, KER_BSEARCH, KER_BITMAP};
     IsectParts parts;
