@@ -319,7 +319,7 @@ tc_status tc_radix_partition_u64(tc_ctx* ctx, const uint64_t* d_in, uint64_t* d_
  * high bits in ascending order), are sorted by the whole key inside every run,
  * in place, so a pair list sorted by row leaves with each row sorted by column
  * (the sorted out-lists of Section 3.2). Runs of up to 64 keys are sorted
- * together by a network across a wave, up to 2048 by one wave's registers, up
+ * together by a network across a wave, up to 1024 by one wave's registers, up
  * to 4096 by a whole block, longer ones by a whole block's radix passes in
  * d_tmp. Any key order is safe (runs are the maximal stretches of equal high
  * bits); only grouped input yields a sorted array.
@@ -385,15 +385,18 @@ tc_status tc_bucket_features(const tc_ctx* ctx, float* h_features);
  * launches of strategy k on bucket b's tiles alone, in milliseconds, into
  * h_ms[k * 256 + b] (-1 where the bucket is empty). h_features (optional)
  * receives the bucket features [256][6]. Uses the same workspace as
- * tc_count_triangles.
+ * tc_count_triangles. The bitmap strategy is timed with its plain kernel. A
+ * count of 2^24 pairs or more gives tiles of that strategy to kernels that share work
+ * between buckets, which have no time of a bucket alone: there tc_profile_choices tells what
+ * a bucket's choice costs.
  */
 tc_status tc_profile_buckets(tc_ctx* ctx, const int32_t* d_edges, int64_t num_edges, int32_t num_vertices,
                              void* d_workspace, size_t workspace_bytes, int32_t repeats, float* h_ms,
                              float* h_features);
 
 /* Like tc_profile_buckets, but each bucket is timed only with the strategy
- * that opts->select chooses for it (the current tile shapes apply):
- * h_ms[256], -1 where the bucket is empty. Used by the tile-shape autotuner. */
+ * that opts->select chooses for it (the current tile shapes apply; the bitmap
+ * strategy with its plain kernel, as there): h_ms[256], -1 where the bucket is empty. Used by the tile-shape autotuner. */
 tc_status tc_profile_selected(tc_ctx* ctx, const int32_t* d_edges, int64_t num_edges, int32_t num_vertices,
                               void* d_workspace, size_t workspace_bytes, const tc_options* opts, int32_t repeats,
                               float* h_ms);
@@ -401,14 +404,15 @@ tc_status tc_profile_selected(tc_ctx* ctx, const int32_t* d_edges, int64_t num_e
 /*
  * Timing data for training the selector inside the combined launch: the
  * pipeline runs up to the tile layout with the caller's choice per bucket,
- * then the whole intersection stage (the three kernels over their tile
- * ranges, as a counting call launches them, and the reduction of T) runs
+ * then the whole intersection stage (the three strategies' kernels over their
+ * tile ranges, as a counting call launches them, and the reduction of T) runs
  * `repeats` (1..64) times. h_choice [256] (host): strategy per degree-pair
  * bucket (0 merge path, 1 binary search, 2 LDS bitmap; any other value: the
  * fixed thresholds' choice); h_chunk [256] (host) or NULL: in-edges per tile
  * per bucket (0: the default rule; clamped as for tc_set_tile_shapes).
  * h_ms [4] receives the medians, in milliseconds, of the stage (the sum of the
- * three kernels) and of each kernel; h_count (optional) receives T from the
+ * strategies) and of each strategy, the bitmap's with the hub, group and wave kernels that
+ * take its tiles in counts of 2^24 pairs and more; h_count (optional) receives T from the
  * last repeat. A bucket's cost is read from the change in the stage time when
  * only its entry changes. Uses the same workspace as tc_count_triangles.
  */

@@ -2,7 +2,9 @@
 
 For each candidate tile size the library lays out the tiles and times every
 busy bucket's tiles alone with the strategy its selection mode picks
-(``profile_selected``); each bucket keeps its fastest size. Tile sizes change
+(``profile_selected``); each bucket keeps its fastest size. From 2^24 pairs on, counts
+give many tiles of the bitmap strategy to kernels other than the one timed here, and
+the sizes are a guess for those buckets. Tile sizes change
 the speed only, never the counts. Results are cached as JSON keyed by the GPU
 architecture, the HIP runtime version and the selection mode.
 """

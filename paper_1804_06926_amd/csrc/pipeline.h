@@ -115,12 +115,12 @@ size_t list_extra_bytes(int64_t E);
 // Extra workspace of the other formulations after make_layout(E, n).total: the
 // symmetric adjacency (row offsets and 2m columns).
 size_t sym_extra_bytes(int64_t E, int32_t n);
-// After a run with stop_before_isect: one intersection kernel over tiles [t0, t1).
+// After a run with stop_before_isect: one strategy's plain kernel over tiles [t0, t1).
 hipError_t launch_isect_range(const RunArgs& r, int ker, uint32_t t0, uint32_t t1);
 // After a run with stop_before_isect: the whole intersection stage as the pipeline
-// launches it (the three kernels over their tile ranges, then the reduction of T
+// launches it (the strategies' kernels over their tile ranges, then the reduction of T
 // into the control block); ev (null, or 4 events) is recorded before the first
-// kernel and after each.
+// strategy and after each, after the hub kernels' tables and columns are prepared.
 hipError_t launch_isect_stage(const RunArgs& r, hipEvent_t* ev);
 int stage_count();
 const char* stage_name(int s);

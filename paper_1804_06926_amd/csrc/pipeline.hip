@@ -18,8 +18,10 @@
 //             graphs, the hub kernels' tile ranges and 16-bit columns)
 //   isect     the three intersection kernels, each over its tile range
 //   finish    map per-vertex / per-edge outputs back to original ids
-// No stage relies on atomics to one address: compaction and grouping go
-// through sorts and scans, so every intermediate array is deterministic. The
+// Compaction and grouping go through sorts and scans. Where many threads add to one
+// address (degrees of hubs, bucket statistics, per-vertex counts of the top ranks), a block
+// adds in LDS and once to memory at its end. All of these are integer sums, so the
+// outputs do not depend on the order. The
 // kernels that write the keys of a sort also take the per-tile digit counts of
 // its first pass (one read of the keys less per sort).
 #include <math.h>
@@ -881,7 +883,7 @@ __global__ __launch_bounds__(NBUCKET) void k_select(Ctrl* ctrl, int mode, const 
     // search 5.6 -> 4.2 ms; R-MAT 20, whose edge-kernel buckets are small,
     // keeps 256; longer lists gained nothing and lost at R-MAT 24). The shape
     // depends on the bucket alone, so a bucket timed alone (selector training)
-    // runs as it does among the others.
+    // has the tiles that it has among the others.
     uint32_t chunk = (ch == KER_BITMAP && (whole_rows || li >= 8)) ? (uint32_t)CHUNK_MAX : 256u;
     if (ch != KER_BITMAP && lo <= 5) {
         const unsigned long long per = ctrl->bucket_in[b] / EDGE_TILES;
@@ -1358,9 +1360,12 @@ static uint64_t* csc_of(const RunArgs& r, const Layout& L) {
 
 // The hub kernel counts (in all, or per middle vertex) on the filtered graph.
 // Its 16-bit columns take the key buffer that the in-edge sort left free, 8 bytes
-// per pair against 2 and a last group of eight. From HUB_MIN_PAIRS on: the
-// preparing kernels and the extra launch cost 25 to 35 us on smaller graphs and
-// gain nothing there (R-MAT 16: 522 us without, 553 us with them; R-MAT 19: 1439 and 1476 us).
+// per pair against 2 and a last group of eight. From HUB_MIN_PAIRS on, about where
+// the preparing kernels and the extra launches (with the group and the wave kernel) pay on
+// graphs of ordinary density. Queued counts without and with them: R-MAT 15, 16, 17, 18 and 19 (16 pairs per
+// vertex) 306 and 377, 368 and 402, 504 and 541, 692 and 700, 1219 and 1202 us; Chung-Lu of 6 million
+// pairs 924 and 963; uniform of 10 million 1210 and 1233; random geometric of 8.4 million 1083
+// and 1099. Denser graphs gain earlier (R-MAT 17 with 12 million pairs: 1733 and 1450).
 constexpr int64_t HUB_MIN_PAIRS = 1 << 24;
 static bool hub_usable(const RunArgs& r) {
     return r.formulation == FORM_FILTERED && r.E >= HUB_MIN_PAIRS && !r.per_vertex && !r.clustering &&

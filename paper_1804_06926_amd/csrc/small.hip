@@ -18,7 +18,7 @@
 // A synchronising call also reports statistics (tc_last_stats): the degree order by
 // comparing every two vertices, the oriented degrees from the neighbour lists, then the
 // pipeline's own bucket selection. A queued call has no use for them.
-// Bound: latency (three or eight launches, one wave's chain of loads each); at the largest
+// Bound: latency (three launches queued, seven to nine with statistics, one wave's chain of loads each); at the largest
 // sizes the rows read (0.5 GB for 16384 vertices and 131072 pairs, 48 us). Measured against
 // the pipeline, queued / synchronous: Erdos-Renyi 4096 vertices, 32768 pairs 299 -> 28 /
 // 335 -> 90 us; Chung-Lu 125 and 1000 171 -> 17 / 246 -> 80 us; uniform 16384 and
@@ -68,9 +68,10 @@ static SmallLayout small_layout(int64_t E, int32_t n) {
     return L;
 }
 
-// Where the matrix wins: every size measured up to these limits (the slowest, Chung-Lu
+// The matrix wins at every size measured up to these limits (the slowest, Chung-Lu
 // of 16384 vertices and 131072 pairs, 96 us queued and 232 us with statistics against
-// 354 and 399 us by the pipeline). Twice the vertices would take 128 MB of
+// 354 and 399 us by the pipeline), so they are no crossover but what the layout holds: an order key
+// of degree and id fits 32 bits up to 2^18 pairs, twice the vertices would take 128 MB of
 // matrix, and every build block reads the whole edge list, 45 us at 131072 pairs.
 bool small_graph(int64_t E, int32_t n) {
     return n >= 1 && n <= SMALL_MAX_N && E >= 1 && E <= SMALL_MAX_PAIRS;

@@ -92,7 +92,7 @@ def collect_in_launch(graphs, repeats: int = 7, device: str = "cuda:0", log=None
                       tiles: bool = True):
     """Time each (strategy, tile size) for each busy bucket inside the combined launch.
 
-    For each graph the whole intersection stage (three kernels over their tile
+    For each graph the whole intersection stage (the strategies' kernels over their tile
     ranges, as a counting call launches them) is timed with the fixed thresholds'
     choice everywhere, then once per (busy bucket, strategy, tile scale) with only
     that bucket changed: the strategy, and its tiles at the rule's size for that
