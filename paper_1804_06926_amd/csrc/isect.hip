@@ -1192,8 +1192,11 @@ __global__ __launch_bounds__(WV_NT, 6) void k_isect_wave(IsectArgs a, uint64_t* 
 
 // ------------------------------------------------------------------ shared helpers for edge-centric kernels
 // Outputs of a launch: none that is written per triangle (T, per edge, per middle
-// vertex); any; t[v] through LDS counters.
-enum { EM_COUNT = 0, EM_ANY = 1, EM_VERTEX = 2 };
+// vertex); any; t[v] through LDS counters; none on whole-row ranges (a kernel of its own, as an
+// end that may or may not carry the group mark cost the merge kernel of the random
+// geometric graph of 2^23 vertices its schedule: the call 14.64 -> 14.76 ms).
+enum { EM_COUNT = 0, EM_ANY = 1, EM_VERTEX = 2, EM_WHOLE = 3 };
+constexpr bool em_counts(int mode) { return mode == EM_COUNT || mode == EM_WHOLE; }
 // A tail of up to this many times N+(v) is searched in N+(v), which is mostly in
 // LDS; where every in-edge took the shorter of its two lists, a wave ran both searches
 // one after the other (1, 2, 4, 8: random geometric graph of 2^23 vertices 16.1, 14.7, 14.6,
@@ -1261,7 +1264,7 @@ __device__ __forceinline__ uint32_t search_list(const IsectArgs& a, const Hot& h
         for (int u = 0; u < 4; ++u) {
             const uint32_t q = q0 + (uint32_t)u * g;
             const bool is = q < nx && y0[u] == xv[u];
-            if (MODE == EM_COUNT) {
+            if (em_counts(MODE)) {
                 c += is ? 1u : 0u;
             } else if (is) {
                 ++c;
@@ -1302,7 +1305,7 @@ __device__ __forceinline__ uint32_t isect_edge(const IsectArgs& a, const Hot& ho
                 while (j < nb && B[j] < av[u]) ++j;
                 if (j < nb && B[j] == av[u]) {
                     ++c;
-                    if (MODE != EM_COUNT) hit(a, hot, av[u], ea0 + i + u, eb0 + j, ea0 - 1u);
+                    if (!em_counts(MODE)) hit(a, hot, av[u], ea0 + i + u, eb0 + j, ea0 - 1u);
                 }
             }
         }
@@ -1377,7 +1380,7 @@ __global__ __launch_bounds__(IS_NT, MODE == EM_VERTEX ? 4 : (MERGE ? 7 : 6)) voi
             uint32_t c = 0, e = 0, v = 0;
             if (q < ne) {
                 v = S.v[sg];
-                const uint32_t s = tail_start(ent), end = tail_end(ent, a.clip != 0);
+                const uint32_t s = tail_start(ent), end = tail_end(ent, MODE == EM_WHOLE);
                 e = s - 1u;
                 const uint32_t nb = s_boff[sg + 1] - s_boff[sg];
                 const uint32_t bo = a.off[v];
@@ -1389,7 +1392,7 @@ __global__ __launch_bounds__(IS_NT, MODE == EM_VERTEX ? 4 : (MERGE ? 7 : 6)) voi
             for (uint32_t o = g >> 1; o > 0; o >>= 1) c += __shfl_xor(c, (int)o, WAVE);
             if (q < ne && gl == 0) {
                 acc += c;
-                if (MODE != EM_COUNT || a.per_edge || a.per_middle) edge_done(a, hot, e, v, c);
+                if (!em_counts(MODE) || a.per_edge || a.per_middle) edge_done(a, hot, e, v, c);
             }
         }
         __syncthreads();
@@ -1545,11 +1548,13 @@ void launch_isect(int ker, const IsectArgs& a, int grid, uint64_t* partials, hip
     }
     switch (ker) {
         case KER_MERGE:
-            if (plain) hipLaunchKernelGGL((k_isect_edges<true, EM_COUNT>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            if (a.clip) hipLaunchKernelGGL((k_isect_edges<true, EM_WHOLE>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            else if (plain) hipLaunchKernelGGL((k_isect_edges<true, EM_COUNT>), dim3(grid), dim3(IS_NT), 0, s, a, p);
             else hipLaunchKernelGGL((k_isect_edges<true, EM_ANY>), dim3(grid), dim3(IS_NT), 0, s, a, p);
             break;
         case KER_BSEARCH:
-            if (plain) hipLaunchKernelGGL((k_isect_edges<false, EM_COUNT>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            if (a.clip) hipLaunchKernelGGL((k_isect_edges<false, EM_WHOLE>), dim3(grid), dim3(IS_NT), 0, s, a, p);
+            else if (plain) hipLaunchKernelGGL((k_isect_edges<false, EM_COUNT>), dim3(grid), dim3(IS_NT), 0, s, a, p);
             else if (a.per_vertex) hipLaunchKernelGGL((k_isect_edges<false, EM_VERTEX>), dim3(grid), dim3(IS_NT), 0, s, a, p);
             else hipLaunchKernelGGL((k_isect_edges<false, EM_ANY>), dim3(grid), dim3(IS_NT), 0, s, a, p);
             break;
