@@ -47,6 +47,14 @@ static unsigned grid_for(size_t n, unsigned cap = 16384) {
     return (unsigned)g;
 }
 
+// Blocks for a kernel whose own work is `blocks` blocks and which also clears a word per vertex: one for
+// each 8192 vertices at least, as a few pairs may come with many vertices (with one block, three
+// pairs on 2^24 vertices took 4.2 ms in all, now 0.96).
+static unsigned clearing_grid(unsigned blocks, int32_t n, unsigned cap) {
+    const unsigned clear = ((unsigned)n + 8191u) / 8192u;
+    return std::min(std::max(blocks, clear), cap);
+}
+
 // ------------------------------------------------------------------ degree
 // Input degree = loop-free valid pairs per vertex. Device-wide atomics would
 // serialise on hub vertices, so the 2E endpoints are first partitioned by
@@ -75,7 +83,7 @@ __global__ __launch_bounds__(NT) void k_endpoints(const int2* __restrict__ edges
                                                   uint32_t ntiles, uint32_t tile_keys, RadixDigit dg,
                                                   uint32_t* __restrict__ pcounts, uint32_t pf, RadixDigit pdg,
                                                   uint32_t* __restrict__ p2tot, uint32_t* __restrict__ deg) {
-    // deg: zeroed on the way, for the counts to come
+    // deg: zeroed on the way, for the counts to come (null: a sort counts)
     // tile t = endpoints [t * tile_keys, (t + 1) * tile_keys) = pairs [t * EPT, (t + 1) * EPT),
     // in rounds of NT * PER pairs; with counts set, the first digit of the endpoint sort is
     // counted per tile. With pcounts set, the digit pdg of the first id is counted too, per
@@ -98,7 +106,8 @@ __global__ __launch_bounds__(NT) void k_endpoints(const int2* __restrict__ edges
     if (FOLD) s_p[threadIdx.x] = s_q[threadIdx.x] = 0;
     const int up = FOLD ? pdg.shift - dg.shift : 0;
     __syncthreads();
-    for (int64_t v = (int64_t)blockIdx.x * NT + threadIdx.x; v < n; v += (int64_t)gridDim.x * NT) deg[v] = 0;
+    if (deg)
+        for (int64_t v = (int64_t)blockIdx.x * NT + threadIdx.x; v < n; v += (int64_t)gridDim.x * NT) deg[v] = 0;
     bool bad = false;
     uint32_t sent = 0;
     for (uint32_t pt = blockIdx.x; pt < pntiles; pt += gridDim.x) {
@@ -324,7 +333,7 @@ __device__ __forceinline__ uint32_t degree_at(const uint32_t* __restrict__ deg, 
     return OFFSETS ? deg[v + 1] - deg[v] : deg[v];
 }
 
-template <bool OFFSETS>
+template <bool OFFSETS, bool ALIKE>
 __global__ __launch_bounds__(NT) void k_vertex_keys(uint32_t* __restrict__ deg, int32_t n,
                                                     const uint32_t* __restrict__ nsent, uint32_t nblocks,
                                                     uint64_t* __restrict__ keys, uint32_t* __restrict__ counts,
@@ -352,7 +361,9 @@ __global__ __launch_bounds__(NT) void k_vertex_keys(uint32_t* __restrict__ deg, 
             }
             const uint64_t key = ((uint64_t)(d < RANK_CAP ? d : RANK_CAP) << 32) | (uint32_t)v;
             keys[v] = key;
-            tc.add((uint32_t)(key >> dg.shift) & dg.mask);
+            const uint32_t digit = (uint32_t)(key >> dg.shift) & dg.mask;
+            if (ALIKE) tc.add_shared(digit);   // most keys are those of isolated vertices
+            else tc.add(digit);
         }
         tc.flush(counts, ntiles, tile);
     }
@@ -919,6 +930,7 @@ __global__ __launch_bounds__(NBUCKET) void k_select(Ctrl* ctrl, int mode, const 
     ctrl->bend[b] = at + s_nv[b];
 }
 
+template <bool ALIKE>
 __global__ __launch_bounds__(NT) void k_vkeys_slot(const uint8_t* __restrict__ vbucket, int32_t n, const Ctrl* ctrl,
                                                    uint64_t* __restrict__ keys, uint32_t* __restrict__ counts,
                                                    uint32_t ntiles, uint32_t tile_keys, RadixDigit dg) {
@@ -934,7 +946,9 @@ __global__ __launch_bounds__(NT) void k_vkeys_slot(const uint8_t* __restrict__ v
             if (v >= (uint64_t)n) break;
             const uint64_t key = ((uint64_t)s_slot[vbucket[v]] << 32) | (uint32_t)v;
             keys[v] = key;
-            tc.add((uint32_t)(key >> dg.shift) & dg.mask);
+            const uint32_t digit = (uint32_t)(key >> dg.shift) & dg.mask;
+            if (ALIKE) tc.add_shared(digit);   // most keys are those of isolated vertices
+            else tc.add(digit);
         }
         tc.flush(counts, ntiles, tile);
     }
@@ -1142,9 +1156,11 @@ constexpr unsigned CL_MAX_BLOCKS = 4096;   // block partials live in the interse
 // last[v] += rows whose highest neighbour is v: the in-edges that the in-edge
 // grouping leaves out. Most rows end in a few hubs, so the top LAST_N ranks
 // are counted in LDS (one atomic per kept edge into the in-degrees took 689 us at
-// R-MAT 18; this takes 6).
+// R-MAT 18; this takes 6). From LAST_FEW vertices on four times the blocks, for the rows
+// themselves (2^24 vertices, few pairs: 66 -> 22 us).
 constexpr uint32_t LAST_N = 8192;
-constexpr unsigned LAST_NT = 1024, LAST_BLOCKS = 128;
+constexpr unsigned LAST_NT = 1024;
+constexpr int32_t LAST_FEW = 1 << 22;
 __global__ __launch_bounds__(LAST_NT) void k_row_last(const uint32_t* __restrict__ off,
                                                       const uint32_t* __restrict__ col, int32_t n,
                                                       uint32_t* __restrict__ last) {
@@ -1543,7 +1559,7 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
             p1_f = pt_pairs / (ep_tile / 2);
         }
         const uint32_t p1_tiles = (ep_tiles + p1_f - 1) / p1_f;
-        const unsigned eg = p1_tiles < DEG_EP_BLOCKS ? p1_tiles : DEG_EP_BLOCKS;
+        const unsigned eg = clearing_grid(p1_tiles, bucketed ? n : 0, DEG_EP_BLOCKS);
         if (p2_tot) fill_u32(p2_tot, 0u, 256, s);
         const bool fold = direct && p1_counts;
         hipLaunchKernelGGL((ep_digits > 256u && direct ? (fold ? k_endpoints<512, true> : k_endpoints<512, false>)
@@ -1552,7 +1568,8 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
                            edges, (uint64_t)E, n,
                            bucketed ? (uint32_t)(n - 1) : (uint32_t)n, direct ? nullptr : ep, ctrl, partial,
                            ep_sort ? radix_first_counts(radix_tmp) : nullptr, ep_tiles, ep_tile, ep_dg, p1_counts,
-                           p1_f, RadixDigit{vbits - ORIENT_PART_BITS, (1u << ORIENT_PART_BITS) - 1u}, p2_tot, deg);
+                           p1_f, RadixDigit{vbits - ORIENT_PART_BITS, (1u << ORIENT_PART_BITS) - 1u}, p2_tot,
+                           bucketed ? deg : nullptr);
         if (direct) {
             const uint32_t* tot = partition_endpoints(edges, (size_t)E, n, (uint32_t)(n - 1), ep_dg, (uint16_t*)ep,
                                                       radix_tmp, s);
@@ -1585,6 +1602,10 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         }
     }
     mark(1);
+    // Few pairs on many vertices: the digits of most vertex keys are alike, and a wave's adds to one counter
+    // take a turn each (3 pairs on 2^24 vertices: 20 us in each of the two kernels that count them). Otherwise
+    // looking for that costs more than it saves (R-MAT 16 with t[v] 427 -> 429 us).
+    const bool alike = 2 * E < (int64_t)n;
     // ---- rank: sort (degree, id); degrees are below 2E + 1
     const Chunking uc = chunking((uint64_t)E);   // of the unique pass, whose counts k_rank clears
     {
@@ -1596,11 +1617,11 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         const RadixDigit v_dg = radix_first_digit(32, 32 + dbits);
         uint32_t* v_counts = radix_first_counts(radix_tmp);
         if (bucketed)
-            hipLaunchKernelGGL(k_vertex_keys<false>, vg, dim3(NT), 0, s, deg, n, partial, nsent_blocks, vkeysA,
-                               v_counts, v_tiles, v_tile, v_dg);
+            hipLaunchKernelGGL((alike ? k_vertex_keys<false, true> : k_vertex_keys<false, false>), vg, dim3(NT), 0, s,
+                               deg, n, partial, nsent_blocks, vkeysA, v_counts, v_tiles, v_tile, v_dg);
         else
-            hipLaunchKernelGGL(k_vertex_keys<true>, vg, dim3(NT), 0, s, deg, n, partial, 0u, vkeysA, v_counts,
-                               v_tiles, v_tile, v_dg);
+            hipLaunchKernelGGL((alike ? k_vertex_keys<true, true> : k_vertex_keys<true, false>), vg, dim3(NT), 0, s,
+                               deg, n, partial, 0u, vkeysA, v_counts, v_tiles, v_tile, v_dg);
         const int alt = radix_sort_u64(vkeysA, vkeysB, nullptr, nullptr, nullptr, (size_t)n, 32, 32 + dbits,
                                        radix_tmp, s, true, false, &ctrl->err);
         const dim3 rg(grid_for((size_t)n));
@@ -1684,7 +1705,7 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         // sort's first pass only partitions.
         const CscPacking pk = csc_packing(E, n, groups_wanted(r));
         auto csc_keys = pk.fbit ? k_csc_keys<true> : k_csc_keys<false>;
-        hipLaunchKernelGGL(csc_keys, dim3(e_tiles < 16384u ? e_tiles : 16384u), dim3(NT), 0, s, col, src, off,
+        hipLaunchKernelGGL(csc_keys, dim3(clearing_grid(e_tiles, n, 16384u)), dim3(NT), 0, s, col, src, off,
                            ctrl, n, other, pk.sh, pk.lbits, pk.fbit ? grp_first((uint32_t)n) : 0u,
                            radix_first_counts(radix_tmp), e_tiles, e_tile, radix_first_digit(pk.sh, pk.sh + nbv),
                            rowend);
@@ -1729,8 +1750,9 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
     {
         const uint32_t v_tile = radix_tile_keys((size_t)n, 8);
         const uint32_t v_tiles = (uint32_t)(((uint64_t)n + v_tile - 1) / v_tile);
-        hipLaunchKernelGGL(k_vkeys_slot, dim3(v_tiles < 16384u ? v_tiles : 16384u), dim3(NT), 0, s, vbucket, n, ctrl,
-                           vkeysA, radix_first_counts(radix_tmp), v_tiles, v_tile, radix_first_digit(32, 40));
+        hipLaunchKernelGGL((alike ? k_vkeys_slot<true> : k_vkeys_slot<false>), dim3(v_tiles < 16384u ? v_tiles : 16384u),
+                           dim3(NT), 0, s, vbucket, n, ctrl, vkeysA, radix_first_counts(radix_tmp), v_tiles, v_tile,
+                           radix_first_digit(32, 40));
         const int a3 = radix_sort_u64(vkeysA, vkeysB, nullptr, nullptr, nullptr, (size_t)n, 32, 40, radix_tmp, s,
                                       true, false, &ctrl->err);
         hipLaunchKernelGGL(k_ntiles, dim3(grid_for((size_t)n)), dim3(NT), 0, s, a3 ? vkeysB : vkeysA, vlist, vbucket,
@@ -1767,7 +1789,7 @@ hipError_t run_pipeline(const RunArgs& r, RunResult* out) {
         hipLaunchKernelGGL(k_map_pv, dim3(grid_for((size_t)n)), dim3(NT), 0, s, pv, inv, n, r.per_middle);
     if (r.clustering) {   // the degree offsets are dead by now: reuse them
         fill_u32(deg, 0u, (size_t)n, s);
-        hipLaunchKernelGGL(k_row_last, dim3(LAST_BLOCKS), dim3(LAST_NT), 0, s, off, col, n, deg);
+        hipLaunchKernelGGL(k_row_last, dim3(n < LAST_FEW ? 128 : 512), dim3(LAST_NT), 0, s, off, col, n, deg);
         const unsigned g = grid_for((size_t)n, CL_MAX_BLOCKS);
         hipLaunchKernelGGL(k_clustering, dim3(g), dim3(NT), 0, s, pv, inv, off, inoff, deg, n, r.clustering,
                            partials);
