@@ -106,6 +106,9 @@ __global__ __launch_bounds__(256) void k_mlp_cast(const float* __restrict__ mast
 }
 
 constexpr int NET_NT = 256, NET_S = NET_NT / NET_G;   // threads and samples per block round
+// Blocks of a forward pass: each loads the network once and takes its samples in rounds (65,536 samples,
+// whole call: a block per round 37.0 us, 1024 blocks 34.8, 512 32.7, 256 33.7; a thread per sample 33.5).
+constexpr int FWD_BLOCKS = 512;
 
 __global__ __launch_bounds__(NET_NT) void k_mlp_forward(const MlpCompute* __restrict__ cw,
                                                         const float* __restrict__ X, int B,
@@ -113,12 +116,14 @@ __global__ __launch_bounds__(NET_NT) void k_mlp_forward(const MlpCompute* __rest
     __shared__ MlpShared S;
     load_net(cw, S);
     const int j = threadIdx.x % NET_G, lane0 = lane_id() - j;
-    const int s = blockIdx.x * NET_S + threadIdx.x / NET_G;
-    const int sr = s < B ? s : B - 1;   // groups past the end repeat the last sample: shuffles need whole waves
-    float x[MLP_IN], h1[NET_U], h2[NET_U], z[MLP_OUT];
-    for (int i = 0; i < MLP_IN; ++i) x[i] = X[sr * MLP_IN + i];
-    net_forward(S, x, j, lane0, h1, h2, z);
-    if (s < B && j < MLP_OUT) logits[s * MLP_OUT + j] = j == 0 ? z[0] : (j == 1 ? z[1] : z[2]);
+    for (int r = blockIdx.x * NET_S; r < B; r += gridDim.x * NET_S) {
+        const int s = r + threadIdx.x / NET_G;
+        const int sr = s < B ? s : B - 1;   // groups past the end repeat the last sample: shuffles need whole waves
+        float x[MLP_IN], h1[NET_U], h2[NET_U], z[MLP_OUT];
+        for (int i = 0; i < MLP_IN; ++i) x[i] = X[sr * MLP_IN + i];
+        net_forward(S, x, j, lane0, h1, h2, z);
+        if (s < B && j < MLP_OUT) logits[s * MLP_OUT + j] = j == 0 ? z[0] : (j == 1 ? z[1] : z[2]);
+    }
 }
 
 // Forward, loss and backward of a block's samples, and their sum of parameter
@@ -286,8 +291,10 @@ void mlp_cast(const float* master, MlpCompute* cw, hipStream_t s) {
     hipLaunchKernelGGL(k_mlp_cast, dim3(1), dim3(256), 0, s, master, cw);
 }
 void mlp_forward(const MlpCompute* cw, const float* X, int B, float* logits, hipStream_t s) {
+    const int rounds = (B + NET_S - 1) / NET_S;
     if (B > 0)
-        hipLaunchKernelGGL(k_mlp_forward, dim3((B + NET_S - 1) / NET_S), dim3(NET_NT), 0, s, cw, X, B, logits);
+        hipLaunchKernelGGL(k_mlp_forward, dim3(rounds < FWD_BLOCKS ? rounds : FWD_BLOCKS), dim3(NET_NT), 0, s, cw, X, B,
+                           logits);
 }
 void mlp_gradient(const MlpCompute* cw, const float* X, const int32_t* y, const float* w, int B, float* part,
                   float* grad, float* loss, hipStream_t s) {
