@@ -227,7 +227,7 @@ __device__ __forceinline__ uint32_t col_at(const uint32_t* col, uint32_t i) {
 
 // Outputs of a bitmap launch: T only; also per middle vertex (one sum per vertex
 // and tile); also per in-edge counts (per-edge outputs); per-vertex counts (t[w] in LDS counters
-// for the top ranks); edge support (the hits per element of N+(v), the support of
+// for the top ranks, gathered per element of N+(v) for others where they are many); edge support (the hits per element of N+(v), the support of
 // edge vw, are gathered in LDS; an element's position in the list is the
 // position of its bitmap word's first element plus the bits before it);
 // or the triangle list (the per-entry count is the cursor of the entry's
@@ -325,7 +325,7 @@ __device__ __forceinline__ uint32_t entry_table(const uint32_t (&st_h)[EPT], con
     return nt;
 }
 
-// Six blocks of four waves fit a CU by LDS in every mode but the per-vertex (35 KB:
+// Six blocks of four waves fit a CU by LDS in every mode but the per-vertex (40 KB:
 // four) and the support one (44 KB: three); the register budget is held to the same occupancy (80 VGPRs).
 template <int MODE, bool NARROW>
 __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT ? 3 : 6)) void k_isect_bitmap(
@@ -342,11 +342,25 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
     constexpr uint32_t BITS = (uint32_t)WORDS * 32u;
     constexpr bool need_cnt = MODE != BM_COUNT && MODE != BM_MIDDLE && !CLIP;
     __shared__ uint32_t s_hot[VERTEX ? HOT_N : 1];
-    __shared__ uint32_t s_wc[SUPPORT ? NV_MAX : 1];       // hits per element of N+(v)
-    __shared__ uint16_t s_first[SUPPORT ? WORDS : 1];  // position in N+(v) of a word's first element
+    // Hits per element of N+(v). In the per-vertex mode of those that have no counter in s_hot ("cold"), two
+    // to a word (a tile has at most CHUNK_MAX in-edges of v), in a tile that follows one of at least
+    // COLD_HITS cold hits per element of its lists in this block: where triangles are dense and not held by a few
+    // vertices, one device-wide add per cold hit is what bounds the kernel (t[v] of 300 cliques of 500 vertices
+    // 105 ms, now 21; of a geometric graph of 2^20 vertices and degree 100 56 ms, now 37.5; R-MAT 22 20.5 and
+    // 17.4), elsewhere the set-up costs more than it saves (R-MAT 18 with coefficients 0.99 ms, with it
+    // everywhere 1.05). COLD_HITS 2: R-MAT 22 18.0 ms, the others alike.
+    constexpr uint32_t COLD_HITS = 1;
+    static_assert(CHUNK_MAX < 65536, "a tile's hits of an element fit 16 bits");
+    __shared__ uint32_t s_wc[SUPPORT ? NV_MAX : (VERTEX ? NV_MAX / 2 : 1)];
+    __shared__ uint32_t s_cold;            // cold hits of the block's last tile
+    uint32_t cold = 0, cold_nb = 0;        // this thread's; the elements of the tile's lists
+    // position in N+(v) of the first element of a word, or (per-vertex mode: all that four
+    // blocks per CU leave) of eight
+    constexpr int FIRST_LOG2 = SUPPORT ? 5 : 8;
+    __shared__ uint16_t s_first[SUPPORT ? WORDS : (VERTEX ? WORDS / 8 : 1)];
     const Hot hot = {VERTEX ? s_hot : nullptr, a.hot_first};
     if (VERTEX) hot.clear();
-    __shared__ uint32_t bm[WORDS + 1];        // + one always-zero word for out-of-window positions
+    __shared__ __align__(16) uint32_t bm[WORDS + 1];   // + one always-zero word for out-of-window positions
     __shared__ uint16_t s_wst[WT_MAX];           // entry holding the first item of each window of a chunk
     __shared__ uint32_t s_pref[CHUNK_MAX + 1];
     __shared__ uint32_t s_cnt[need_cnt ? CHUNK_MAX : 1];
@@ -365,7 +379,10 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
     const bool ranges = RANGES && a.hub && a.hub->used != 0;
     if (ranges) ntile = a.hub->rest_pref[NBUCKET];
     for (uint32_t i = blockIdx.x; i < ntile; i = grab_tile(a.ctrl, KER_BITMAP, gridDim.x, &s_tile)) {
+        const bool dense = VERTEX && cold_nb != 0 && s_cold >= COLD_HITS * cold_nb;   // grab_tile's barriers are between
         const uint32_t nseg = load_tile(a, ranges ? range_tile(a.hub->rest_tile, a.hub->rest_pref, i) : t_begin + i, S);
+        if (VERTEX && threadIdx.x == 0) s_cold = 0;   // read by all before load_tile's barrier
+        cold_nb = 0;
         for (uint32_t sg = 0; sg < nseg; ++sg) {
             const uint32_t v = S.v[sg];
             const uint32_t e0 = S.e0[sg];
@@ -391,9 +408,10 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
             const uint32_t lo = a.col[b0], hi = a.col[b1 - 1];
             const uint32_t base = lo & ~31u;
             const uint32_t nwin = (hi - base) / BITS + 1;
-            const bool gather = SUPPORT && nb <= (uint32_t)NV_MAX;
+            const bool gather = nb <= (uint32_t)NV_MAX &&
+                                (SUPPORT || (dense && lo < a.hot_first));
             if (gather)
-                for (uint32_t j = threadIdx.x; j < nb; j += IS_NT) s_wc[j] = 0u;
+                for (uint32_t j = threadIdx.x; j < (SUPPORT ? nb : (nb + 1u) / 2u); j += IS_NT) s_wc[j] = 0u;
             __syncthreads();
             // clipped tails: each entry keeps a cursor (st_h, with len_h left) and the
             // value under it, so a window that holds none of its elements costs no load
@@ -448,8 +466,8 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
                     const uint32_t x = a.col[b0 + j] - wlo;
                     if (x < BITS) {
                         atomicOr(&bm[x >> 5], 1u << (x & 31u));
-                        if (gather && (j == 0 || (a.col[b0 + j - 1] - wlo) >> 5 != x >> 5))
-                            s_first[x >> 5] = (uint16_t)j;
+                        if (gather && (j == 0 || (a.col[b0 + j - 1] - wlo) >> FIRST_LOG2 != x >> FIRST_LOG2))
+                            s_first[x >> FIRST_LOG2] = (uint16_t)j;
                     }
                 }
                 __syncthreads();
@@ -580,6 +598,7 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
                         // counts alone: 60 million uniform pairs on 300,000 vertices 16.7 ms, now 13.6)
                         const bool by_window = MODE != BM_LIST && W + WAVE * UNROLL <= lim &&
                                                __popcll(__ballot(hits != 0)) >= 8;
+                        uint32_t colds = 0;   // windows in which this lane has a cold hit
 #pragma unroll
                         for (int j = 0; j < UNROLL; ++j) {
                             const uint32_t x = xs[j];
@@ -599,13 +618,44 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
                                 } else if (!by_window) {
                                     atomicAdd(&s_cnt[ks[j]], 1u);
                                 }
-                                if (VERTEX) hot.add(a, x + wlo, 1u);
+                                if (VERTEX) {
+                                    if (x + wlo >= a.hot_first) {
+                                        atomicAdd(&s_hot[x + wlo - a.hot_first], 1u);
+                                    } else {
+                                        colds |= 1u << j;
+                                    }
+                                }
                                 if (SUPPORT) {   // edge (u, w): the tail element's own position
                                     atomicAdd(&a.support[s_base[ks[j]] + W + (uint32_t)j * WAVE + ln], 1u);
                                     if (gather)   // w's place in N+(v), flushed per vertex
                                         atomicAdd(&s_wc[s_first[x >> 5] + __popc(wd[j] & ((1u << (x & 31u)) - 1u))], 1u);
                                     else
                                         atomicAdd(&a.support[b0 + find_pos(a.col + b0, nb, x + wlo)], 1u);
+                                }
+                            }
+                        }
+                        while (VERTEX && __ballot(colds != 0)) {   // one per lane and step
+                            if (colds != 0) {
+                                const uint32_t jj = (uint32_t)__ffs((int)colds) - 1u;
+                                colds &= colds - 1u;
+                                ++cold;
+                                uint32_t x = xs[0];
+#pragma unroll
+                                for (int j = 1; j < UNROLL; ++j) x = jj == (uint32_t)j ? xs[j] : x;
+                                if (gather) {
+                                    // x's place in N+(v): elements before its eight words, in those before its own,
+                                    // and below it there
+                                    const uint32_t w = (x >> 5) & 7u, below = (1u << (x & 31u)) - 1u;
+                                    const uint4* eight = (const uint4*)&bm[(x >> 8) * 8u];
+                                    const uint4 p = eight[0], q = eight[1];
+                                    const uint32_t word[8] = {p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w};
+                                    uint32_t at = s_first[x >> FIRST_LOG2];
+#pragma unroll
+                                    for (uint32_t i = 0; i < 8; ++i)
+                                        at += (uint32_t)__popc(word[i] & (i < w ? ~0u : (i == w ? below : 0u)));
+                                    atomicAdd(&s_wc[at >> 1], 1u << (16u * (at & 1u)));
+                                } else {
+                                    atomicAdd((unsigned long long*)&a.per_vertex[x + wlo], 1ull);
                                 }
                             }
                         }
@@ -637,8 +687,10 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
             }
             if (gather) {
                 for (uint32_t j = threadIdx.x; j < nb; j += IS_NT) {
-                    const uint32_t c = s_wc[j];
-                    if (c) atomicAdd(&a.support[b0 + j], c);
+                    const uint32_t c = SUPPORT ? s_wc[j] : (s_wc[j >> 1] >> (16u * (j & 1u))) & 0xFFFFu;
+                    if (!c) continue;
+                    if (SUPPORT) atomicAdd(&a.support[b0 + j], c);
+                    else atomicAdd((unsigned long long*)&a.per_vertex[a.col[b0 + j]], (unsigned long long)c);
                 }
             }
             if (VERTEX) {   // t[u] per in-edge, t[v] once per wave
@@ -650,6 +702,7 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
                 }
                 mine = wave_sum(mine);
                 if (lane_id() == 0 && mine) hot.add(a, v, mine);
+                cold_nb += nb;
             } else if (need_cnt) {
                 for (uint32_t k = threadIdx.x; k < nt; k += IS_NT)
                     edge_done(a, hot, s_base[k] + s_pref[k] - 1u, v, s_cnt[k]);
@@ -661,6 +714,11 @@ __global__ __launch_bounds__(IS_NT, MODE == BM_VERTEX ? 4 : (MODE == BM_SUPPORT 
                     atomicAdd((unsigned long long*)&a.per_middle[v], (unsigned long long)total);
             }
             __syncthreads();
+        }
+        if (VERTEX && __ballot(cold != 0)) {
+            cold = wave_sum(cold);
+            if (lane_id() == 0) atomicAdd(&s_cold, cold);
+            cold = 0;
         }
     }
     if (VERTEX) {
